@@ -35,6 +35,12 @@ __host__ __device__ inline uint32_t pack_row(int64_t e0, int64_t count) {
 constexpr int kNoAllocFlagWords = 16;
 constexpr int kNoAllocWords = kNoAllocFlagWords + 64 * kMaxK * 6;
 
+// Copies of an instance's line-search sums, one per XCD (workgroups go round
+// robin over the 8 XCDs), added up by whoever reads them: [inst][copy][K][2][3]
+// words.  Atomics on one copy from every workgroup took longer than the
+// evaluation itself.
+constexpr int kLsReps = 8;
+
 // One shortest-path label word: (not-queued flag << 31) | FP32 bits of the
 // distance.
 typedef uint32_t label_t;
@@ -167,15 +173,25 @@ hipError_t launch_gap_decide(hipStream_t s, int ninst, const long long* acc, Ins
 hipError_t launch_ls_begin(hipStream_t s, int ninst, InstState* st, double* alphas, int K, int ls_mode,
                            double dx, long long* ls_acc, int only_fallback);
 
-hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y,
-                          double alpha_b, int beta, int K, const double* alphas, long long* ls_acc,
-                          const InstState* st, int only_pending, int* err, int k0 = 0, int kstride = 0);
+// How a line-search pass is decided.  on: by the last workgroup of each
+// instance's pass itself, counted in ticket[instance] (zero between passes).
+struct LsRule {
+    int on, K, mode, passes, max_ls;     // mode: 0 K-section, 1 quasi-Newton
+    double T1, T2, dx;
+    unsigned int* ticket;
+};
 
-hipError_t launch_ls_decide(hipStream_t s, int ninst, InstState* st, double* alphas, int K, int ls_mode,
-                            int passes, int max_ls, double T1, double T2, double dx, long long* ls_acc);
+// rule.on needs st, and K = rule.K step sizes in this one launch
+hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y,
+                          double alpha_b, int beta, int K, double* alphas, long long* ls_acc,
+                          InstState* st, int only_pending, int* err, const LsRule& rule, int k0 = 0,
+                          int kstride = 0, int reps = kLsReps);
+
+hipError_t launch_ls_decide(hipStream_t s, int ninst, InstState* st, double* alphas, const LsRule& rule,
+                            long long* ls_acc);
 
 hipError_t launch_stall_check(hipStream_t s, int ninst, InstState* st, int fixed_iters);
-hipError_t launch_ls_export(hipStream_t s, int ninst, const long long* ls_acc, int K, int64_t* sums);
+hipError_t launch_ls_export(hipStream_t s, int ninst, const long long* ls_acc, int K, int reps, int64_t* sums);
 // device address of the static scratch of the allocation-free line search on
 // `device` (which must be current); looked up once per device
 hipError_t noalloc_scratch(int device, long long** out);

@@ -53,6 +53,9 @@ __device__ __forceinline__ int32_t ld_coherent(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Every access this wavefront has issued (atomics without a result too) is done.
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // round-half-even(x * 2^16) as int128; flags values that are not finite or
 // beyond the int128 range.
 __device__ __forceinline__ i128 quant(double x, int& bad) {
@@ -62,16 +65,26 @@ __device__ __forceinline__ i128 quant(double x, int& bad) {
 }
 
 // Exact int128 accumulation with 64-bit atomics: the value is kept as three
-// chunk sums, v = c2 * 2^84 + c1 * 2^42 + c0, each term split into a signed
-// top part and two non-negative 42-bit parts.
+// signed chunk sums, v = c2 * 2^84 + c1 * 2^42 + c0.  A term takes as few of
+// them as it needs (each part below 2^42 in size, so 2^20 terms fit a chunk):
+// atomics on one line run one after another, about 12 ns each.
 __device__ __forceinline__ void acc3_add(long long* acc, i128 v) {
+    const i128 one = 1;
+    if (v > -(one << 42) && v < (one << 42)) {
+        if (v != 0) atomicAdd((unsigned long long*)&acc[0], (unsigned long long)(long long)v);
+        return;
+    }
     const unsigned long long m42 = (1ull << 42) - 1;
-    unsigned long long lo = (unsigned long long)v & m42;
-    unsigned long long mid = (unsigned long long)(v >> 42) & m42;
-    long long hi = (long long)(v >> 84);
+    const unsigned long long lo = (unsigned long long)v & m42;
     if (lo) atomicAdd((unsigned long long*)&acc[0], lo);
+    v >>= 42;
+    if (v > -(one << 42) && v < (one << 42)) {
+        atomicAdd((unsigned long long*)&acc[1], (unsigned long long)(long long)v);
+        return;
+    }
+    const unsigned long long mid = (unsigned long long)v & m42;
     if (mid) atomicAdd((unsigned long long*)&acc[1], mid);
-    if (hi) atomicAdd((unsigned long long*)&acc[2], (unsigned long long)hi);
+    atomicAdd((unsigned long long*)&acc[2], (unsigned long long)(long long)(v >> 42));
 }
 
 __device__ __forceinline__ i128 acc3_value(const long long* acc) {
@@ -86,6 +99,33 @@ __device__ __forceinline__ void put128(long long* out, i128 v) {
 __device__ __forceinline__ i128 get128(const long long* in) {
     return (i128)(((unsigned __int128)(unsigned long long)in[1] << 64) | (unsigned long long)in[0]);
 }
+
+// Exact sums of many terms rint(s), s = x * 2^16, in two doubles: H takes the
+// term's multiple of 2^26 (adding 1.5 * 2^78 rounds to one), L the rest.  With
+// |term| < 2^66 and at most 2^13 terms (a workgroup's chunk has 2^11 links)
+// |H| stays below 2^79 and |L| below 2^39, so every addition is exact and the
+// order does not matter: five FP64 additions a term, where the same term as an
+// int128 took the compiler's double -> int128 conversion and a 4-word add.
+// A larger term goes straight to the global accumulator; one beyond the int128
+// range (or not finite) sets bad, as quant does.
+struct XSum {
+    double H = 0.0, L = 0.0;
+};
+constexpr double kXSplit = 453347182355485940514816.0;    // 1.5 * 2^78
+constexpr double kXLimit = 73786976294838206464.0;        // 2^66
+__device__ __forceinline__ void xsum_add(XSum& a, double s, long long* acc, int& bad) {
+    const double v = __builtin_rint(s);
+    if (__builtin_fabs(v) < kXLimit) {
+        const double h = (v + kXSplit) - kXSplit;
+        a.H += h;
+        a.L += v - h;
+    } else if (__builtin_fabs(v) < 1.7e38) {
+        acc3_add(acc, (i128)v);
+    } else {
+        bad = 1;
+    }
+}
+__device__ __forceinline__ i128 xsum_value(const XSum& a) { return (i128)a.H + (i128)a.L; }
 
 // Workgroup sum of one int128 per thread, added to an exact accumulator.
 __device__ void wg_acc_add(i128 v, long long* acc, i128* lds) {
@@ -277,183 +317,322 @@ hipError_t launch_gap_decide(hipStream_t s, int ninst, const long long* acc, Ins
 // ---------------------------------------------------------------------------
 // A5: line search
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void ks_alphas(double lo, double hi, int K, double* out) {
-    for (int k = 0; k < K; ++k) out[k] = lo + ((hi - lo) * (double)k) / (double)(K - 1);
+// The K step sizes of a K-section pass over [lo, hi], one per lane.
+__device__ __forceinline__ void ks_alphas(double lo, double hi, int K, int lane, double* out) {
+    if (lane < K) out[lane] = lo + ((hi - lo) * (double)lane) / (double)(K - 1);
+}
+
+// Start the line search of iteration S.iter of one instance: one wavefront,
+// every lane with the same arguments.
+__device__ void ls_begin_wave(InstState& S, double* al, long long* acc, int K, int ls_mode, double dx, int lane) {
+    for (int k = lane; k < K * 6 * kLsReps; k += 64) acc[k] = 0;
+    if (ls_mode == 2) {                  // MSA
+        if (lane == 0) S.alpha = 1.0 / ((double)S.iter + 1.0);
+    } else if (ls_mode == 1) {           // quasi-Newton, Alg. 8 initial guess
+        const double a = 2.0 / (2.0 + (double)S.iter);
+        if (lane == 0) S.qn_alpha = a;
+        if (lane < 3) al[lane] = lane == 0 ? a - dx : lane == 1 ? a : a + dx;
+    } else {                              // K-section on [0, 1]
+        if (lane == 0) {
+            S.lo = 0.0;
+            S.hi = 1.0;
+        }
+        ks_alphas(0.0, 1.0, K, lane, al);
+    }
+    if (lane == 0) {
+        S.ls_pass = 0;
+        S.ls_done = ls_mode == 2 ? 1 : 0;
+    }
 }
 
 // Start the line search of iteration j for every live instance.
 // only_fallback: restart as K-section only the instances whose quasi-Newton
 // search met a non-positive C'' (ls_done == 2).
-__global__ void k_ls_begin(int ninst, InstState* st, double* alphas, int K, int ls_mode, double dx,
-                           long long* ls_acc, int only_fallback) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
+__global__ __launch_bounds__(64) void k_ls_begin(InstState* st, double* alphas, int K, int ls_mode, double dx,
+                                                 long long* ls_acc, int only_fallback) {
+    const int i = blockIdx.x;
     InstState& S = st[i];
     if (!S.active || S.converged) return;
     if (only_fallback && S.ls_done != 2) return;
-    S.ls_done = 0;
-    S.ls_pass = 0;
-    for (int k = 0; k < K * 6; ++k) ls_acc[(long long)i * K * 6 + k] = 0;
-    double* al = alphas + (long long)i * K;
-    if (ls_mode == 2) {                  // MSA
-        S.alpha = 1.0 / ((double)S.iter + 1.0);
-        S.ls_done = 1;
-    } else if (ls_mode == 1) {           // quasi-Newton, Alg. 8 initial guess
-        double a = 2.0 / (2.0 + (double)S.iter);
-        S.qn_alpha = a;
-        al[0] = a - dx; al[1] = a; al[2] = a + dx;
-    } else {                              // K-section on [0, 1]
-        S.lo = 0.0; S.hi = 1.0;
-        ks_alphas(0.0, 1.0, K, al);
-    }
+    ls_begin_wave(S, alphas + (long long)i * K, ls_acc + (long long)i * K * 6 * kLsReps, K, ls_mode, dx,
+                  (int)threadIdx.x);
 }
 
 hipError_t launch_ls_begin(hipStream_t s, int ninst, InstState* st, double* alphas, int K, int ls_mode, double dx,
                            long long* ls_acc, int only_fallback) {
-    hipLaunchKernelGGL(k_ls_begin, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, st, alphas, K, ls_mode, dx,
-                       ls_acc, only_fallback);
+    hipLaunchKernelGGL(k_ls_begin, dim3(ninst), dim3(64), 0, s, st, alphas, K, ls_mode, dx, ls_acc, only_fallback);
     return hipGetLastError();
 }
 
-// One pass over the links: C(alpha_k) and C'(alpha_k) for all k at once.
-// Lanes of a group take the K step sizes of one link; a workgroup covers
-// kWG / GK links per step over a 2048-link chunk of one instance.
-template <int GK>
-__global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __restrict__ f,
-                                                 const int64_t* __restrict__ y, double alpha_b, int beta, int K,
-                                                 const double* __restrict__ alphas, long long* ls_acc,
-                                                 const InstState* st, int only_pending, int* err, int k0, int kstride) {
-    __shared__ i128 ldsC[kWG];
-    __shared__ i128 ldsD[kWG];
-    constexpr int LPB = kWG / GK;
-    const int b = blockIdx.x;
-    const int inst = net.blk_inst[b];
-    if (st && (!st[inst].active || st[inst].converged || (only_pending && st[inst].ls_done))) return;
-    const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    const int k = threadIdx.x % GK;
-    const int g = threadIdx.x / GK;
-    const bool live = k < K;
-    const double alpha = live ? alphas[(long long)inst * kstride + k0 + k] : 0.0;
-    i128 sc = 0, sd = 0;
-    int bad = 0;
-    if (live) {
-        for (int a = a0 + g; a < a1; a += LPB) {
-            double obj, der;
-            ls_terms((double)f[a] * kFxInv, (double)y[a] * kFxInv, net.c0[a], net.cap[a], alpha_b, beta, I.kappa,
-                     alpha, net.objective, obj, der);
-            sc += quant(obj, bad);
-            sd += quant(der, bad);
-        }
-    }
-    if (bad) atomicOr(err, 1);
-    ldsC[threadIdx.x] = sc;
-    ldsD[threadIdx.x] = sd;
-    __syncthreads();
-    for (int s = LPB / 2; s > 0; s >>= 1) {
-        if (g < s) {
-            ldsC[threadIdx.x] += ldsC[threadIdx.x + s * GK];
-            ldsD[threadIdx.x] += ldsD[threadIdx.x + s * GK];
-        }
-        __syncthreads();
-    }
-    if (g == 0 && live) {
-        long long* acc = ls_acc + ((long long)inst * kstride + k0 + k) * 6;
-        if (ldsC[threadIdx.x] != 0) acc3_add(acc, ldsC[threadIdx.x]);
-        if (ldsD[threadIdx.x] != 0) acc3_add(acc + 3, ldsD[threadIdx.x]);
-    }
-}
-
-hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b,
-                          int beta, int K, const double* alphas, long long* ls_acc, const InstState* st,
-                          int only_pending, int* err, int k0, int kstride) {
-    if (net.nblk == 0) return hipSuccess;
-    if (kstride <= 0) kstride = K;
-    dim3 g(net.nblk), blk(kWG);
-    if (K <= 1)
-        hipLaunchKernelGGL(k_ls_eval<1>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st, only_pending,
-                           err, k0, kstride);
-    else if (K <= 4)
-        hipLaunchKernelGGL(k_ls_eval<4>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st, only_pending,
-                           err, k0, kstride);
-    else if (K <= 8)
-        hipLaunchKernelGGL(k_ls_eval<8>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st, only_pending,
-                           err, k0, kstride);
-    else if (K <= 16)
-        hipLaunchKernelGGL(k_ls_eval<16>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st,
-                           only_pending, err, k0, kstride);
-    else if (K <= 32)
-        hipLaunchKernelGGL(k_ls_eval<32>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st,
-                           only_pending, err, k0, kstride);
-    else
-        hipLaunchKernelGGL(k_ls_eval<64>, g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st,
-                           only_pending, err, k0, kstride);
-    return hipGetLastError();
-}
-
-// Decide after a pass: K-section bracket update (root of C', C convex in
-// alpha), or one quasi-Newton step (Alg. 8 with Eq. 10).
-__global__ void k_ls_decide(int ninst, InstState* st, double* alphas, int K, int ls_mode, int passes, int max_ls,
-                            double T1, double T2, double dx, long long* ls_acc) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
-    InstState& S = st[i];
-    if (!S.active || S.converged || S.ls_done) return;
-    long long* acc = ls_acc + (long long)i * K * 6;
-    double* al = alphas + (long long)i * K;
-    S.ls_evals++;
-    S.ls_pass++;
-    if (ls_mode == 0) {
-        int kk = -1;
-        for (int k = 0; k < K; ++k)
-            if (acc3_value(acc + k * 6 + 3) >= 0) { kk = k; break; }
-        if (kk == 0) { S.alpha = al[0]; S.ls_done = 1; }
-        else if (kk < 0) { S.alpha = al[K - 1]; S.ls_done = 1; }
-        else {
-            S.lo = al[kk - 1];
-            S.hi = al[kk];
-            put128(S.dlo, acc3_value(acc + (kk - 1) * 6 + 3));
-            put128(S.dhi, acc3_value(acc + kk * 6 + 3));
-            if (S.ls_pass >= passes) {
-                double a = S.lo, bb = S.hi;
-                double da = (double)get128(S.dlo), db = (double)get128(S.dhi);
-                S.alpha = a - (da * (bb - a)) / (db - da);
-                S.ls_done = 1;
+// Decide after a pass over the links: K-section bracket update (root of C', C
+// convex in alpha), or one quasi-Newton step (Alg. 8 with Eq. 10).  One
+// wavefront per instance, lane k with the sums of step size k (K <= 64): read
+// one after another by one thread they took 8.6 us at K = 32.  The sums are
+// read coherently, so the last workgroup of a pass may decide.
+__device__ void ls_decide_wave(InstState& S, double* al, long long* acc, const LsRule& R, int lane) {
+    const int K = R.K;
+    auto sum_of = [&](int k, int which) -> i128 {
+        long long c[3] = {0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < kLsReps; ++r)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                c[j] += __hip_atomic_load(acc + (r * K + k) * 6 + which * 3 + j, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+        return acc3_value(c);
+    };
+    auto from = [&](i128 v, int src) -> i128 {
+        long long w[2];
+        put128(w, v);
+        w[0] = __shfl(w[0], src);
+        w[1] = __shfl(w[1], src);
+        return get128(w);
+    };
+    int done = 0;
+    const int pass = S.ls_pass + 1;
+    double alpha = 0.0;
+    if (R.mode == 0) {
+        const i128 d = lane < K ? sum_of(lane, 1) : 0;
+        const unsigned long long up = __ballot(lane < K && d >= 0);
+        const int kk = up ? __ffsll(up) - 1 : -1;
+        if (kk <= 0) {                     // the root lies at or outside an end
+            alpha = al[kk == 0 ? 0 : K - 1];
+            done = 1;
+        } else {
+            const double lo = al[kk - 1], hi = al[kk];
+            const i128 dlo = from(d, kk - 1), dhi = from(d, kk);
+            if (pass >= R.passes) {
+                const double da = (double)dlo, db = (double)dhi;
+                alpha = lo - (da * (hi - lo)) / (db - da);
+                done = 1;
             } else {
-                ks_alphas(S.lo, S.hi, K, al);
+                ks_alphas(lo, hi, K, lane, al);
+            }
+            if (lane == 0) {
+                S.lo = lo;
+                S.hi = hi;
+                put128(S.dlo, dlo);
+                put128(S.dhi, dhi);
             }
         }
     } else {
-        S.qn_iters++;
-        double cm = (double)acc3_value(acc + 0) / kSumQ;
-        double c0v = (double)acc3_value(acc + 6) / kSumQ;
-        double cp = (double)acc3_value(acc + 12) / kSumQ;
-        double d1 = (cp - cm) / (2.0 * dx);
-        double d2 = ((cm - 2.0 * c0v) + cp) / (dx * dx);
-        double a = S.qn_alpha;
-        if (__builtin_fabs(d1) < T1) { S.alpha = a; S.ls_done = 1; }
-        else if (!(d2 > 0.0)) { S.ls_done = 2; }          // fall back to K-section
+        const i128 c = lane < 3 ? sum_of(lane, 0) : 0;
+        const double cm = (double)from(c, 0) / kSumQ;
+        const double c0v = (double)from(c, 1) / kSumQ;
+        const double cp = (double)from(c, 2) / kSumQ;
+        const double d1 = (cp - cm) / (2.0 * R.dx);
+        const double d2 = ((cm - 2.0 * c0v) + cp) / (R.dx * R.dx);
+        const double a = S.qn_alpha;
+        if (lane == 0) S.qn_iters++;
+        if (__builtin_fabs(d1) < R.T1) { alpha = a; done = 1; }
+        else if (!(d2 > 0.0)) { done = 2; }               // fall back to K-section
         else {
             double an = a - d1 / d2;
             if (an < 0.0) an = 0.0;
             if (an > 1.0) an = 1.0;
-            if (__builtin_fabs(an - a) < T2) { S.alpha = an; S.ls_done = 1; }
-            else if (S.ls_pass >= max_ls) { S.alpha = an; S.ls_done = 1; }
+            if (__builtin_fabs(an - a) < R.T2 || pass >= R.max_ls) { alpha = an; done = 1; }
             else {
-                S.qn_alpha = an;
-                al[0] = an - dx; al[1] = an; al[2] = an + dx;
+                if (lane == 0) S.qn_alpha = an;
+                if (lane < 3) al[lane] = lane == 0 ? an - R.dx : lane == 1 ? an : an + R.dx;
             }
         }
     }
-    if (!S.ls_done)
-        for (int k = 0; k < K * 6; ++k) acc[k] = 0;
+    if (!done)
+        for (int k = lane; k < K * 6 * kLsReps; k += 64) acc[k] = 0;
+    if (lane == 0) {
+        S.ls_evals++;
+        S.ls_pass = pass;
+        S.ls_done = done;
+        if (done == 1) S.alpha = alpha;
+    }
 }
 
-hipError_t launch_ls_decide(hipStream_t s, int ninst, InstState* st, double* alphas, int K, int ls_mode, int passes,
-                            int max_ls, double T1, double T2, double dx, long long* ls_acc) {
-    hipLaunchKernelGGL(k_ls_decide, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, st, alphas, K, ls_mode, passes,
-                       max_ls, T1, T2, dx, ls_acc);
+__global__ __launch_bounds__(64) void k_ls_decide(InstState* st, double* alphas, LsRule R, long long* ls_acc) {
+    const int i = blockIdx.x;
+    InstState& S = st[i];
+    if (!S.active || S.converged || S.ls_done) return;
+    ls_decide_wave(S, alphas + (long long)i * R.K, ls_acc + (long long)i * R.K * 6 * kLsReps, R, (int)threadIdx.x);
+}
+
+hipError_t launch_ls_decide(hipStream_t s, int ninst, InstState* st, double* alphas, const LsRule& R,
+                            long long* ls_acc) {
+    hipLaunchKernelGGL(k_ls_decide, dim3(ninst), dim3(64), 0, s, st, alphas, R, ls_acc);
+    return hipGetLastError();
+}
+
+// a / b correctly rounded, y = RN(1 / b): two residual corrections (Markstein's
+// theorem: the first leaves a faithful quotient, the second, whose residual is
+// then exact, the rounded one) instead of the 11 operations of a division.
+// Needs a quotient and residuals in the normal range: an infinite or NaN
+// quotient comes out as NaN (both set the overflow flag of the sums).
+template <bool FAST>
+__device__ __forceinline__ double div_by(double a, double b, double y) {
+    if (!FAST) return a / b;
+    double q = a * y;
+    q = __builtin_fma(__builtin_fma(-b, q, a), y, q);
+    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// One link as a pass over the links reads it from LDS, once for all K step
+// sizes: F, Y - F, c0 * 2^16 (the sums' scale; a power of two changes no
+// rounding), the capacity and its reciprocal.
+struct LsLink {
+    double F, t, c0q, cap, rcap;
+};
+
+// ls_terms at step size alpha, both terms times 2^16.
+template <int BETA, bool SO, bool FAST>
+__device__ __forceinline__ void ls_terms_q(const LsLink& l, double ab, int beta, double kappa, double rbeta1,
+                                           double alpha, double& obj, double& der) {
+    const double v = l.F + alpha * l.t;
+    const double r = div_by<FAST>(v * kappa, l.cap, l.rcap);
+    double p = r;
+    if (BETA > 0) {
+#pragma unroll
+        for (int k = 1; k < BETA; ++k) p = p * r;
+    } else {
+        for (int k = 1; k < beta; ++k) p = p * r;
+    }
+    const double cost = l.c0q * (1.0 + ab * p);
+    if (SO) {
+        obj = v * cost;
+        der = l.t * (l.c0q * (1.0 + (ab * (double)(beta + 1)) * p));
+        return;
+    }
+    const double g = div_by<FAST>((ab * v) * p, (double)(beta + 1), rbeta1);
+    obj = l.c0q * (v + g);
+    der = l.t * cost;
+}
+
+// One pass over the links: C(alpha_k) and C'(alpha_k) for all k at once.
+// Bound by FP64 issue: about 40 operations per (link, step size), 41 us for
+// 1.25M links x 32 at the vector rate of the card.  A workgroup takes
+// kChunk / gridDim.y links of one chunk (launch_ls_eval), stages them in LDS
+// 256 at a time, and thread (g, k) = (tid / K, tid % K) takes every
+// (kWG / K)-th link at step size k.  rule.on: the last workgroup of an
+// instance decides (the ticket counts them), which saves the decision's own
+// launch.
+constexpr int kLsTile = kWG;
+template <int BETA, bool SO>
+__global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __restrict__ f,
+                                                 const int64_t* __restrict__ y, double alpha_b, int beta, int K,
+                                                 double* alphas, long long* ls_acc, InstState* st, int only_pending,
+                                                 int* err, int k0, int kstride, int reps, LsRule rule) {
+    __shared__ LsLink s_link[kLsTile];
+    __shared__ double s_red[4][kWG];
+    __shared__ int s_last;
+    const int b = blockIdx.x;
+    const int inst = net.blk_inst[b];
+    if (st && (!st[inst].active || st[inst].converged || (only_pending && st[inst].ls_done))) return;
+    const InstDev I = net.inst[inst];
+    const int part = kChunk / (int)gridDim.y;
+    const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
+    const int a1 = min(a0 + part, I.link0 + I.m);
+    const int tid = threadIdx.x;
+    const int G = kWG / K;                    // links taken side by side
+    const int k = tid % K, g = tid / K;
+    const bool live = g < G;
+    double* al = alphas + (long long)inst * kstride + k0;
+    long long* sums = ls_acc + (long long)inst * reps * kstride * 6;     // [reps][kstride][2][3]
+    const int rep = (int)((blockIdx.y * gridDim.x + blockIdx.x) % (unsigned)reps);
+    long long* acc = sums + ((long long)rep * kstride + k0) * 6;
+    const double alpha = live ? al[k] : 0.0;
+    const double kappa = I.kappa, rbeta1 = 1.0 / (double)(beta + 1);
+    // kappa far from 1 could take the quotient out of the normal range
+    const bool fast = kappa > 0x1p-60 && kappa < 0x1p60;
+    XSum sc, sd;
+    int bad = 0;
+    for (int t0 = a0; t0 < a1; t0 += kLsTile) {
+        const int nt = min(kLsTile, a1 - t0);
+        if (tid < nt) {
+            const int a = t0 + tid;
+            LsLink l;
+            l.F = (double)f[a] * kFxInv;
+            l.t = (double)y[a] * kFxInv - l.F;
+            l.c0q = (double)net.c0[a] * kSumQ;
+            l.cap = (double)net.cap[a];
+            l.rcap = 1.0 / l.cap;
+            s_link[tid] = l;
+        }
+        __syncthreads();
+        if (live) {
+            double obj, der;
+            if (fast) {
+#pragma unroll 2
+                for (int x = g; x < nt; x += G) {
+                    ls_terms_q<BETA, SO, true>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
+                    xsum_add(sc, obj, acc + k * 6, bad);
+                    xsum_add(sd, der, acc + k * 6 + 3, bad);
+                }
+            } else {
+                for (int x = g; x < nt; x += G) {
+                    ls_terms_q<BETA, SO, false>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
+                    xsum_add(sc, obj, acc + k * 6, bad);
+                    xsum_add(sd, der, acc + k * 6 + 3, bad);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (bad) atomicOr(err, 1);
+    s_red[0][tid] = sc.H;
+    s_red[1][tid] = sc.L;
+    s_red[2][tid] = sd.H;
+    s_red[3][tid] = sd.L;
+    __syncthreads();
+    int s = 1;
+    while (s < G) s <<= 1;
+    for (s >>= 1; s > 0; s >>= 1) {
+        if (g < s && g + s < G) {
+            for (int q = 0; q < 4; ++q) s_red[q][tid] += s_red[q][tid + s * K];
+        }
+        __syncthreads();
+    }
+    // threads 0..K-1 add the objective's sums, K..2K-1 the derivative's
+    if (tid < 2 * K) {
+        const int w = tid / K, kk = tid % K;
+        XSum x;
+        x.H = s_red[2 * w][kk];
+        x.L = s_red[2 * w + 1][kk];
+        acc3_add(acc + kk * 6 + 3 * w, xsum_value(x));
+    }
+    if (!rule.on) return;
+    wait_memory();                            // this workgroup's sums are in before its ticket
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
+        s_last = atomicAdd(&rule.ticket[inst], 1u) == all - 1;
+        if (s_last) rule.ticket[inst] = 0u;
+    }
+    __syncthreads();
+    if (s_last && tid < 64) ls_decide_wave(st[inst], al, sums, rule, tid);
+}
+
+hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b,
+                          int beta, int K, double* alphas, long long* ls_acc, InstState* st, int only_pending,
+                          int* err, const LsRule& rule, int k0, int kstride, int reps) {
+    if (net.nblk == 0) return hipSuccess;
+    if (kstride <= 0) kstride = K;
+    // Workgroups per chunk: enough of them to fill the card, each thread with
+    // 16 evaluations at least (below that its reduction and atomics weigh more:
+    // 256k links at K = 3 took 36 us a pass with 1,000 workgroups, 16 with 250).
+    // A pass over 1.25M links at K = 32: 77 us (307 us with one workgroup per
+    // chunk, int128 terms and divisions); over 1,520 links, where one chunk
+    // used to be one workgroup: 8 us (114 us, and 8 us more for its decision).
+    int split = 1;
+    while (split < kChunk / 64 && (int64_t)net.nblk * split < 1024 && (kChunk / split) * K >= 16 * kWG) split *= 2;
+    const dim3 g(net.nblk, split), blk(kWG);
+#define QDTA_LS(B, SO)                                                                                             \
+    hipLaunchKernelGGL((k_ls_eval<B, SO>), g, blk, 0, s, net, f, y, alpha_b, beta, K, alphas, ls_acc, st, only_pending, \
+                       err, k0, kstride, reps, rule)
+    if (net.objective) {
+        if (beta == 4) QDTA_LS(4, true);
+        else QDTA_LS(0, true);
+    } else {
+        if (beta == 4) QDTA_LS(4, false);
+        else QDTA_LS(0, false);
+    }
+#undef QDTA_LS
     return hipGetLastError();
 }
 
@@ -472,16 +651,19 @@ hipError_t launch_stall_check(hipStream_t s, int ninst, InstState* st, int fixed
     return hipGetLastError();
 }
 
-__global__ void k_ls_export(int ninst, const long long* ls_acc, int K, int64_t* sums) {
+__global__ void k_ls_export(int ninst, const long long* ls_acc, int K, int reps, int64_t* sums) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ninst * K * 2) return;
-    i128 v = acc3_value(ls_acc + (long long)t * 3);
+    const int inst = t / (2 * K);
+    i128 v = 0;
+    for (int r = 0; r < reps; ++r)
+        v += acc3_value(ls_acc + (((long long)inst * reps + r) * K * 2 + (t - inst * 2 * K)) * 3);
     put128((long long*)sums + 2 * (long long)t, v);
 }
 
-hipError_t launch_ls_export(hipStream_t s, int ninst, const long long* ls_acc, int K, int64_t* sums) {
+hipError_t launch_ls_export(hipStream_t s, int ninst, const long long* ls_acc, int K, int reps, int64_t* sums) {
     int n = ninst * K * 2;
-    hipLaunchKernelGGL(k_ls_export, dim3((n + 63) / 64), dim3(64), 0, s, ninst, ls_acc, K, sums);
+    hipLaunchKernelGGL(k_ls_export, dim3((n + 63) / 64), dim3(64), 0, s, ninst, ls_acc, K, reps, sums);
     return hipGetLastError();
 }
 
@@ -2665,8 +2847,6 @@ hipError_t launch_walk(hipStream_t s, const NetDev& net, const DemDev& dem, cons
 // walker meets FP32 absorption is flagged; pass 2 walks its legs as k_walk
 // does (clearing the counts pass 1 left on their paths) and the tie
 // fallback finishes them.  Used only when every instance is plain.
-__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 __global__ __launch_bounds__(kWG) void k_sweep_count(NetDev net, DemDev dem, const label_t* __restrict__ labels,
                                                      const InstState* st, FlagsDev fl, uint32_t* cnt) {
     const int l = blockIdx.x * kWG + threadIdx.x;

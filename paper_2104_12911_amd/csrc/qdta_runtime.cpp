@@ -123,6 +123,7 @@ struct qdta_ctx {
     DBuf<InstState> st;
     DBuf<long long> acc, ls_acc;
     DBuf<double> alphas, alpha_arr;
+    DBuf<unsigned int> ls_ticket; // workgroups of an instance done with the current line-search pass (zero between)
     DBuf<int> flags;              // [0] overflow, [1] unreach, [2] absorb count, [3] path-record faults
     DBuf<int32_t> absorb_q, int_node;
     DBuf<float> int_tau;
@@ -493,9 +494,11 @@ int ensure_network(qdta_ctx* c) {
     RC(dalloc(c, c->tcost, c->M));
     RC(dalloc(c, c->st, ni));
     RC(dalloc(c, c->acc, (size_t)ni * 6));
-    RC(dalloc(c, c->ls_acc, (size_t)ni * kMaxK * 6));
+    RC(dalloc(c, c->ls_acc, (size_t)ni * kMaxK * 6 * kLsReps));
     RC(dalloc(c, c->alphas, (size_t)ni * kMaxK));
     RC(dalloc(c, c->alpha_arr, ni));
+    RC(dalloc(c, c->ls_ticket, ni));
+    HIPCHECK(c, launch_fill_u32(c->stream, c->ls_ticket.p, 0u, ni));
     RC(dalloc(c, c->flags, 4));
     RC(dalloc(c, c->done_fx, ni));
     if (c->h_st_n < ni) {
@@ -1147,37 +1150,31 @@ int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
     NetDev net = net_in ? *net_in : net_view(c, o);
     int ni = (int)c->inst.size();
     int* err = c->flags.p;
-    int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
+    const bool plain = o->launch_form == 2;
+    const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
+    LsRule rule{!plain, K, o->ls_mode == QDTA_LS_QN ? 1 : 0, o->passes, o->max_ls, o->T1, o->T2, o->dx, c->ls_ticket.p};
     HIPCHECK(c, launch_ls_begin(c->stream, ni, c->st.p, c->alphas.p, K, o->ls_mode, o->dx, c->ls_acc.p, 0));
     if (o->ls_mode == QDTA_LS_MSA) return QDTA_OK;
-    const bool plain = o->launch_form == 2;
-    if (o->ls_mode == QDTA_LS_KSECTION) {
-        for (int p = 0; p < o->passes; ++p) {
-            if (plain) {
-                for (int k = 0; k < K; ++k)
-                    HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, 1, c->alphas.p, c->ls_acc.p,
-                                               c->st.p, 1, err, k, K));
-            } else {
-                HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, K, c->alphas.p, c->ls_acc.p,
-                                           c->st.p, 1, err));
-            }
-            HIPCHECK(c, launch_ls_decide(c->stream, ni, c->st.p, c->alphas.p, K, 0, o->passes, o->max_ls, o->T1, o->T2,
-                                         o->dx, c->ls_acc.p));
+    // one pass over the links and its decision
+    auto pass = [&]() -> int {
+        if (!plain) {
+            HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, rule.K, c->alphas.p, c->ls_acc.p,
+                                       c->st.p, 1, err, rule));
+            return QDTA_OK;
         }
+        for (int k = 0; k < rule.K; ++k)
+            HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, 1, c->alphas.p, c->ls_acc.p, c->st.p, 1,
+                                       err, rule, k, rule.K));
+        HIPCHECK(c, launch_ls_decide(c->stream, ni, c->st.p, c->alphas.p, rule, c->ls_acc.p));
+        return QDTA_OK;
+    };
+    if (o->ls_mode == QDTA_LS_KSECTION) {
+        for (int p = 0; p < o->passes; ++p) RC(pass());
         return QDTA_OK;
     }
     // quasi-Newton (Alg. 8): iterate until every live instance is done
     for (int l = 0; l < o->max_ls; ++l) {
-        if (plain) {
-            for (int k = 0; k < 3; ++k)
-                HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, 1, c->alphas.p, c->ls_acc.p, c->st.p,
-                                           1, err, k, 3));
-        } else {
-            HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, 3, c->alphas.p, c->ls_acc.p, c->st.p, 1,
-                                       err));
-        }
-        HIPCHECK(c, launch_ls_decide(c->stream, ni, c->st.p, c->alphas.p, 3, 1, o->passes, o->max_ls, o->T1, o->T2,
-                                     o->dx, c->ls_acc.p));
+        RC(pass());
         RC(pull_state(c));
         bool pending = false, fallback = false;
         for (int i = 0; i < ni; ++i) {
@@ -1190,12 +1187,9 @@ int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
             if (fallback) {
                 // C'' <= 0: K-section for those instances (non-convex stencil)
                 HIPCHECK(c, launch_ls_begin(c->stream, ni, c->st.p, c->alphas.p, o->K, 0, o->dx, c->ls_acc.p, 1));
-                for (int p = 0; p < o->passes; ++p) {
-                    HIPCHECK(c, launch_ls_eval(c->stream, net, f, y, o->alpha, o->beta, o->K, c->alphas.p, c->ls_acc.p,
-                                               c->st.p, 1, err));
-                    HIPCHECK(c, launch_ls_decide(c->stream, ni, c->st.p, c->alphas.p, o->K, 0, o->passes, o->max_ls,
-                                                 o->T1, o->T2, o->dx, c->ls_acc.p));
-                }
+                rule.K = o->K;
+                rule.mode = 0;
+                for (int p = 0; p < o->passes; ++p) RC(pass());
             }
             break;
         }
@@ -1473,8 +1467,8 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4); add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4);
     add(nblk, 4); add(nblk, 4); add(ni, sizeof(InstDev));
     add(M, 8); add(M, 8); add(M, 4); add(M, 8); add(M, 8); add(M, 4); add(M, 4); add(M, 4);
-    add(ni, sizeof(InstState)); add((size_t)ni * 6, 8); add((size_t)ni * kMaxK * 6, 8); add((size_t)ni * kMaxK, 8);
-    add(ni, 8); add(4, 4); add(ni, 8);
+    add(ni, sizeof(InstState)); add((size_t)ni * 6, 8); add((size_t)ni * kMaxK * 6 * kLsReps, 8); add((size_t)ni * kMaxK, 8);
+    add(ni, 8); add(ni, 4); add(4, 4); add(ni, 8);
     // demand tables and shortest-path labels
     add(pq, 4); add(pq, 4); add(pq, 8); add(pq + 1, 4); add(pp, 4); add(pp, 8); add(pp, 4); add(pp, 4);
     add(labels, 4); add(pq, 4); add(pp, 4); add(pp, 4);
@@ -1812,10 +1806,10 @@ int qdta_ls_eval(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const int64_
     if (c->dem_dirty) RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
     int ni = (int)c->inst.size();
     RC(clear_flags(c));
-    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->ls_acc.p), 0, (int64_t)ni * K * 6));
-    HIPCHECK(c, launch_ls_eval(c->stream, net_view(c, o), f, y, o->alpha, o->beta, K, alphas, c->ls_acc.p, nullptr, 0,
-                               c->flags.p));
-    HIPCHECK(c, launch_ls_export(c->stream, ni, c->ls_acc.p, K, sums));
+    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->ls_acc.p), 0, (int64_t)ni * K * 6 * kLsReps));
+    HIPCHECK(c, launch_ls_eval(c->stream, net_view(c, o), f, y, o->alpha, o->beta, K, const_cast<double*>(alphas),
+                               c->ls_acc.p, nullptr, 0, c->flags.p, LsRule{}));   // no decision: alphas stay
+    HIPCHECK(c, launch_ls_export(c->stream, ni, c->ls_acc.p, K, kLsReps, sums));
     int h[4];
     RC(read_flags(c, h));
     return flag_code(c, h);
@@ -1839,8 +1833,9 @@ int qdta_ls_eval_noalloc(qdta_ctx* c, const qdta_opts* o, const int64_t* f, cons
     // the scratch keeps the last call's contents: clear the flags and the
     // accumulators this call uses (a fill kernel, safe under graph capture)
     HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->noalloc), 0, kNoAllocFlagWords + words));
-    HIPCHECK(c, launch_ls_eval(c->stream, net_view(c, o), f, y, o->alpha, o->beta, K, alphas, acc, nullptr, 0, flags));
-    HIPCHECK(c, launch_ls_export(c->stream, ni, acc, K, sums));
+    HIPCHECK(c, launch_ls_eval(c->stream, net_view(c, o), f, y, o->alpha, o->beta, K, const_cast<double*>(alphas), acc,
+                               nullptr, 0, flags, LsRule{}, 0, 0, 1));   // the static scratch holds one copy of the sums
+    HIPCHECK(c, launch_ls_export(c->stream, ni, acc, K, 1, sums));
     int h[4];
     HIPCHECK(c, hipMemcpyAsync(h, flags, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));

@@ -1,0 +1,89 @@
+"""The kernels at the sizes where their work splits change: GPU against the oracle through the C ABI.  Integer
+sums and flows are exact in any order, so the tolerance is zero throughout."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from synth.networks import Network
+
+pytestmark = pytest.mark.gpu
+
+FX = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2104_12911_amd import qdta
+    qdta.lib()
+    return qdta
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def i128(lo, hi):
+    return (int(hi) << 64) | (int(lo) & ((1 << 64) - 1))
+
+
+def parallel_links(m, rng, cap):
+    """Two nodes and m links from one to the other."""
+    return Network(2, np.array([0, m, m], np.int32), np.ones(m, np.int32),
+                   rng.uniform(1.0, 100.0, m).astype(np.float32), (cap * rng.uniform(1.0, 4.0, m)).astype(np.float32))
+
+
+# links: one, either side of a 256-link tile and of a 2,048-link chunk, several chunks; step sizes: one, a few that
+# do not divide the workgroup, the most; demand: ordinary, terms beyond 2^66 (and 2^84), an interval length whose
+# kappa is beyond 2^60 (true divisions)
+@pytest.mark.parametrize("m", [1, 63, 255, 256, 257, 2047, 2048, 2049, 70_001])
+@pytest.mark.parametrize("K,beta,objective", [(1, 4, 0), (3, 4, 1), (7, 3, 0), (32, 4, 0), (33, 16, 1), (64, 1, 1)])
+def test_line_search_sums_at_split_edges(q, orc, m, K, beta, objective):
+    import torch
+    rng = np.random.default_rng(m * 100 + K)
+    for kind in ("ordinary", "large", "short"):
+        if kind == "large" and beta > 4:
+            continue
+        if kind == "short" and beta != 1:
+            continue
+        net = parallel_links(m, rng, 900.0 if kind != "large" else 10.0)
+        veh = {"ordinary": 300.0, "large": 1e5, "short": 1e-3}[kind]
+        dt = {"ordinary": 900.0, "large": 900.0, "short": 1e-16}[kind]
+        f = (rng.uniform(0.0, veh, m) * FX).astype(np.int64)
+        y = (rng.uniform(0.0, veh, m) * FX).astype(np.int64) * rng.integers(0, 2, m)
+        alphas = np.linspace(0.0, 1.0, K) if K > 1 else np.array([0.37])
+        Co, Do, _ = orc.ls_eval(f, y, net.fftt, net.cap, 0.15, beta, dt, alphas, objective=objective)
+        with q.Context() as ctx:
+            ctx.add(net)
+            ctx.set_demand(0, [], [], [], dt)
+            ctx.layout()
+            for call in (ctx.ls_eval, ctx.ls_eval_noalloc):
+                sums = torch.zeros(K * 4, dtype=torch.int64, device="cuda")
+                call(q.default_opts(beta=beta, objective=objective), dev(f), dev(y), dev(alphas), sums)
+                s = sums.cpu().numpy().reshape(K, 2, 2)
+                for k in range(K):
+                    assert i128(*s[k, 0]) == Co[k], (kind, k)
+                    assert i128(*s[k, 1]) == Do[k], (kind, k)
+
+
+@pytest.mark.parametrize("m", [1, 257, 2049, 70_001])
+@pytest.mark.parametrize("K", [3, 32, 64])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_step_size_at_split_edges(q, orc, m, K, mode):
+    """The decision in the last workgroup of a pass, several searches on one context."""
+    import torch
+    rng = np.random.default_rng(m + K)
+    net = parallel_links(m, rng, 900.0)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], 900.0)
+        a = torch.zeros(1, dtype=torch.float64, device="cuda")
+        for j in (1, 2, 9):
+            f = (rng.uniform(0.0, 300.0, m) * FX).astype(np.int64)
+            y = (rng.uniform(0.0, 900.0, m) * FX).astype(np.int64) * rng.integers(0, 2, m)
+            ao, _, _ = orc.line_search(f, y, net.fftt, net.cap, 0.15, 4, 900.0, j, ls_mode=mode, K=K)
+            ctx.line_search(q.default_opts(ls_mode=mode, K=K), dev(f), dev(y), j, a)
+            assert float(a.cpu()[0]) == ao, (j, mode)
