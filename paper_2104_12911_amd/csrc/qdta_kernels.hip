@@ -2715,31 +2715,28 @@ __device__ __forceinline__ bool stop_at_node(int rule, float tau, float dt) {
 
 // time_cost: the costs that clock the truncation (Eq. 2); NULL = the trees'
 // own costs (the forward records), as in the AON of an iteration.
-// Legs per thread of the walk: the threads of a wavefront walk legs of
-// different lengths, so each takes several (a workgroup walks a contiguous
-// run of kWG * kWalkLegsPerThread legs, a wavefront 64 consecutive legs at a
-// time) and the sums of their lengths vary less than single lengths do.
-constexpr int kWalkLegsPerThread = 4;
+// NT threads of a workgroup walk a contiguous run of NT * LPT legs, LPT each.
 // Loads of a workgroup's legs are summed per link in an LDS table first
 // (legs of one destination share links); the table is added to y when the
 // workgroup is done, and a load whose probes find no slot goes to y directly.
-// Integer sums: the order does not change them.  4,096 slots (48 KB, three
-// workgroups per CU): a workgroup's 1,024 legs load more distinct links than
-// 2,048 slots hold, and 8,192 leave one workgroup per CU.
-constexpr int kWalkSlots = 4096;
-
-__global__ __launch_bounds__(kWG) void k_walk(NetDev net, DemDev dem, const label_t* __restrict__ labels,
+// Integer sums: the order does not change them.  16 slots per thread (48 KB at
+// 256 threads, twelve wavefronts per CU): half as many hold too few of the
+// distinct links (1,191 against 823 us at 316k legs), and twice as many leave
+// half the wavefronts.
+template <int NT, int LPT>
+__global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label_t* __restrict__ labels,
                                               const float* __restrict__ time_cost, const InstState* st,
                                               FlagsDev fl, WalkOut o, int l_begin, int l_end) {
-    __shared__ int s_key[kWalkSlots];
-    __shared__ unsigned long long s_sum[kWalkSlots];
-    for (int x = threadIdx.x; x < kWalkSlots; x += kWG) {
+    constexpr int SLOTS = 16 * NT;
+    __shared__ int s_key[SLOTS];
+    __shared__ unsigned long long s_sum[SLOTS];
+    for (int x = threadIdx.x; x < SLOTS; x += NT) {
         s_key[x] = -1;
         s_sum[x] = 0ull;
     }
     __syncthreads();
     auto load = [&](int e, int64_t d) {
-        int h = (int)(((unsigned)e * 2654435761u) >> 20) & (kWalkSlots - 1);
+        int h = (int)(((unsigned)e * 2654435761u) >> 20) & (SLOTS - 1);
         for (int probe = 0; probe < 4; ++probe) {
             int k = s_key[h];
             if (k == -1) k = atomicCAS(&s_key[h], -1, e);
@@ -2747,13 +2744,13 @@ __global__ __launch_bounds__(kWG) void k_walk(NetDev net, DemDev dem, const labe
                 atomicAdd(&s_sum[h], (unsigned long long)d);
                 return;
             }
-            h = (h + 1) & (kWalkSlots - 1);
+            h = (h + 1) & (SLOTS - 1);
         }
         atomicAdd(reinterpret_cast<unsigned long long*>(&o.y[e]), (unsigned long long)d);
     };
-    const int base = l_begin + blockIdx.x * kWG * kWalkLegsPerThread;
-    const int lim = min(l_end, base + kWG * kWalkLegsPerThread);
-    for (int l = base + threadIdx.x; l < lim; l += kWG) {
+    const int base = l_begin + blockIdx.x * NT * LPT;
+    const int lim = min(l_end, base + NT * LPT);
+    for (int l = base + threadIdx.x; l < lim; l += NT) {
         const int qi = dem.leg_q[l];
         const int inst = dem.dest_inst[qi];
         if (!inst_live(st, inst)) continue;
@@ -2807,7 +2804,7 @@ __global__ __launch_bounds__(kWG) void k_walk(NetDev net, DemDev dem, const labe
         if (!absorbed) finish_leg(o, l, u, q, qi, dem.dest_lab[qi], inst, node0, d, delay);
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < kWalkSlots; x += kWG)
+    for (int x = threadIdx.x; x < SLOTS; x += NT)
         if (s_key[x] >= 0) atomicAdd(reinterpret_cast<unsigned long long*>(&o.y[s_key[x]]), s_sum[x]);
 }
 
@@ -2820,9 +2817,19 @@ hipError_t launch_walk(hipStream_t s, const NetDev& net, const DemDev& dem, cons
     if (l_end <= l_begin) return hipSuccess;
     WalkOut o{y, stop, stop_delay, residual_mode, lambda, r_dense, done_fx,
               tr ? *tr : TransitOut{nullptr, nullptr, nullptr, nullptr, nullptr, 0u}, fl.err_overflow};
-    const int64_t per = (int64_t)kWG * kWalkLegsPerThread;
-    hipLaunchKernelGGL(k_walk, dim3((unsigned)((l_end - l_begin + per - 1) / per)), dim3(kWG), 0, s, net, dem, labels,
-                       time_cost, st, fl, o, l_begin, l_end);
+    // Fewer legs than threads in flight (12 wavefronts per CU with this table,
+    // 196,608 threads): one leg per thread, since a thread's legs run one after
+    // another and a hop is two dependent loads, and 128-thread workgroups, which
+    // spread better.  More legs: two per thread, whose loads share the table.
+    // Phase times at 1 / 2 / 4 legs per thread, us: 1,560 legs 45 / 73 / 116;
+    // 73k legs of 250 trees 250 / 438 / 858; 90k legs of 300 static trees 506 /
+    // 833 / 1,560; 316k legs 823 / 704 / 1,084; 1.2M legs 3,688 / 3,655 / 4,507.
+#define QDTA_WALK(NT, LPT)                                                                                         \
+    hipLaunchKernelGGL((k_walk<NT, LPT>), dim3((unsigned)((l_end - l_begin + NT * LPT - 1) / (NT * LPT))), dim3(NT), \
+                       0, s, net, dem, labels, time_cost, st, fl, o, l_begin, l_end)
+    if (l_end - l_begin < 200000) QDTA_WALK(128, 1);
+    else QDTA_WALK(256, 2);
+#undef QDTA_WALK
     return hipGetLastError();
 }
 

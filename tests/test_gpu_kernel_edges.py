@@ -87,3 +87,31 @@ def test_step_size_at_split_edges(q, orc, m, K, mode):
             ao, _, _ = orc.line_search(f, y, net.fftt, net.cap, 0.15, 4, 900.0, j, ls_mode=mode, K=K)
             ctx.line_search(q.default_opts(ls_mode=mode, K=K), dev(f), dev(y), j, a)
             assert float(a.cpu()[0]) == ao, (j, mode)
+
+
+@pytest.mark.parametrize("legs", [1, 127, 128, 129, 511, 513, 199_999, 200_001, 201_217])
+def test_walk_at_split_edges(q, orc, legs):
+    """Legs either side of a workgroup's run and of the change from one leg per thread to two."""
+    import torch
+    import synth
+    rng = np.random.default_rng(legs)
+    net = synth.grid_network(30, rng)
+    nodes = net.n
+    pair = rng.choice(nodes * nodes, min(4 * legs, nodes * nodes), replace=False)
+    o, d = (pair // nodes).astype(np.int32), (pair % nodes).astype(np.int32)
+    keep = np.nonzero(o != d)[0][:legs]
+    o, d = o[keep], d[keep]
+    assert o.size == legs
+    trips = rng.uniform(0.1, 5.0, legs)
+    cost = (net.fftt * rng.uniform(1.0, 3.0, net.m)).astype(np.float32)
+    lo, ld, lw = orc.demand_legs(o, d, trips)
+    for dt, rule in ((float("inf"), 0), (900.0, 1)):
+        ref_y, ref_stop = orc.aon(net, cost, lo, ld, lw, dt, rule=rule)[:2]
+        with q.Context() as ctx:
+            ctx.add(net)
+            ctx.set_demand(0, o, d, trips, dt)
+            y = torch.empty(net.m, dtype=torch.int64, device="cuda")
+            stop = torch.empty(legs, dtype=torch.int32, device="cuda")
+            ctx.aon(q.default_opts(trunc_rule=rule), dev(cost), y, stop)
+            assert np.array_equal(y.cpu().numpy(), ref_y)
+            assert np.array_equal(stop.cpu().numpy(), ref_stop)
