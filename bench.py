@@ -64,8 +64,9 @@ def sssp_bytes_per_tree(n, m):
     return 8.0 * n + 8.0 * m
 
 
-# kernel instantiation per (sssp_shape, tree_waves): nodes per thread and
-# in-links per thread of each relaxation chunk
+# kernel instantiation per (sssp_shape, tree_waves): a workgroup per tree, its
+# threads in units of 128 and the in-links each relaxes per step; one wavefront
+# per tree, nodes per thread and in-links per thread of each relaxation chunk
 WG_SHAPES = {1: (1, 2), 2: (1, 4), 3: (2, 4), 4: (4, 4), 5: (2, 2), 6: (4, 2)}
 DS_SHAPES = {1: (1, 4), 2: (2, 4), 3: (4, 4), 4: (4, 8), 5: (8, 8), 6: (1, 1)}
 
@@ -767,7 +768,7 @@ def main():
                                f"intervals: {net.n} nodes, {net.m} links, {Q} destinations, {P} legs "
                                f"({dem.P} original + {ro.size} residual), dt {dem.dt_s:g} s",
                    "sssp_kernel": kname, "delta_scale": opts.delta_scale or 10.0,
-                   "waves_per_cu": opts.waves_per_cu or (32 if opts.tree_waves == 1 else 28),
+                   "waves_per_cu": opts.waves_per_cu or (32 if opts.tree_waves == 1 else 16),
                    "line_search": "K-section K=32 x3", "launch": "HIP graph per FW iteration"},
         "gteps": Q * net.m / sssp_avg_s / 1e9,
         "gteps_counted": work_links / n_launch / sssp_avg_s / 1e9,

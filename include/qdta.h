@@ -116,16 +116,17 @@ typedef struct {
     int32_t fixed_iters;   /* > 0: exactly this many updates, stop rule ignored */
     int32_t keep_history;  /* record (alpha_j, c_j) per iteration; needed by qdta_advance_interval */
     int32_t waves_per_cu;  /* shortest-path wavefronts in flight per compute unit (a tree takes
-                              tree_waves of them): 0 auto (28 for the chain-contracted search, 24
-                              for the other kernels with four wavefronts per tree, 32 with one),
-                              else 1..32 */
+                              tree_waves of them): 0 auto (16 for the node queue with a workgroup per
+                              tree, 24 for the other kernels with a workgroup per tree, 32 with one
+                              wavefront per tree), else 1..32 */
     double delta_scale;    /* delta-stepping bucket width as a multiple of the instance's geometric-mean
                               link cost: 0 auto (10.0); any value > 0 gives the same trees, only the speed
                               changes */
-    int32_t sssp_shape;    /* shortest-path kernel shape, nodes per lane per step x links per lane per
-                              chunk, 0 auto (3); four wavefronts per tree: 1 (1,2), 2 (1,4), 3 (2,4),
-                              4 (4,4), 5 (2,2), 6 (4,2); one: 1 (1,4), 2 (2,4), 3 (4,4), 4 (4,8),
-                              5 (8,8), 6 (1,1) */
+    int32_t sssp_shape;    /* shortest-path kernel shape, 0 auto (3); a workgroup per tree, its threads in
+                              units of 128 x links per thread per step: 1 (1,2), 2 (1,4), 3 (2,4),
+                              4 (4,4), 5 (2,2), 6 (4,2); one wavefront per tree, nodes per lane per step
+                              x links per lane per chunk: 1 (1,4), 2 (2,4), 3 (4,4), 4 (4,8), 5 (8,8),
+                              6 (1,1) */
     int32_t launch_form;   /* 0 batched: every tree of every instance in one launch, all K step sizes in
                               one pass, one FW iteration replayed as a captured HIP graph when possible
                               (K-section or MSA); 1 batched with direct launches; 2 plain: one launch per
@@ -145,7 +146,7 @@ typedef struct {
                               nodes' in-links (sssp_shape 1..4 = nodes x links per thread 1x4, 2x4, 2x2,
                               1x2), 4 node queue (one workgroup per tree, sssp_shape as above) over the
                               chain-contracted network: nodes with exactly two neighbours that are no
-                              tree's destination are left out of the search, each run of at most 8 of them
+                              tree's destination are left out of the search, each run of at most 2 of them
                               between two kept nodes is relaxed as one link applying its link costs one
                               by one, and their labels are filled from the run's ends after the search
                               (built on the host when first needed and again when a destination is a

@@ -14,18 +14,18 @@ constexpr int kMaxK = 64;                // step sizes per line-search pass
 // (instances up to kBlkMaxBits * block-size nodes)
 constexpr int kBlkMaxBits = 8192;
 // chain-contracted search: most nodes one chain holds (longer runs of
-// two-neighbour nodes are cut by keeping a node)
-constexpr int kChainMax = 8;
+// two-neighbour nodes are cut by keeping a node); the two or three link costs
+// of such a chain fit its record
+constexpr int kChainMax = 2;
 constexpr int kFillChunk = 1024;         // chains per work item of the fill after the contracted search
-// A kept node's row of contracted records packed in one word, (first record
-// << 6) | count, carried by the records that name the node as their source
-// and by its queue entries so that a pop need not read the row pointers;
-// kNoRow when the row does not fit (64 records or more, or a first record at
-// 2^26 or beyond) or the record has no room for it.
-constexpr uint32_t kNoRow = 0xffffffffu;
+// A node's row of records packed in one word, (first record << 6) | count,
+// carried by the records that name the node as their source and by its queue
+// entries so that a pop need not read the row pointers; kNoRow when the row
+// does not fit (64 records or more, or a first record at 2^25 or beyond).
+constexpr uint32_t kNoRow = 0x80000000u;
 constexpr int kRowCountBits = 6;
 __host__ __device__ inline uint32_t pack_row(int64_t e0, int64_t count) {
-    return (count < (1 << kRowCountBits) && e0 < ((int64_t)1 << (32 - kRowCountBits)))
+    return (count < (1 << kRowCountBits) && e0 < ((int64_t)1 << (31 - kRowCountBits)))
                ? (uint32_t)(e0 << kRowCountBits) | (uint32_t)count
                : kNoRow;
 }
@@ -41,8 +41,12 @@ constexpr int kNoAllocWords = kNoAllocFlagWords + 64 * kMaxK * 6;
 // evaluation itself.
 constexpr int kLsReps = 8;
 
-// One shortest-path label word: (not-queued flag << 31) | FP32 bits of the
-// distance.
+// Far-queue entries of the workgroup-per-tree search beyond one per node: a
+// step may queue this many before the queue is compacted.
+constexpr int kSearchSlack = 2560;
+
+// One shortest-path label word: FP32 bits of the distance, under a flag bit 31
+// that some of the search kernels keep while they run (readers mask it).
 typedef uint32_t label_t;
 
 // Static description of one instance inside the concatenated layout.
@@ -95,11 +99,12 @@ struct NetDev {
     // chain contraction (NULL until built): the search's reverse CSR over the
     // kept nodes, whose records are 4 words: source | form << 30, then the
     // cost bits in the order they are added, one for a plain link (form 0),
-    // two or three for a chain of one or two nodes (forms 1, 2); form 3, a
-    // longer chain, holds the word offset of its cost block (count, then the
-    // costs) instead; cslot[a] is the word that holds link a's cost (-1 none)
+    // two or three for a chain of one or two nodes (forms 1, 2), the last word
+    // the source's packed row where no cost takes it; cslot[a] is the word that
+    // holds link a's cost (-1 none)
     const int32_t* crptr;    // [N+1]
-    uint32_t* cbuf;          // records, cost blocks, then the chains' fill blocks
+    const uint32_t* crow;    // [N]   the same rows packed (pack_row)
+    uint32_t* cbuf;          // records, then the chains' fill blocks
     const int2* cslot;       // [M] (record word, fill word) holding link a's cost, -1 none
     const uint2* anc;        // [N] nodes whose labels must be final before the node's own is (itself if kept)
     const int32_t* inst_chain;// [ninst+1] chains of each instance
@@ -132,15 +137,14 @@ struct DemDev {
 // Per-wavefront scratch of the shortest-path kernel (also the workgroup
 // scratch of the tie fallback, slot = workgroup there).
 struct Scratch {
-    // near queue (ring of n + 1) and far queue of each slot: nmax entries of
-    // the node (1 word; contracted search: the node and its packed row, 2
-    // words) and of (node, label) (2 words; contracted search: node, label,
-    // packed row and a pad word, 4 words)
+    // near queue and far queue of each slot: nmax entries each, of the node (1
+    // word) and of (node, label) (2 words), or for the workgroup-per-tree search
+    // 4 words in both (node, packed row, value, parent)
     int32_t* nearq;
     int32_t* farq;
-    int64_t nmax;            // >= largest n + 65
+    int64_t nmax;            // >= largest n + kSearchSlack + 65
     int32_t* work;           // tree work counter
-    int32_t nslots;          // slots allocated (a launch is clamped to them)
+    int32_t near_w, far_w;   // words allocated per nmax in either queue (a launch is clamped to the slots they hold)
     unsigned long long* stats; // [2] nodes taken and in-links relaxed, added up by the kernels
 };
 

@@ -859,6 +859,7 @@ hipError_t launch_copy_alpha(hipStream_t s, int ninst, const InstState* st, doub
 // label.  A tree starts from +inf, not queued, on every node.
 constexpr uint32_t kNotQueued = 0x80000000u;
 constexpr uint32_t kValueBits = 0x7fffffffu;
+constexpr uint32_t kNoNode = 0xffffffffu;
 __device__ __forceinline__ const label_t* tree_labels(const label_t* labels, const DemDev& dem, int t) {
     return labels + dem.dest_lab[t];
 }
@@ -868,6 +869,11 @@ __device__ __forceinline__ float lab_val(const label_t* lab, int64_t v) {
 
 __device__ __forceinline__ unsigned long long lanes_below(int lane) {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+}
+
+// how many of the mask's lanes are below this one
+__device__ __forceinline__ int lanes_set_below(unsigned long long mask) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 __device__ __forceinline__ float wave_min(float x) {
@@ -1177,33 +1183,34 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
     }
 }
 
-// Candidate label of a shortcut's source: the target's label plus each cost
-// of the chain in turn (blk[0] = number of costs, then the costs), rounded to
-// FP32 after every addition as the link-by-link relaxations would be.
-__device__ __forceinline__ float chain_fold(const uint32_t* __restrict__ blk, float d) {
-    const uint4 h = *reinterpret_cast<const uint4*>(blk);
-    const int len = (int)h.x;
-    d = d + __uint_as_float(h.y);
-    if (len > 1) d = d + __uint_as_float(h.z);
-    if (len > 2) d = d + __uint_as_float(h.w);
-    for (int i = 3; i < len; i += 4) {
-        const uint4 g = *reinterpret_cast<const uint4*>(blk + 1 + i);
-        d = d + __uint_as_float(g.x);
-        if (i + 1 < len) d = d + __uint_as_float(g.y);
-        if (i + 2 < len) d = d + __uint_as_float(g.z);
-        if (i + 3 < len) d = d + __uint_as_float(g.w);
-    }
-    return d;
-}
-
-// Workgroup-per-tree form of the same delta-stepping: the four wavefronts of
-// a workgroup grow one tree together, popping up to 256 U nodes per step
-// from the lowest node-id ranges, so a quarter as many trees are in flight
-// for the same number of wavefronts and each keeps four times as many of its
-// label lines in the L2.  Queue state (range heads and counts, near / far
-// counts) is in LDS; a step is: wavefront 0 takes the pops from the lowest
-// ranges; every thread pops; a workgroup prefix sum of the in-degrees;
-// every thread relaxes V in-links per chunk; the counts are folded in.
+// Workgroup-per-tree form of delta-stepping: the NT = 128 U threads of a
+// workgroup grow one tree together, each relaxing V records a step.
+//   - A label here is the plain FP32 value, with no queued flag: a relaxation
+//     that lowers a label queues the node together with the value it wrote, and
+//     a pop uses that value.  A node improved again while it waits is queued
+//     again, and its older entry relaxes nothing that the newer one would not
+//     lower further.  A pop therefore touches no label at all.
+//   - A queue entry is (node, row, value, parent).  The row is the node's
+//     packed record row, which saves a pop the row pointers, or kNoRow + the
+//     number of records already relaxed.  Records whose source is the parent,
+//     the node this value came from, are skipped: adding non-negative costs to a
+//     value that came from the parent's label cannot lower that label.
+//   - A step takes up to NT entries, one per thread: from a circular buffer in
+//     LDS, then from the ring in memory that takes the buffer's overflow.  Each
+//     thread relaxes up to V records of its entry, their loads issued together;
+//     the rest of a longer row is queued again in pieces of V.
+//   - No label is changed by an atomic: on this memory they are carried out
+//     beyond the L2 (one memory write each, and the line leaves the L2).  Only
+//     the tree's own workgroup touches its labels, so a step's improvements
+//     meet in a hash table in LDS; after a barrier the least candidate of each
+//     node (one of equal ones) stores the label and queues the node.  Two
+//     barriers a step, and two dependent memory accesses, record and label.
+//   - Entries at or above the bucket bound thr go to the far queue.  When the
+//     near entries are used up, thr moves delta above the smallest far value and
+//     one pass moves the far entries below it, dropping those whose label has
+//     been lowered since.  A near entry that finds the ring full goes to the far
+//     queue too; a far queue that could overflow in the next step is compacted
+//     to its live entries first, of which a node has at most one.
 //
 // CT: the chain-contracted search.  Nodes left out by the contraction are
 // never queued; the kept nodes' in-links come from the contracted records
@@ -1211,51 +1218,49 @@ __device__ __forceinline__ float chain_fold(const uint32_t* __restrict__ blk, fl
 // is left out waits for the kept nodes its label depends on; the chain
 // nodes' labels are filled from their chains' ends afterwards (k_chain_fill).
 //
+// Bound by memory traffic where all trees together are far larger than the L2
+// (550k nodes, 5,000 trees: 51 ms, 84 ms before this form; the same at 16 to 32
+// wavefronts per CU), by the latency of a step's chain of accesses below that
+// (metro network, 100k nodes, 1,000 trees: 2.4 ms, 5.7; 22,801-node grid, 300
+// trees: 0.80 ms, 3.77; 400-node grid, 40 trees: 0.07 ms, 0.13).  What each part
+// gave on the 550k nodes: no flag and no pop access 84 -> 65 ms, no atomics ->
+// 56, no dependent cost block for a chain -> 54.6, the step's two barriers and
+// branch-free phases -> 51 (and 2.7 -> 2.4 ms on the metro network, 1.2 -> 0.8
+// on the grid).
+//
 // W: wavefronts per SIMD the register allocation leaves room for (1: the
-// compiler's choice).  The contracted <2, 4> form fits 7 in 72 VGPRs with no
-// spill, one more than the 6 the compiler's own choice of 74 allows.
+// compiler's choice).  The LDS holds four workgroups of <2, 4> per CU whatever
+// it is; 7 keeps it at 72 VGPRs instead of 90, in the same time.
 template <int U, int V, bool CT, int W = 1>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(W))) void k_sssp_wg(NetDev net, DemDev dem, const uint2* __restrict__ radj,
-                                                 label_t* labels, Scratch scr, const InstState* st,
-                                                 const float* __restrict__ delta_inst, int early, int t_begin,
-                                                 int t_end) {
-    constexpr int NT = kWG;
-    constexpr int NW = NT / 64;
-    constexpr int NP = NT * U;                    // nodes per step
-    __shared__ int s_pre[NP + 1];
-    __shared__ float s_dw[NP];
-    __shared__ int s_e0[NP];
-    __shared__ int s_rh[64], s_rc[64], s_rhp[64], s_tail[64], s_push[64], s_tpre[64];
-    __shared__ int s_wsum[NW];
-    __shared__ int s_t, s_nn, s_fn;
-    __shared__ uint32_t s_fm;
-    __shared__ uint32_t s_row[CT ? NT * V : 1];   // each relaxation's source row, kept out of registers
-    // queue entries: the node (near) and (node, label) (far); the contracted
-    // search's also carry the node's packed row (kNoRow: read the row pointers)
-    using NearE = typename std::conditional<CT, uint2, int32_t>::type;
-    using FarE = typename std::conditional<CT, uint4, uint2>::type;
-    // The near entries one pushing phase makes go to an LDS buffer first (the
-    // next step pops them all, before the rings), and to the rings in HBM
-    // once it is full: s_bp counts the pushes since the last pop.
-    constexpr int NB = NP;
-    __shared__ NearE s_buf[NB];
-    __shared__ int s_bp;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    NearE* nearq = reinterpret_cast<NearE*>(scr.nearq) + (int64_t)blockIdx.x * scr.nmax;
-    FarE* farq = reinterpret_cast<FarE*>(scr.farq) + (int64_t)blockIdx.x * scr.nmax;
-    auto near_entry = [](int v, uint32_t row) -> NearE {
-        if constexpr (CT) return make_uint2((uint32_t)v, row);
-        else return v;
-    };
-    auto far_entry = [](uint32_t v, uint32_t lab, uint32_t row) -> FarE {
-        if constexpr (CT) return make_uint4(v, lab, row, 0u);
-        else return make_uint2(v, lab);
-    };
-    auto far_row = [](const FarE& e) -> uint32_t {
-        if constexpr (CT) return e.z;
-        else return kNoRow;
-    };
-    unsigned long long n_taken = 0, n_relaxed = 0;    // counted by every thread alike (uniform values)
+__global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(W))) void k_sssp_wg(
+    NetDev net, DemDev dem, const uint2* __restrict__ radj, label_t* labels, Scratch scr, const InstState* st,
+    const float* __restrict__ delta_inst, int early, int t_begin, int t_end) {
+    constexpr int NT = 128 * U;
+    constexpr int NB = 2 * NT;                    // entries of the LDS buffer
+    constexpr int NH = 2 * V * NT;                // slots of the hash table, twice what a step can take
+    constexpr unsigned long long kFree = ~0ull;
+    constexpr int F = NT >= 512 ? 1 : 512 / NT;   // far entries per thread and turn of a pass over them
+    static_assert(NT * (V + 1) <= kSearchSlack, "the far queue has room for one step beyond a node each");
+    // 64 spare words after each array: what a lane without work reads and writes
+    // (its own word), so that the V accesses of a phase are issued back to back
+    // with no branch between them
+    __shared__ uint4 s_buf[NB + 64];              // near entries
+    __shared__ unsigned long long s_val[NH + 64]; // the step's improvements: least (candidate, its number)
+    __shared__ uint32_t s_key[NH + 64];           // of this node
+    __shared__ unsigned long long s_cnt[2];       // far << 32 | near entries pushed in a step (odd, even)
+    __shared__ int s_t;                           // next tree
+    __shared__ uint32_t s_fm;                     // smallest value pushed to far
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int cap = (int)scr.nmax;                // entries of the ring and of the far queue
+    uint4* nearq = reinterpret_cast<uint4*>(scr.nearq) + (int64_t)blockIdx.x * scr.nmax;
+    uint4* farq = reinterpret_cast<uint4*>(scr.farq) + (int64_t)blockIdx.x * scr.nmax;
+    const uint4* __restrict__ crec = reinterpret_cast<const uint4*>(net.cbuf);
+    for (int x = tid; x < NH + 64; x += NT) {
+        s_key[x] = kNoNode;
+        s_val[x] = kFree;
+    }
+    unsigned long long n_taken = 0;               // counted by every thread alike (uniform values)
+    unsigned int n_relaxed = 0;                   // this thread's own
     for (;;) {
         if (tid == 0) s_t = t_begin + atomicAdd(scr.work, 1);
         __syncthreads();
@@ -1265,245 +1270,307 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(W))) void k
         const int inst = dem.dest_inst[t];
         if (!inst_live(st, inst)) continue;
         const InstDev I = net.inst[inst];
-        const int n = I.n, node0 = I.node0;
+        const int n = I.n;
+        const uint32_t node0 = (uint32_t)I.node0;
         const int* __restrict__ rptr = (CT ? net.crptr : net.rptr) + node0;
-        const uint2* __restrict__ recs = radj;
-        const uint4* __restrict__ crec = reinterpret_cast<const uint4*>(net.cbuf);
+        const uint32_t* __restrict__ crow = CT ? net.crow + node0 : nullptr;
         label_t* D = labels + dem.dest_lab[t];
-        const int root = dem.dest_node[t] - node0;
+        const int root = dem.dest_node[t] - (int)node0;
         const float delta = delta_inst[inst];
         {
             uint4* D4 = reinterpret_cast<uint4*>(D);
-            const uint32_t w0 = kNotQueued | kInfBits;
-            const uint4 inf4 = make_uint4(w0, w0, w0, w0);
+            const uint4 inf4 = make_uint4(kInfBits, kInfBits, kInfBits, kInfBits);
             const int n4 = (n + 31) / 32 * 8;
             for (int i = tid; i < n4; i += NT) D4[i] = inf4;
         }
-        int rsh = 0;
-        while (((n - 1) >> rsh) >= 64) ++rsh;
-        const int rs = 1 << rsh;
-        const int nranges = ((n - 1) >> rsh) + 1;
-        if (tid < 64) {
-            s_rh[tid] = 0;
-            s_rc[tid] = (tid == (root >> rsh)) ? 1 : 0;
-            s_push[tid] = 0;
-        }
-        if (tid == 0) {
-            s_nn = 0;
-            s_fn = 0;
-            s_fm = kInfBits;
-            s_bp = 0;
-        }
         __threadfence_block();
         __syncthreads();
         if (tid == 0) {
-            D[root] = 0u;                         // value 0, queued
-            nearq[(root >> rsh) * (rs + 1)] = near_entry(root, pack_row(rptr[root], rptr[root + 1] - rptr[root]));
+            D[root] = 0u;
+            s_buf[0] = make_uint4((uint32_t)root, CT ? crow[root] : kNoRow, 0u, kNoNode);
+            s_cnt[0] = s_cnt[1] = 0ull;
         }
         __threadfence_block();
         __syncthreads();
-        auto ring_at = [&](int r, int pos) -> NearE* {
-            const int cap = min(rs, n - r * rs) + 1;
-            if (pos >= cap) pos -= cap;
-            return nearq + (int64_t)r * (rs + 1) + pos;
+        int bh = 0, bc = 1, rh = 0, rc = 0;       // head and count of the buffer and of the ring
+        int fcnt = 0, par = 0;                    // far entries; which counters the next pushes use
+        float thr = delta;
+        float lfm = __uint_as_float(kInfBits);    // smallest far value this thread has pushed since the last pass
+        // first positions of this wavefront's entries of the two queues
+        auto reserve = [&](int near, int far, int& pn, int& pf) {
+            unsigned long long p = 0ull;
+            if (lane == 0) p = atomicAdd(&s_cnt[par], ((unsigned long long)far << 32) | (unsigned)near);
+            pn = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+            pf = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
         };
-        auto push_near = [&](int v, uint32_t row) {
-            const int b = atomicAdd(&s_bp, 1);
-            if (b < NB) {
-                s_buf[b] = near_entry(v, row);
-            } else {
-                const int r = v >> rsh;
-                *ring_at(r, s_tail[r] + atomicAdd(&s_push[r], 1)) = near_entry(v, row);
+        // The near entry number p of a pushing phase that found bc and rc entries:
+        // into the buffer, else the ring; false if both are full.
+        auto put_near = [&](int p, const uint4& ent) -> bool {
+            if (p < NB - bc) {
+                s_buf[(bh + bc + p) & (NB - 1)] = ent;
+                return true;
             }
-            atomicAdd(&s_nn, 1);
+            const int r = p - (NB - bc);
+            if (r >= cap - rc) return false;
+            int q = rh + rc + r;
+            if (q >= cap) q -= cap;
+            nearq[q] = ent;
+            return true;
         };
-        // wavefront 0: tails of the rings for the pushes to come
-        auto open_push = [&]() {
-            if (wv == 0) {
-                const int cap = lane < nranges ? min(rs, n - lane * rs) + 1 : 1;
-                int tl = s_rh[lane] + s_rc[lane];
-                if (tl >= cap) tl -= cap;
-                s_tail[lane] = tl;
-                s_push[lane] = 0;
+        auto put_far = [&](int p, const uint4& ent) {
+            farq[fcnt + p] = ent;
+            lfm = fminf(lfm, __uint_as_float(ent.z));
+        };
+        // after the barrier that ends a pushing phase: its entries are counted in
+        auto fold = [&]() {
+            const unsigned long long c = s_cnt[par];
+            const int nn = __builtin_amdgcn_readfirstlane((int)(uint32_t)c), ib = min(nn, NB - bc);
+            fcnt += __builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32));
+            rc += min(nn - ib, cap - rc);
+            bc += ib;
+            par ^= 1;
+            if (tid == 0) s_cnt[par] = 0ull;      // read by all before the phase that just ended
+        };
+        // One pass over the first total_far far entries: those below `below_thr`
+        // whose label is still theirs go to near, the others below it are dropped,
+        // the rest stay; all = drop every entry whose label is not its own.
+        auto sweep_far = [&](float below_thr, bool all) {
+            const int total_far = fcnt;
+            fcnt = 0;                             // entries kept are pushed from the front again
+            lfm = __uint_as_float(kInfBits);
+            for (int i0 = 0; i0 < total_far; i0 += NT * F) {
+                uint4 ent[F];
+                bool low[F], keep[F];
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const int i = i0 + f * NT + tid;
+                    keep[f] = i < total_far;
+                    ent[f] = keep[f] ? farq[i] : make_uint4(0u, 0u, kInfBits, 0u);
+                }
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    low[f] = keep[f] && __uint_as_float(ent[f].z) < below_thr;
+                    if (low[f] || (keep[f] && all)) keep[f] = D[ent[f].x] == ent[f].z;
+                    low[f] = low[f] && keep[f];
+                    keep[f] = keep[f] && !(__uint_as_float(ent[f].z) < below_thr);
+                }
+                __syncthreads();                  // the turn's entries are read before they are overwritten
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const unsigned long long bn = __ballot(low[f]);
+                    int p, q;
+                    if (bn) {
+                        reserve(__popcll(bn), 0, p, q);
+                        if (low[f]) keep[f] = !put_near(p + lanes_set_below(bn), ent[f]);
+                    }
+                    const unsigned long long bf = __ballot(keep[f]);
+                    if (bf) {
+                        reserve(0, __popcll(bf), p, q);
+                        if (keep[f]) put_far(q + lanes_set_below(bf), ent[f]);
+                    }
+                }
             }
-        };
-        // after a pushing phase (all threads past a barrier): counts folded in
-        int ncnt = 1, fcnt = 0;
-        float thr = delta, fmin = __uint_as_float(kInfBits);
-        auto fold = [&]() -> int {
-            __threadfence_block();
             __syncthreads();
-            const int nn = s_nn, fn = s_fn;
-            const float fm = __uint_as_float(s_fm);
-            __syncthreads();
-            if (wv == 0) {
-                if (lane < nranges) s_rc[lane] += s_push[lane];
-                s_push[lane] = 0;
-            }
-            if (tid == 0) {
-                s_nn = 0;
-                s_fn = 0;
-                s_fm = kInfBits;
-            }
-            ncnt += nn;
-            fcnt += fn;
-            fmin = fminf(fmin, fm);
-            return nn;
+            fold();
         };
         int lcur = early ? dem.qptr[t] : 0;
         const int lend = early ? dem.qptr[t + 1] : 0;
         for (;;) {
-            while (ncnt > 0) {
-                const int k = ncnt < NP ? ncnt : NP;
-                // the buffer's entries first (all of them: kb <= k), then the
-                // lowest ranges' rings
-                const int kb = min(s_bp, NB);
-                if (wv == 0) {
-                    const int rc = s_rc[lane], rh = s_rh[lane];
-                    int incl = rc;
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int x = __shfl_up(incl, o);
-                        if (lane >= o) incl += x;
-                    }
-                    const int excl = incl - rc;
-                    const int take = max(0, min(rc, NP - kb - excl));
-                    const int cap = lane < nranges ? min(rs, n - lane * rs) + 1 : 1;
-                    s_tpre[lane] = min(excl, NP - kb);
-                    s_rhp[lane] = rh;
-                    int nh = rh + take;
-                    if (nh >= cap) nh -= cap;
-                    s_rh[lane] = nh;
-                    s_rc[lane] = rc - take;
-                    int tl = nh + rc - take;
-                    if (tl >= cap) tl -= cap;
-                    s_tail[lane] = tl;
-                    s_push[lane] = 0;
+            while (bc + rc > 0) {
+                if (fcnt + NT * (V + 1) > cap) {
+                    __syncthreads();              // the counters' reset is seen
+                    sweep_far(0.0f, true);        // keep only the live far entries
                 }
-                __syncthreads();
-                if (tid == 0) s_bp = 0;               // every thread has read it; pushes come after barriers
-                int deg[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int j = u * NT + tid;
-                    deg[u] = 0;
-                    if (j < k) {
-                        NearE qe;
-                        if (j < kb) {
-                            qe = s_buf[j];
-                        } else {
-                            const int jr = j - kb;
-                            int lo = 0, hi = 64;
-                            while (hi - lo > 1) {
-                                const int mid = (lo + hi) >> 1;
-                                if (s_tpre[mid] <= jr) lo = mid; else hi = mid;
-                            }
-                            qe = *ring_at(lo, s_rhp[lo] + (jr - s_tpre[lo]));
+                const int k = min(bc + rc, NT), kb = min(bc, k);
+                uint4 ent = make_uint4(0u, 0u, 0u, 0u), r[V];
+                int e0 = 0, deg = 0;
+                uint32_t cb[V], okm = 0u;         // candidates; bit x: record x may lower its source
+                int slot[V];
+                const bool some = (tid & ~63) < k;    // this wavefront has entries
+                if (some) {
+                    if (tid < kb) {
+                        ent = s_buf[(bh + tid) & (NB - 1)];
+                    } else if (tid < k) {
+                        int q = rh + (tid - kb);
+                        if (q >= cap) q -= cap;
+                        ent = nearq[q];
+                    }
+                    if (tid < k) {
+                        e0 = (int)(ent.y >> kRowCountBits);
+                        deg = (int)(ent.y & ((1u << kRowCountBits) - 1u));
+                        if (!CT || (ent.y & kNoRow)) {
+                            e0 = rptr[ent.x] + (int)(ent.y & ~kNoRow);
+                            deg = rptr[ent.x + 1] - e0;
+                            if (deg == 0) e0 = 0;
                         }
-                        int w, e0;
-                        if constexpr (CT) {
-                            w = (int)qe.x;
-                            if (qe.y != kNoRow) {
-                                e0 = (int)(qe.y >> kRowCountBits);
-                                deg[u] = (int)(qe.y & ((1u << kRowCountBits) - 1u));
-                            } else {
-                                e0 = rptr[w];
-                                deg[u] = rptr[w + 1] - e0;
-                            }
-                        } else {
-                            w = qe;
-                            e0 = rptr[w];
-                            deg[u] = rptr[w + 1] - e0;
-                        }
-                        const uint32_t lw = atomicOr(&D[w], kNotQueued);   // dequeue, read the label
-                        s_e0[j] = e0;
-                        s_dw[j] = __uint_as_float(lw & kValueBits);
                     }
-                }
-                // exclusive prefix of the in-degrees in slot order (workgroup-wide)
-                int base = 0;
+                    const int top = max(deg - 1, 0);
+                    const float d = __uint_as_float(ent.z);
+                    if (CT) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    int incl = deg[u];
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int x = __shfl_up(incl, o);
-                        if (lane >= o) incl += x;
+                        for (int x = 0; x < V; ++x) r[x] = crec[e0 + min(x, top)];
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < V; ++x) {
+                            const uint2 q = radj[e0 + min(x, top)];
+                            r[x] = make_uint4(q.x, q.y, 0u, kNoRow);
+                        }
                     }
-                    if (lane == 63) s_wsum[wv] = incl;
-                    __syncthreads();
-                    int before = 0, all = 0;
-                    for (int q = 0; q < NW; ++q) {
-                        if (q < wv) before += s_wsum[q];
-                        all += s_wsum[q];
+                    uint32_t cur[V], two = 0u;
+#pragma unroll
+                    for (int x = 0; x < V; ++x) {
+                        // form 0: a link; 1, 2: a chain's two or three costs; the last
+                        // word is the source's packed row but for form 2 (see below)
+                        const uint32_t form = CT ? r[x].x >> 30 : 0u;
+                        r[x].x = (CT ? r[x].x & 0x3fffffffu : r[x].x) - node0;
+                        const float c1 = d + __uint_as_float(r[x].y);
+                        const float c2 = c1 + __uint_as_float(r[x].z);
+                        const float c3 = c2 + __uint_as_float(r[x].w);
+                        cb[x] = __float_as_uint(form == 0u ? c1 : form == 1u ? c2 : c3);
+                        const bool ok = x < deg && r[x].x != ent.w;
+                        okm |= ok ? 1u << x : 0u;
+                        if (CT) two |= ok && form == 2u ? 1u << x : 0u;
+                        cur[x] = D[ok ? r[x].x : 0u];
                     }
-                    s_pre[u * NT + tid] = base + before + incl - deg[u];
-                    base += all;
-                    __syncthreads();
+                    if (CT && __ballot(two != 0u)) {
+#pragma unroll
+                        for (int x = 0; x < V; ++x)
+                            if (two >> x & 1u) r[x].w = crow[r[x].x];
+                    }
+                    n_relaxed += (unsigned)min(deg, V);
+                    // claim a slot per node, the V probes of a round together (at most
+                    // half of the slots are taken)
+                    uint32_t pend = 0u;
+#pragma unroll
+                    for (int x = 0; x < V; ++x) {
+                        pend |= cb[x] < cur[x] ? 1u << x : 0u;
+                        slot[x] = (int)((r[x].x * 2654435761u) >> 16) & (NH - 1);
+                    }
+                    okm &= pend;
+                    pend = okm;
+                    do {
+                        uint32_t o[V], key[V];
+#pragma unroll
+                        for (int x = 0; x < V; ++x) {
+                            const bool p = pend >> x & 1u;
+                            key[x] = p ? r[x].x : kNoNode;
+                            o[x] = atomicCAS(&s_key[p ? slot[x] : NH + lane], kNoNode, key[x]);
+                        }
+#pragma unroll
+                        for (int x = 0; x < V; ++x) {
+                            const bool p = o[x] != kNoNode && o[x] != key[x];
+                            slot[x] = p ? (slot[x] + 1) & (NH - 1) : slot[x];
+                            pend &= p ? ~0u : ~(1u << x);
+                        }
+                    } while (__ballot(pend != 0u));
+#pragma unroll
+                    for (int x = 0; x < V; ++x) {
+                        const bool p = okm >> x & 1u;
+                        slot[x] = p ? slot[x] : NH + lane;
+                        atomicMin(&s_val[slot[x]],
+                                  p ? ((unsigned long long)cb[x] << 32) | (unsigned)(tid * V + x) : kFree);
+                    }
                 }
-                if (tid == 0) s_pre[NP] = base;
-                if (k < NP && tid == 0) s_pre[k] = base;
-                __syncthreads();
-                const int total = base;
-                ncnt -= k;
+                const int kr = k - kb;
+                bh = (bh + kb) & (NB - 1);
+                bc -= kb;
+                rh += kr;
+                if (rh >= cap) rh -= cap;
+                rc -= kr;
                 n_taken += (unsigned)k;
-                n_relaxed += (unsigned)total;
-                for (int g0 = 0; g0 < total; g0 += NT * V) {
-                    int vv[V];
-                    float cd[V];
-                    bool ok[V];
+                __syncthreads();
+                // the least candidate of each node (the lowest numbered of equal ones)
+                // writes the label, queues the node and clears the slot (a candidate
+                // that reads it afterwards loses as well)
+                if (some) {
+                    unsigned long long best[V], bn[V], bf[V];
+                    int cn = 0, cf = 0;
+#pragma unroll
+                    for (int x = 0; x < V; ++x) best[x] = s_val[slot[x]];
+                    uint32_t win = 0u;
 #pragma unroll
                     for (int x = 0; x < V; ++x) {
-                        const int g = g0 + x * NT + tid;
-                        ok[x] = g < total;
-                        vv[x] = 0;
-                        cd[x] = 0.0f;
-                        if (ok[x]) {
-                            int lo = 0, hi = k;   // owner slot: pre[lo] <= g < pre[lo + 1]
-                            while (hi - lo > 1) {
-                                const int mid = (lo + hi) >> 1;
-                                if (s_pre[mid] <= g) lo = mid; else hi = mid;
-                            }
-                            const int e = s_e0[lo] + (g - s_pre[lo]);
-                            if (CT) {
-                                // form 0: a link; 1, 2: a chain's two or three
-                                // costs inline; 3: a longer chain's cost block
-                                const uint4 r = crec[e];
-                                const uint32_t form = r.x >> 30;
-                                vv[x] = (int)(r.x & 0x3fffffffu) - node0;
-                                s_row[x * NT + tid] = form != 2u ? r.w : kNoRow;   // the source's packed row
-                                if (form == 3u) {
-                                    cd[x] = chain_fold(net.cbuf + r.y, s_dw[lo]);
-                                } else {
-                                    float d = s_dw[lo] + __uint_as_float(r.y);
-                                    if (form >= 1u) d = d + __uint_as_float(r.z);
-                                    if (form >= 2u) d = d + __uint_as_float(r.w);
-                                    cd[x] = d;
-                                }
-                            } else {
-                                const uint2 r = recs[e];
-                                vv[x] = (int)r.x - node0;
-                                cd[x] = s_dw[lo] + __uint_as_float(r.y);
+                        const bool w = (okm >> x & 1u) && best[x] == (((unsigned long long)cb[x] << 32) |
+                                                                      (unsigned)(tid * V + x));
+                        const bool nr = __uint_as_float(cb[x]) < thr;
+                        win |= w ? 1u << x : 0u;
+                        bn[x] = __ballot(w && nr);
+                        bf[x] = __ballot(w && !nr);
+                        cn += __popcll(bn[x]);
+                        cf += __popcll(bf[x]);
+                        slot[x] = w ? slot[x] : NH + lane;
+                        s_val[slot[x]] = kFree;
+                        s_key[slot[x]] = kNoNode;
+                    }
+                    int p, q;
+                    reserve(cn, cf, p, q);
+#pragma unroll
+                    for (int x = 0; x < V; ++x)
+                        if (win >> x & 1u) D[r[x].x] = cb[x];
+                    if (p + cn <= NB - bc) {      // this wavefront's near entries all go to the buffer
+#pragma unroll
+                        for (int x = 0; x < V; ++x) {
+                            const bool w = (win >> x & 1u) && __uint_as_float(cb[x]) < thr;
+                            const int at = (bh + bc + p + lanes_set_below(bn[x])) & (NB - 1);
+                            s_buf[w ? at : NB + lane] = make_uint4(r[x].x, r[x].w, cb[x], ent.x);
+                            p += __popcll(bn[x]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < V; ++x) {
+                            const uint4 e = make_uint4(r[x].x, r[x].w, cb[x], ent.x);
+                            bool full = false;
+                            if ((win >> x & 1u) && __uint_as_float(cb[x]) < thr)
+                                full = !put_near(p + lanes_set_below(bn[x]), e);
+                            p += __popcll(bn[x]);
+                            const unsigned long long bx = __ballot(full);
+                            if (bx) {             // ring full
+                                int p1, q1;
+                                reserve(0, __popcll(bx), p1, q1);
+                                if (full) put_far(q1 + lanes_set_below(bx), e);
                             }
                         }
                     }
-                    uint32_t cur[V];
+                    if (cf) {
 #pragma unroll
-                    for (int x = 0; x < V; ++x) cur[x] = ok[x] ? (ld_coherent(&D[vv[x]]) & kValueBits) : 0u;
-#pragma unroll
-                    for (int x = 0; x < V; ++x) {
-                        const uint32_t cb = __float_as_uint(cd[x]);
-                        if (ok[x] && cb < cur[x] && (atomicMin(&D[vv[x]], cb) & kNotQueued)) {
-                            const uint32_t row = CT ? s_row[x * NT + tid] : kNoRow;
-                            if (cd[x] < thr) {
-                                push_near(vv[x], row);
-                            } else {
-                                farq[fcnt + atomicAdd(&s_fn, 1)] = far_entry((uint32_t)vv[x], cb, row);
-                                atomicMin(&s_fm, cb);
-                            }
+                        for (int x = 0; x < V; ++x) {
+                            if ((win >> x & 1u) && !(__uint_as_float(cb[x]) < thr))
+                                put_far(q + lanes_set_below(bf[x]), make_uint4(r[x].x, r[x].w, cb[x], ent.x));
+                            q += __popcll(bf[x]);
                         }
                     }
                 }
+                // the rest of a longer row: pieces of V records; or, if its row does
+                // not pack or the near queues are full, one entry with all of it
+                for (int done = V; __ballot(done < deg) != 0ull; done += V) {
+                    const bool more = done < deg;
+                    const uint32_t rest = kNoRow + (uint32_t)(e0 + done - (more ? rptr[ent.x] : 0));
+                    uint4 e = make_uint4(ent.x, CT ? pack_row(e0 + done, min(V, deg - done)) : kNoRow, ent.z, ent.w);
+                    if (e.y == kNoRow) e.y = rest;
+                    const unsigned long long bm = __ballot(more);
+                    int p, q;
+                    reserve(__popcll(bm), 0, p, q);
+                    const bool full = more && !put_near(p + lanes_set_below(bm), e);
+                    const unsigned long long bw = __ballot(full);
+                    if (bw) {
+                        e.y = rest;
+                        reserve(0, __popcll(bw), p, q);
+                        if (full) put_far(q + lanes_set_below(bw), e);
+                    }
+                    if (more && (e.y & kNoRow)) deg = 0;   // all of it is queued
+                }
+                __syncthreads();
                 fold();
             }
+            // the smallest far value
+            if (tid == 0) s_fm = kInfBits;
+            __syncthreads();
+            {
+                const float m = wave_min(lfm);
+                if (lane == 0) atomicMin(&s_fm, __float_as_uint(m));
+            }
+            __syncthreads();
+            const float fmin = __uint_as_float(s_fm);
             if (early) {
                 bool pend = false;
                 while (lcur < lend) {
@@ -1512,111 +1579,29 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(W))) void k
                     if (l < lend) {
                         if (CT) {
                             const uint2 an = net.anc[dem.leg_orig[l]];
-                            p = !(__uint_as_float(ld_coherent(&D[(int)an.x - node0]) & kValueBits) < thr &&
-                                  __uint_as_float(ld_coherent(&D[(int)an.y - node0]) & kValueBits) < thr);
+                            p = !(__uint_as_float(D[an.x - node0]) < thr && __uint_as_float(D[an.y - node0]) < thr);
                         } else {
-                            const int o = dem.leg_orig[l] - node0;
-                            p = !(__uint_as_float(ld_coherent(&D[o]) & kValueBits) < thr);
+                            p = !(__uint_as_float(D[(uint32_t)dem.leg_orig[l] - node0]) < thr);
                         }
                     }
                     if (__syncthreads_or(p)) { pend = true; break; }
                     lcur += NT;
                 }
-                if (!pend) {
-                    // exact: queue the far nodes whose current label is below thr
-                    int moved = 0, keep = 0;
-                    float km = __uint_as_float(kInfBits);
-                    open_push();
-                    __syncthreads();
-                    for (int i0 = 0; i0 < fcnt; i0 += NT) {
-                        const int i = i0 + tid;
-                        const bool h = i < fcnt;
-                        FarE ent = h ? farq[i] : far_entry(0u, kInfBits, kNoRow);
-                        if (h) ent.y = ld_coherent(&D[ent.x]) & kValueBits;   // the label now
-                        const bool late = h && __uint_as_float(ent.y) < thr;
-                        __syncthreads();                  // the chunk is read before it is overwritten
-                        if (late) {
-                            push_near((int)ent.x, far_row(ent));
-                        } else if (h) {
-                            farq[keep + atomicAdd(&s_fn, 1)] = ent;
-                            atomicMin(&s_fm, ent.y);
-                        }
-                        __threadfence_block();
-                        __syncthreads();
-                        const int nn = s_nn, fn = s_fn;
-                        const float fm = __uint_as_float(s_fm);
-                        __syncthreads();
-                        if (tid == 0) {
-                            s_nn = 0;
-                            s_fn = 0;
-                            s_fm = kInfBits;
-                        }
-                        ncnt += nn;
-                        moved += nn;
-                        keep += fn;
-                        km = fminf(km, fm);
-                    }
-                    if (wv == 0) {
-                        if (lane < nranges) s_rc[lane] += s_push[lane];
-                        s_push[lane] = 0;
-                    }
-                    __syncthreads();
-                    fcnt = keep;
-                    fmin = km;
-                    if (moved == 0) break;                // every label below thr is final
-                    continue;
-                }
+                // no entry below thr is left: every label below it is final
+                if (!pend && !(fmin < thr)) break;
             }
             if (fcnt == 0) break;
             thr = fmaxf(thr, fmin) + delta;
             if (!(thr > fmin)) thr = __uint_as_float(__float_as_uint(fmin) + 1u);
-            int keep = 0;
-            float km = __uint_as_float(kInfBits);
-            open_push();
-            __syncthreads();
-            for (int i0 = 0; i0 < fcnt; i0 += NT) {
-                const int i = i0 + tid;
-                const bool h = i < fcnt;
-                FarE ent = h ? farq[i] : far_entry(0u, kInfBits, kNoRow);
-                // key by the label now: a far node improved since its push keeps
-                // its queued flag and is not pushed again, and waiting for the
-                // threshold to pass its old label would make every node it
-                // reaches meanwhile be popped again
-                if (h) ent.y = ld_coherent(&D[ent.x]) & kValueBits;
-                __syncthreads();
-                if (h && __uint_as_float(ent.y) < thr) {
-                    push_near((int)ent.x, far_row(ent));
-                } else if (h) {
-                    farq[keep + atomicAdd(&s_fn, 1)] = ent;
-                    atomicMin(&s_fm, ent.y);
-                }
-                __threadfence_block();
-                __syncthreads();
-                const int nn = s_nn, fn = s_fn;
-                const float fm = __uint_as_float(s_fm);
-                __syncthreads();
-                if (tid == 0) {
-                    s_nn = 0;
-                    s_fn = 0;
-                    s_fm = kInfBits;
-                }
-                ncnt += nn;
-                keep += fn;
-                km = fminf(km, fm);
-            }
-            if (wv == 0) {
-                if (lane < nranges) s_rc[lane] += s_push[lane];
-                s_push[lane] = 0;
-            }
-            __syncthreads();
-            fcnt = keep;
-            fmin = km;
+            bh = rh = 0;
+            sweep_far(thr, false);
         }
         __syncthreads();
     }
-    if (scr.stats && tid == 0) {
-        atomicAdd(&scr.stats[0], n_taken);
-        atomicAdd(&scr.stats[1], n_relaxed);
+    if (scr.stats) {
+        for (int o = 32; o > 0; o >>= 1) n_relaxed += __shfl_xor(n_relaxed, o);
+        if (tid == 0) atomicAdd(&scr.stats[0], n_taken);
+        if (lane == 0) atomicAdd(&scr.stats[1], (unsigned long long)n_relaxed);
     }
 }
 
@@ -2467,34 +2452,45 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
     hipError_t e = launch_fill_u32(s, reinterpret_cast<uint32_t*>(scr.work), 0u, 1);
     if (e != hipSuccess) return e;
     int blocks = (slots + (kWG / 64) - 1) / (kWG / 64);
-    if (variant >= 32) {
-        // chain-contracted search, one workgroup per tree (scratch slot = workgroup)
-        if (!net.cbuf) return hipErrorInvalidValue;
-        blocks = min(blocks, scr.nslots);
+    if (variant >= 32 || (variant >= 8 && variant < 16)) {
+        // node queue, one workgroup of 128 U threads per tree (scratch slot =
+        // workgroup), V records per thread and step.  256 threads and 4 records by
+        // default: a step's entries are 100 to 250 on road networks and grids, so
+        // 512 threads mostly wait at barriers and 128 take twice the steps, and
+        // two records leave most rows to a second step.  Metro network, 1,000
+        // trees, <2, 4> / <4, 4> / <1, 4> / <2, 2>: 2.4 / 2.8 / 2.7 / 3.3 ms;
+        // 22,801-node grid, 300 trees, congested: 0.80 / 1.36 / 1.20 / 1.55.
+        const bool ct = variant >= 32;
+        if (ct && !net.cbuf) return hipErrorInvalidValue;
+        static const int units[] = {1, 1, 2, 4, 2, 4};
+        const int v = min(variant - (ct ? 32 : 8), 5), nt = 128 * units[v];
+        blocks = min((slots * 64 + nt - 1) / nt, min(scr.near_w, scr.far_w) / 4);
         if (blocks <= 0) return hipErrorInvalidValue;
-        dim3 g(blocks), b(kWG);
-#define QDTA_SSSP_CT(U, V) \
-    hipLaunchKernelGGL((k_sssp_wg<U, V, true>), g, b, 0, s, net, dem, radj, labels, scr, st, delta_inst, early, \
-                       t_begin, t_end)
-        switch (variant - 32) {
-            case 0: QDTA_SSSP_CT(1, 2); break;
-            case 1: QDTA_SSSP_CT(1, 4); break;
-            case 2:
-                hipLaunchKernelGGL((k_sssp_wg<2, 4, true, 7>), g, b, 0, s, net, dem, radj, labels, scr, st, delta_inst,
-                                   early, t_begin, t_end);
-                break;
-            case 3: QDTA_SSSP_CT(4, 4); break;
-            case 4: QDTA_SSSP_CT(2, 2); break;
-            default: QDTA_SSSP_CT(4, 2); break;
+#define QDTA_SSSP_WG(...)                                                                                          \
+    hipLaunchKernelGGL((k_sssp_wg<__VA_ARGS__>), dim3(blocks), dim3(nt), 0, s, net, dem, radj, labels, scr, st,     \
+                       delta_inst, early, t_begin, t_end)
+        switch (2 * v + ct) {
+            case 0: QDTA_SSSP_WG(1, 2, false); break;
+            case 1: QDTA_SSSP_WG(1, 2, true); break;
+            case 2: QDTA_SSSP_WG(1, 4, false); break;
+            case 3: QDTA_SSSP_WG(1, 4, true); break;
+            case 4: QDTA_SSSP_WG(2, 4, false); break;
+            case 5: QDTA_SSSP_WG(2, 4, true, 7); break;
+            case 6: QDTA_SSSP_WG(4, 4, false); break;
+            case 7: QDTA_SSSP_WG(4, 4, true); break;
+            case 8: QDTA_SSSP_WG(2, 2, false); break;
+            case 9: QDTA_SSSP_WG(2, 2, true); break;
+            case 10: QDTA_SSSP_WG(4, 2, false); break;
+            default: QDTA_SSSP_WG(4, 2, true); break;
         }
-#undef QDTA_SSSP_CT
+#undef QDTA_SSSP_WG
         e = hipGetLastError();
-        if (e != hipSuccess || !fill) return e;
+        if (e != hipSuccess || !ct || !fill) return e;
         return launch_chain_fill(s, net, dem, labels, st, t_begin, t_end);   // the left-out chain nodes
     }
     if (variant >= 24) {
         // one workgroup per tree, every thread relaxing its own nodes' in-links
-        blocks = min(blocks, scr.nslots);
+        blocks = min(blocks, min(scr.near_w, scr.far_w / 2));
         if (blocks <= 0) return hipErrorInvalidValue;
         dim3 g(blocks), b(kWG);
 #define QDTA_SSSP_WN(U, V) \
@@ -2511,7 +2507,7 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
     }
     if (variant >= 16) {
         // block-local trees, one workgroup per tree (scratch slot = workgroup)
-        blocks = min(blocks, scr.nslots);
+        blocks = min(blocks, min(scr.near_w, scr.far_w / 2));
         if (blocks <= 0) return hipErrorInvalidValue;
         dim3 g(blocks), b(kWG);
 #define QDTA_SSSP_BLK(B, KB) \
@@ -2526,27 +2522,8 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
 #undef QDTA_SSSP_BLK
         return hipGetLastError();
     }
-    if (variant >= 8) {
-        // one workgroup per tree (scratch slot = workgroup)
-        blocks = min(blocks, scr.nslots);
-        if (blocks <= 0) return hipErrorInvalidValue;
-        dim3 g(blocks), b(kWG);
-#define QDTA_SSSP_WG(U, V) \
-    hipLaunchKernelGGL((k_sssp_wg<U, V, false>), g, b, 0, s, net, dem, radj, labels, scr, st, delta_inst, early, \
-                       t_begin, t_end)
-        switch (variant - 8) {
-            case 0: QDTA_SSSP_WG(1, 2); break;
-            case 1: QDTA_SSSP_WG(1, 4); break;
-            case 2: QDTA_SSSP_WG(2, 4); break;
-            case 3: QDTA_SSSP_WG(4, 4); break;
-            case 4: QDTA_SSSP_WG(2, 2); break;
-            default: QDTA_SSSP_WG(4, 2); break;
-        }
-#undef QDTA_SSSP_WG
-        return hipGetLastError();
-    }
     // one wavefront per tree (scratch slot = wavefront)
-    blocks = min(blocks, scr.nslots / (kWG / 64));
+    blocks = min(blocks, min(scr.near_w, scr.far_w / 2) / (kWG / 64));
     if (blocks <= 0) return hipErrorInvalidValue;
     dim3 g(blocks), b(kWG);
 #define QDTA_SSSP(U, V) \

@@ -79,9 +79,9 @@ struct qdta_ctx {
 
     // demand layout
     int64_t Q = 0, P = 0, nmax = 0;
-    int slots = 0, scr_slots = 0;
+    int slots = 0;
+    int scr_near_w = 0, scr_far_w = 0; // words of the near and far queues per scr_nmax (see Scratch)
     int64_t scr_nmax = 0;
-    bool scr_wide = false;             // queues sized for the contracted search's entries
     size_t label_count = 0;
     DBuf<int32_t> dest_node, dest_inst, qptr, leg_orig, leg_q;
     DBuf<int64_t> dest_lab, leg_dfx;
@@ -109,7 +109,7 @@ struct qdta_ctx {
     int64_t c_chains = 0, c_left = 0;
     DBuf<int32_t> crptr, inst_chain;
     DBuf<int4> ch_hdr;
-    DBuf<uint32_t> cbuf;
+    DBuf<uint32_t> cbuf, crow;
     DBuf<uint2> anc;
     DBuf<int2> cslot;
     int32_t c_fill_chunks = 0;         // most chain chunks of one instance (k_chain_fill items)
@@ -366,12 +366,12 @@ bool opts_ok(qdta_ctx* c, const qdta_opts* o) {
 int tree_waves(const qdta_opts* o) { return (o->sssp_kernel < 2 && o->tree_waves == 1) ? 1 : 4; }
 // FW updates a solve may apply (iterates 1..this, plus the initial AON)
 int hist_iters(const qdta_opts* o) { return o->fixed_iters > 0 ? o->fixed_iters : std::max(o->max_iter, 0); }
-bool uses_contraction(const qdta_opts* o);
-// wavefronts in flight per CU by default: what the kernels' registers allow
-// (one tree per wavefront: 32; the contracted <2, 4> form: 28; else 24)
+// wavefronts in flight per CU by default: what the kernels' registers and LDS
+// allow (one tree per wavefront: 32; the node queue with a workgroup per tree:
+// 16, four workgroups' LDS; else 24)
 int waves_per_cu(const qdta_opts* o) {
     if (o->waves_per_cu) return o->waves_per_cu;
-    return tree_waves(o) == 1 ? 32 : uses_contraction(o) ? 28 : 24;
+    return tree_waves(o) == 1 ? 32 : o->sssp_kernel == 2 || o->sssp_kernel == 3 ? 24 : 16;
 }
 double delta_scale(const qdta_opts* o) { return o->delta_scale > 0.0 ? o->delta_scale : 10.0; }
 // Block size of each block-local shape (qdta_opts.sssp_shape 1..4)
@@ -532,6 +532,7 @@ NetDev net_view(qdta_ctx* c, const qdta_opts* o = nullptr) {
     v.inst = c->d_inst.p;
     const bool ct = c->c_built;
     v.crptr = ct ? c->crptr.p : nullptr;
+    v.crow = ct ? c->crow.p : nullptr;
     v.cbuf = ct ? c->cbuf.p : nullptr;
     v.cslot = ct ? c->cslot.p : nullptr;
     v.anc = ct ? c->anc.p : nullptr;
@@ -563,21 +564,18 @@ NetDev net_view(qdta_ctx* c, const qdta_opts* o = nullptr) {
 // label is the lesser of the two folds from the ends' labels (see the kernel).
 // Records are 4 words: (source | form << 30, then up to three costs in the
 // order they are added).  Form 0 is a plain link (one cost), forms 1 and 2 a
-// chain of one or two nodes (two or three costs inline), form 3 a longer
-// chain, whose second word is the offset of its cost block (count, then the
-// costs).  Inline costs spare the search a dependent read per relaxation.
-// The last word of forms 0, 1 and 3 holds the source's packed row
-// (pack_row), which the search queues with the node.
-// After the records and cost blocks, one fill block per chain: per chain
+// chain of one or two nodes (two or three costs): inline costs spare the
+// search a dependent read per relaxation, which is why chains are no longer
+// than that.  The last word of forms 0 and 1 holds the source's packed row
+// (pack_row), which the search queues with the node; form 2's is read from
+// crow together with the label.
+// After the records, one fill block per chain: per chain
 // node x1..xk its id, the cost of its link toward v and of its link toward u
 // (+inf bits where the link is missing); the chain's header (u, v, k, word
 // offset of the block) is in ch_hdr.  k_chain_fill labels the chain nodes.
 // Words at most: one record per link at most (a chain's record stands for
-// two links or more), per chain of k > 2 nodes two cost blocks of
-// ceil((k + 2) / 4) * 4 words (under 6 words per left-out node), and per
-// chain a fill block of 3k words.
-constexpr int kInlineCosts = 3;
-size_t contraction_words(int64_t N, int64_t M) { return 4 * (size_t)M + 4 + 9 * (size_t)N; }
+// two links or more) and per chain a fill block of 3k words.
+size_t contraction_words(int64_t N, int64_t M) { return 4 * (size_t)M + 4 + 3 * (size_t)N; }
 
 int build_contraction(qdta_ctx* c) {
     const int64_t N = c->N;
@@ -748,35 +746,22 @@ int build_contraction(qdta_ctx* c) {
     for (const Rec& r : recs) crp[r.head + 1]++;
     for (int64_t v = 0; v < N; ++v) crp[v + 1] += crp[v];
     size_t words = 4 * recs.size();
-    std::vector<size_t> blk(sc_links.size(), 0);
-    for (size_t s = 0; s < sc_links.size(); ++s) {
-        if (sc_links[s].size() <= (size_t)kInlineCosts) continue;
-        blk[s] = words;
-        words += (1 + sc_links[s].size() + 3) / 4 * 4;
-    }
     std::vector<uint32_t> cbuf(words, 0u);
     for (size_t k = 0; k < recs.size(); ++k) {
         const Rec& r = recs[k];
         // the last word carries the source's packed row where no cost takes it
-        const uint32_t row = pack_row(crp[r.src], crp[r.src + 1] - crp[r.src]);
-        cbuf[4 * k + 3] = row;
+        cbuf[4 * k + 3] = pack_row(crp[r.src], crp[r.src + 1] - crp[r.src]);
         if (r.link >= 0) {
             cbuf[4 * k] = (uint32_t)r.src;
             cslot[r.link].x = (int32_t)(4 * k + 1);
             continue;
         }
         const std::vector<int32_t>& ls = sc_links[r.chain];
-        if (ls.size() <= (size_t)kInlineCosts) {
-            cbuf[4 * k] = (uint32_t)r.src | (uint32_t)(ls.size() - 1) << 30;
-            for (size_t j = 0; j < ls.size(); ++j) cslot[ls[j]].x = (int32_t)(4 * k + 1 + j);
-        } else {
-            const size_t b = blk[r.chain];
-            cbuf[4 * k] = (uint32_t)r.src | 3u << 30;
-            cbuf[4 * k + 1] = (uint32_t)b;
-            cbuf[b] = (uint32_t)ls.size();
-            for (size_t j = 0; j < ls.size(); ++j) cslot[ls[j]].x = (int32_t)(b + 1 + j);
-        }
+        cbuf[4 * k] = (uint32_t)r.src | (uint32_t)(ls.size() - 1) << 30;
+        for (size_t j = 0; j < ls.size(); ++j) cslot[ls[j]].x = (int32_t)(4 * k + 1 + j);
     }
+    std::vector<uint32_t> crow(N);
+    for (int64_t v = 0; v < N; ++v) crow[v] = pack_row(crp[v], crp[v + 1] - crp[v]);
     // fill blocks and chain headers
     const size_t nch = ch_end.size();
     std::vector<int4> ch_hdr(nch);
@@ -813,6 +798,7 @@ int build_contraction(qdta_ctx* c) {
     // contraction_words), so later rebuilds fit in place
     const bool ws = c->ws_base != nullptr;
     RC(upload(c, c->crptr, crp));
+    RC(upload(c, c->crow, crow));
     RC(upload(c, c->cbuf, cbuf, ws ? contraction_words(N, c->M) : 0));
     RC(upload(c, c->cslot, cslot));
     RC(upload(c, c->anc, anc));
@@ -845,12 +831,6 @@ int ensure_contraction(qdta_ctx* c, const int32_t* roots, size_t nroots) {
 // before a search of the current demand's trees
 int ensure_contract(qdta_ctx* c, const qdta_opts* o) {
     if (!uses_contraction(o)) return QDTA_OK;
-    // queues sized for the other search's narrower entries: widen them in place
-    if (!c->scr_wide && c->scr_slots > 0) {
-        RC(dalloc(c, c->nearq, (size_t)c->scr_slots * (size_t)c->scr_nmax * 2));
-        RC(dalloc(c, c->farq, (size_t)c->scr_slots * (size_t)c->scr_nmax * 4));
-        c->scr_wide = true;
-    }
     return ensure_contraction(c, c->h_dest_node.data(), c->h_dest_node.size());
 }
 
@@ -858,25 +838,33 @@ int ensure_contract(qdta_ctx* c, const qdta_opts* o) {
 // are n 32-bit words at dest_lab[t], each tree padded to 32 words (128 bytes).
 int64_t tree_words(int64_t n) { return (n + 31) / 32 * 32; }
 
-// c->slots: wavefronts of a shortest-path launch (whole workgroups of four).
-// Scratch: one slot per tree in flight, i.e. per wavefront (tree_waves 1) or
-// per workgroup (tree_waves 4); launches never use more slots than exist.
-int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw, bool wide) {
-    // every tree takes tw wavefronts; never more than wpc per CU
-    int slots = (int)std::min<int64_t>(std::max<int64_t>(trees, 1) * (tw == 1 ? 1 : 4), (int64_t)c->cus * wpc);
-    slots = (slots + 3) / 4 * 4;
-    c->slots = slots;
-    const int need = tw == 1 ? slots : slots / 4;
-    nmax = std::max<int64_t>(nmax, 1) + 65;      // near rings: n queued nodes in n + (up to 64) slots
-    // the contracted search's queue entries are twice as wide (see Scratch)
-    if (need > c->scr_slots || nmax > c->scr_nmax || (wide && !c->scr_wide)) {
-        int64_t ns = std::max<int64_t>(need, c->scr_slots), nm = std::max<int64_t>(nmax, c->scr_nmax);
-        const bool w = wide || c->scr_wide;
-        RC(dalloc(c, c->nearq, (size_t)ns * nm * (w ? 2 : 1)));
-        RC(dalloc(c, c->farq, (size_t)ns * nm * (w ? 4 : 2)));
-        c->scr_slots = (int)ns;
+// Queue entries per slot: the near rings' n + 64 at most, and the far queue's
+// window beyond one per node.
+int64_t scratch_nmax(int64_t n) { return std::max<int64_t>(n, 1) + 65 + kSearchSlack; }
+
+// Wavefronts of a shortest-path launch (whole workgroups of four): every tree
+// takes tw of them, and never more than wpc per CU.
+int search_slots(const qdta_ctx* c, int64_t trees, int wpc, int tw) {
+    const int slots = (int)std::min<int64_t>(std::max<int64_t>(trees, 1) * (tw == 1 ? 1 : 4), (int64_t)c->cus * wpc);
+    return (slots + 3) / 4 * 4;
+}
+
+// Scratch per tree in flight: one wavefront's takes 1 + 2 words of the queues
+// (near, far) per nmax, one workgroup's (four wavefronts) at most 4 + 4; so
+// the near queue has a word per wavefront in either form.  Launches never use
+// more slots than exist.
+int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw) {
+    c->slots = search_slots(c, trees, wpc, tw);
+    const int near_w = c->slots, far_w = tw == 1 ? 2 * c->slots : c->slots;
+    nmax = scratch_nmax(nmax);
+    if (near_w > c->scr_near_w || far_w > c->scr_far_w || nmax > c->scr_nmax) {
+        const int nw = std::max(near_w, c->scr_near_w), fw = std::max(far_w, c->scr_far_w);
+        const int64_t nm = std::max<int64_t>(nmax, c->scr_nmax);
+        RC(dalloc(c, c->nearq, (size_t)nw * nm));
+        RC(dalloc(c, c->farq, (size_t)fw * nm));
+        c->scr_near_w = nw;
+        c->scr_far_w = fw;
         c->scr_nmax = nm;
-        c->scr_wide = w;
     }
     RC(dalloc(c, c->work, 1));
     if (!c->sssp_stats.p) {
@@ -889,10 +877,10 @@ int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw, bo
 }
 
 // wpc = 0: the demand tables only (no shortest-path scratch).
-int ensure_demand(qdta_ctx* c, int wpc, int tw = 1, bool wide = false) {
+int ensure_demand(qdta_ctx* c, int wpc, int tw = 1) {
     RC(ensure_network(c));
     if (!c->dem_dirty)
-        return wpc > 0 ? ensure_scratch(c, (int64_t)plan_dests(c, (size_t)c->Q), c->nmax, wpc, tw, wide) : QDTA_OK;
+        return wpc > 0 ? ensure_scratch(c, (int64_t)plan_dests(c, (size_t)c->Q), c->nmax, wpc, tw) : QDTA_OK;
     int64_t total_legs = 0;
     for (const Instance& I : c->inst) total_legs += (int64_t)I.orig.size();
     if (total_legs >= INT32_MAX) return set_err(c, QDTA_EARG, "total legs beyond int32 ids");
@@ -956,7 +944,7 @@ int ensure_demand(qdta_ctx* c, int wpc, int tw = 1, bool wide = false) {
     RC(dalloc(c, c->absorb_q, pq));
     RC(dalloc(c, c->int_node, pp));
     RC(dalloc(c, c->int_tau, pp));
-    if (wpc > 0) RC(ensure_scratch(c, (int64_t)pq, nmax, wpc, tw, wide));
+    if (wpc > 0) RC(ensure_scratch(c, (int64_t)pq, nmax, wpc, tw));
     c->dem_dirty = false;
     c->solved = false;
     c->lab_hist_ok.clear();
@@ -1001,9 +989,15 @@ Scratch scr_view(qdta_ctx* c) {
     s.farq = c->farq.p;
     s.nmax = c->scr_nmax;
     s.work = c->work.p;
-    s.nslots = c->scr_slots;
+    s.near_w = c->scr_near_w;
+    s.far_w = c->scr_far_w;
     s.stats = c->sssp_stats.p;
     return s;
+}
+
+// Workgroups of the tie fallback: each takes nmax words of either queue.
+int fallback_slots(const qdta_ctx* c, int64_t trees) {
+    return (int)std::min<int64_t>(std::max(std::min(c->scr_near_w, c->scr_far_w) / 4, 1), std::max<int64_t>(trees, 1));
 }
 
 FlagsDev flags_view(qdta_ctx* c) {
@@ -1118,7 +1112,7 @@ int aon_core(qdta_ctx* c, const qdta_opts* o, const float* cost, const float* ti
     }
     HIPCHECK(c, launch_fallback(c->stream, net, dem, c->labels.p, cost, time_cost ? time_cost : cost, y, stop, st, fl,
                                 scr_view(c),
-                                (int)std::min<int64_t>(c->scr_slots, std::max<int64_t>(c->Q, 1)), 0, nullptr, nullptr,
+                                fallback_slots(c, c->Q), 0, nullptr, nullptr,
                                 nullptr, 0, nullptr, 0, stop_delay));
     if (marks) RC(prof_mark(c, PH_WALK, 1));
     return QDTA_OK;
@@ -1474,19 +1468,20 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     add(labels, 4); add(pq, 4); add(pp, 4); add(pp, 4);
     if (o->load_form == 2) { add(labels, 4); add(labels, 8); }   // plain-interval loading by merged paths
     if (uses_contraction(o)) {                                    // chain contraction (at its bounds)
-        add(N + 1, 4); add(contraction_words(N, M), 4); add(M, 8); add(N, 8);
+        add(N + 1, 4); add(N, 4); add(contraction_words(N, M), 4); add(M, 8); add(N, 8);
         add(N, 16); add(ni + 1, 4);
     }
     // shortest-path scratch (as ensure_scratch sizes it)
     {
         const int tw = tree_waves(o), wpc = waves_per_cu(o);
-        int slots = (int)std::min<int64_t>(std::max<int64_t>((int64_t)pq, 1) * (tw == 1 ? 1 : 4),
-                                           (int64_t)c->cus * wpc);
-        slots = (slots + 3) / 4 * 4;
-        const int64_t need = tw == 1 ? slots : slots / 4;
-        const int64_t nm = std::max<int64_t>(nmax, 1) + 65;
-        const size_t qw = uses_contraction(o) || o->sssp_kernel == 0 ? 2 : 1;   // wider entries (Scratch)
-        add((size_t)(need * nm) * qw, 4); add((size_t)(need * nm * 2) * qw, 4);
+        const size_t nm = (size_t)scratch_nmax(nmax);
+        size_t near_w = (size_t)search_slots(c, (int64_t)pq, wpc, tw), far_w = tw == 1 ? 2 * near_w : near_w;
+        if (o->sssp_kernel == 0) {                                // either form may be asked for later
+            const size_t other = (size_t)search_slots(c, (int64_t)pq, wpc, tw == 1 ? 4 : 1);
+            near_w = std::max(near_w, other);
+            far_w = std::max(far_w, tw == 1 ? other : 2 * other);
+        }
+        add(near_w * nm, 4); add(far_w * nm, 4);
         add(1, 4); add(2, 8); add(ni, 4); add(ni, 8);
     }
     if (o->keep_history) {
@@ -1728,9 +1723,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         if ((rc = dalloc(c, lab, (size_t)nq * tree_words(I.n)))) break;
         if ((rc = dalloc(c, aq, nq))) break;
         int saved_slots = c->slots;
-        if ((rc = ensure_scratch(c, nq, std::max<int64_t>(c->nmax, I.n), waves_per_cu(o), tree_waves(o),
-                                 uses_contraction(o))))
-            break;
+        if ((rc = ensure_scratch(c, nq, std::max<int64_t>(c->nmax, I.n), waves_per_cu(o), tree_waves(o)))) break;
         int slots = c->slots;
         c->slots = saved_slots;
         DemDev dem;
@@ -1757,7 +1750,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         FlagsDev fl = flags_view(c);
         fl.absorb_q = aq.p;
         if ((e = launch_fallback(c->stream, net, dem, lab.p, c->cost.p, c->cost.p, nullptr, nullptr, nullptr, fl,
-                                 scr_view(c), (int)std::min<int64_t>(c->scr_slots, nq), 0, nullptr, nullptr, nullptr,
+                                 scr_view(c), fallback_slots(c, nq), 0, nullptr, nullptr, nullptr,
                                  1, succ, I.n)))
             { rc = set_err(c, QDTA_EHIP, "fallback: %s", hipGetErrorString(e)); break; }
         std::vector<int32_t> ha(nq);
@@ -1777,7 +1770,7 @@ int qdta_aon(qdta_ctx* c, const qdta_opts* o, const float* cost, int64_t* y, int
     c->err.clear();
     if (!opts_ok(c, o)) return QDTA_EARG;
     if (!cost || !y) return set_err(c, QDTA_EARG, "null array");
-    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
+    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o)));
     RC(apply_rule(c, o));
     RC(ensure_sweep(c, o));
     RC(ensure_contract(c, o));
@@ -1803,7 +1796,7 @@ int qdta_ls_eval(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const int64_
     if (!opts_ok(c, o)) return QDTA_EARG;
     if (K < 1 || K > kMaxK || !f || !y || !alphas || !sums) return set_err(c, QDTA_EARG, "bad arguments");
     RC(ensure_network(c));
-    if (c->dem_dirty) RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
+    if (c->dem_dirty) RC(ensure_demand(c, waves_per_cu(o), tree_waves(o)));
     int ni = (int)c->inst.size();
     RC(clear_flags(c));
     HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->ls_acc.p), 0, (int64_t)ni * K * 6 * kLsReps));
@@ -1849,7 +1842,7 @@ int qdta_line_search(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
     if (!opts_ok(c, o)) return QDTA_EARG;
     if (!f || !y || !alpha_out || j < 1) return set_err(c, QDTA_EARG, "bad arguments");
     RC(ensure_network(c));
-    if (c->dem_dirty) RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
+    if (c->dem_dirty) RC(ensure_demand(c, waves_per_cu(o), tree_waves(o)));
     int ni = (int)c->inst.size();
     RC(init_state(c, true, j));
     RC(clear_flags(c));
@@ -1877,7 +1870,7 @@ int qdta_fw_begin(qdta_ctx* c, const qdta_opts* o) {
     if (!opts_ok(c, o)) return QDTA_EARG;
     for (const Instance& I : c->inst)
         if (!I.has_demand) return set_err(c, QDTA_ESTATE, "every instance needs qdta_set_demand before solving");
-    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
+    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o)));
     RC(apply_rule(c, o));
     RC(ensure_sweep(c, o));
     RC(ensure_contract(c, o));
@@ -2101,8 +2094,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     if (!(budget_ms > 0.0)) return set_err(c, QDTA_EARG, "budget_ms must be > 0");
     for (const Instance& I : c->inst)
         if (!I.has_demand) return set_err(c, QDTA_ESTATE, "autotune needs the demand of every instance");
-    RC(ensure_demand(c, waves_per_cu(o), 1,               // slots for either kernel form
-                     o->sssp_kernel == 0 || o->sssp_kernel == 4));
+    RC(ensure_demand(c, waves_per_cu(o), 1));             // slots for either kernel form
     RC(apply_rule(c, o));
     if (o->sssp_kernel == 0 || o->sssp_kernel == 4)       // trials of either tree form
         RC(ensure_contraction(c, c->h_dest_node.data(), c->h_dest_node.size()));
@@ -2116,7 +2108,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     hipEvent_t e0, e1;
     HIPCHECK(c, hipEventCreate(&e0));
     HIPCHECK(c, hipEventCreate(&e1));
-    static const int shapes[] = {3, 4, 2, 5};
+    static const int shapes[] = {3, 4, 2};
     static const double scales[] = {10.0, 5.0, 20.0, 2.5, 1.25};
     static const int tws[] = {4, 1};
     // trial order: the bucket widths at the starting shape first (on heavily
@@ -2352,7 +2344,7 @@ int qdta_advance_interval(qdta_ctx* c, const qdta_opts* o) {
         HIPCHECK(c, launch_walk(c->stream, net, dem, lab, c->cfin.p, nullptr, nullptr, stj, fl, 1, lamj,
                                 c->r_dense.p, c->done_fx.p, 0, -1, nullptr, progress ? &tr : nullptr));
         HIPCHECK(c, launch_fallback(c->stream, net, dem, lab, cj, c->cfin.p, nullptr, nullptr, stj, fl,
-                                    scr_view(c), (int)std::min<int64_t>(c->scr_slots, std::max<int64_t>(c->Q, 1)), 1,
+                                    scr_view(c), fallback_slots(c, c->Q), 1,
                                     lamj, c->r_dense.p, c->done_fx.p, 0, nullptr, 0, nullptr,
                                     progress ? &tr : nullptr));
     }
@@ -2474,7 +2466,7 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
     const int J = I.solved_iters;
     if (J < 0 || (int)I.hist_alpha.size() < J + 1 || c->hist_iters_cap < (size_t)J + 1)
         return set_err(c, QDTA_ESTATE, "no iteration history");
-    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o), uses_contraction(o)));
+    RC(ensure_demand(c, waves_per_cu(o), tree_waves(o)));
     RC(apply_rule(c, o));
     RC(ensure_contract(c, o));
     const int64_t P = c->P, M = c->M;

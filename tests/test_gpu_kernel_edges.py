@@ -115,3 +115,49 @@ def test_walk_at_split_edges(q, orc, legs):
             ctx.aon(q.default_opts(trunc_rule=rule), dev(cost), y, stop)
             assert np.array_equal(y.cpu().numpy(), ref_y)
             assert np.array_equal(stop.cpu().numpy(), ref_stop)
+
+
+def hub_net(rng, leaves, arms):
+    """A ring of `arms` nodes around a hub that every leaf has a link to and from: the hub's record row is longer than
+    one piece of a step (4), than a packed count (63) or than the LDS buffer (512), by `leaves`."""
+    n = 1 + leaves + arms
+    tail, head = [], []
+    for v in range(1, 1 + leaves):
+        tail += [v, 0]
+        head += [0, v]
+    ring = list(range(1 + leaves, n))
+    for i, v in enumerate(ring):
+        w = ring[(i + 1) % arms]
+        tail += [v, w, v, 1 + i % leaves]
+        head += [w, v, 1 + i % leaves, v]
+    tail, head = np.array(tail), np.array(head)
+    order = np.lexsort((head, tail))
+    row = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(tail, minlength=n), out=row[1:])
+    m = tail.size
+    return Network(n, row, head[order].astype(np.int32), rng.integers(1, 9, m).astype(np.float32),
+                   np.full(m, 900.0, np.float32))
+
+
+@pytest.mark.parametrize("leaves", [3, 4, 5, 8, 9, 62, 63, 64, 257, 1500])
+@pytest.mark.parametrize("kernel", [1, 4])
+def test_search_rows_and_queues_at_edges(q, orc, leaves, kernel):
+    """Rows cut into pieces, rows that do not pack, buffers that overflow into the rings, equal candidates (whole-number
+    costs), every workgroup size, tiny and huge bucket widths."""
+    import torch
+    rng = np.random.default_rng(leaves)
+    net = hub_net(rng, leaves, 40)
+    dests = np.unique(rng.integers(0, net.n, 6)).astype(np.int32)
+    ref = [orc.tree(net, net.fftt, int(t)) for t in dests]
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], float("inf"))
+        dist = torch.empty((dests.size, net.n), dtype=torch.float32, device="cuda")
+        succ = torch.empty((dests.size, net.n), dtype=torch.int32, device="cuda")
+        for shape in (1, 2, 3, 4, 5, 6):
+            for scale in (0.01, 1.0, 1e6):
+                o = q.default_opts(sssp_kernel=kernel, sssp_shape=shape, delta_scale=scale)
+                ctx.trees(o, 0, dev(net.fftt), dev(dests), dist, succ)
+                for k in range(dests.size):
+                    assert np.array_equal(dist[k].cpu().numpy(), ref[k][0]), (shape, scale, k)
+                    assert np.array_equal(succ[k].cpu().numpy(), ref[k][1]), (shape, scale, k)
