@@ -161,3 +161,33 @@ def test_search_rows_and_queues_at_edges(q, orc, leaves, kernel):
                 for k in range(dests.size):
                     assert np.array_equal(dist[k].cpu().numpy(), ref[k][0]), (shape, scale, k)
                     assert np.array_equal(succ[k].cpu().numpy(), ref[k][1]), (shape, scale, k)
+
+
+@pytest.mark.parametrize("legs", [1, 129, 3000])
+def test_residual_walk_counts_completed_weight_of_mixed_instances(q, orc, legs):
+    """A workgroup of the residual walk whose legs belong to several instances: completed and unfinished weight of
+    each instance, against the oracle's residual."""
+    import synth
+    rng = np.random.default_rng(legs)
+    nets, dems = [], []
+    for k in (5, 7, 6):
+        net = synth.grid_network(k, rng)
+        o, d = rng.integers(0, net.n, legs).astype(np.int32), rng.integers(0, net.n, legs).astype(np.int32)
+        nets.append(net)
+        dems.append((o, d, rng.uniform(0.1, 5.0, legs)))
+    with q.Context() as ctx:
+        opts = q.default_opts(fixed_iters=3, keep_history=1, ls_mode=q.LS_MSA)
+        for i, (net, dm) in enumerate(zip(nets, dems)):
+            ctx.add(net)
+            ctx.set_demand(i, *dm, 300.0)
+        ctx.solve(opts)
+        ctx.advance_interval(opts)
+        got = [ctx.residual(i) for i in range(3)]
+    for (net, dm), (ro, rd, rw, done) in zip(zip(nets, dems), got):
+        lo, ld, lw = orc.demand_legs(*dm)
+        ref = orc.fw_solve(net, lo, ld, lw, dt_s=300.0, rule=orc.RULE_CEIL, fixed_iters=3, ls_mode=orc.LS_MSA,
+                           keep_history=True)
+        eo, ed, ew, edone = orc.residual(net, ref.f, ref.hist_alpha, ref.hist_cost, lo, ld, lw, dt_s=300.0)[:4]
+        eo, ed, ew = orc.merge_legs(eo, ed, ew)[:3]
+        assert np.array_equal(ro, eo) and np.array_equal(rd, ed) and np.array_equal(rw, ew)
+        assert done == edone
