@@ -45,6 +45,11 @@ constexpr int kLsReps = 8;
 // step may queue this many before the queue is compacted.
 constexpr int kSearchSlack = 2560;
 
+// Copies of the gap and objective sums of an instance, for the same reason:
+// [inst][copy][2][3] words, zero between the kernels that use them.
+constexpr int kSumReps = 8;
+constexpr int kLogParts = kChunk / kWG;  // workgroups per link chunk in the kernels with one link per thread
+
 // One shortest-path label word: FP32 bits of the distance, under a flag bit 31
 // that some of the search kernels keep while they run (readers mask it).
 typedef uint32_t label_t;
@@ -116,6 +121,7 @@ struct NetDev {
     int32_t fill_chunks;     // most chunks of kFillChunk chains in one instance
     const int32_t* blk_inst; // [nblk] instance of each link chunk
     const int32_t* blk_start;// [nblk] first global link of each chunk
+    const int32_t* inst_blk; // [ninst] first chunk of each instance
     int32_t ninst, nblk;
     int64_t N, M;
     int32_t objective;       // 0 user equilibrium (BPR costs route, Beckmann objective, Eq. 6);
@@ -163,16 +169,21 @@ hipError_t launch_fill_u32(hipStream_t s, uint32_t* p, uint32_t v, int64_t count
 hipError_t launch_fill_i64(hipStream_t s, int64_t* p, int64_t v, int64_t count);
 
 // cost: the routing costs (marginal ones under net.objective = 1); tcost (may
-// be NULL): the travel times BPR(f) as well
+// be NULL): the travel times BPR(f) as well; logpart (may be NULL): the log
+// sums launch_prep reads, [nblk][kLogParts]
 hipError_t launch_bpr(hipStream_t s, const NetDev& net, const int64_t* f, double alpha, int beta,
                       float* cost, uint2* radj, const InstState* st, int only_active, int* err,
-                      float* tcost = nullptr);
+                      float* tcost = nullptr, double* logpart = nullptr);
 
-hipError_t launch_gap_sums(hipStream_t s, const NetDev& net, const float* cost, const int64_t* f,
-                           const int64_t* y, long long* acc /*[ninst][2][3]*/, const InstState* st, int* err);
-
-hipError_t launch_gap_decide(hipStream_t s, int ninst, const long long* acc, InstState* st, int stop_rule,
-                             double tol, int fixed_iters, int cap_iter);
+// Stop test of an iteration and start of its line search (see k_gap); acc:
+// [ninst][kSumReps][2][3], ticket: [ninst], both zero before and after
+struct GapRule {
+    int stop_rule, fixed_iters, cap_iter, K, ls_mode;
+    double tol, dx;
+};
+hipError_t launch_gap(hipStream_t s, const NetDev& net, const float* cost, const int64_t* f, const int64_t* y,
+                      long long* acc, InstState* st, int* err, unsigned int* ticket, const GapRule& rule,
+                      double* alphas, long long* ls_acc);
 
 hipError_t launch_ls_begin(hipStream_t s, int ninst, InstState* st, double* alphas, int K, int ls_mode,
                            double dx, long long* ls_acc, int only_fallback);
@@ -194,38 +205,39 @@ hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, co
 hipError_t launch_ls_decide(hipStream_t s, int ninst, InstState* st, double* alphas, const LsRule& rule,
                             long long* ls_acc);
 
-hipError_t launch_stall_check(hipStream_t s, int ninst, InstState* st, int fixed_iters);
 hipError_t launch_ls_export(hipStream_t s, int ninst, const long long* ls_acc, int K, int reps, int64_t* sums);
 // device address of the static scratch of the allocation-free line search on
 // `device` (which must be current); looked up once per device
 hipError_t noalloc_scratch(int device, long long** out);
 
-hipError_t launch_obj_pair(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y,
-                           double alpha_b, int beta, long long* acc /*[ninst][2][3]*/, const InstState* st,
-                           int use_alpha, int* err);
+// acc, ticket as launch_gap's
+hipError_t launch_obj(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b, int beta,
+                      long long* acc, InstState* st, int apply_rule, double tol, int* err, unsigned int* ticket);
 
-hipError_t launch_obj_decide(hipStream_t s, int ninst, const long long* acc, InstState* st, double tol,
-                             int apply_rule);
-
+// alpha_per_inst NULL: the running iteration's step of each live instance
 hipError_t launch_fw_update(hipStream_t s, const NetDev& net, int64_t* f, const int64_t* y,
-                            const double* alpha_per_inst, const InstState* st);
+                            const double* alpha_per_inst, InstState* st, int fixed_iters = 0);
 
 hipError_t launch_copy_alpha(hipStream_t s, int ninst, const InstState* st, double* out);
-hipError_t launch_after_update(hipStream_t s, int ninst, InstState* st);
-hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj);
+hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart);
 // contracted records' costs from the forward link records (after a rebuild)
 hipError_t launch_cslot_init(hipStream_t s, const NetDev& net);
 
-hipError_t launch_delta(hipStream_t s, const NetDev& net, const float* cost, double delta_scale, float* delta_inst,
-                        double* logsum);
+// Bucket widths, the tree counter at zero, and (where not NULL) y and absorb_q
+// at zero: before launch_trees, from the log sums of the last launch_bpr or
+// launch_scatter_rcost.
+hipError_t launch_prep(hipStream_t s, const NetDev& net, const double* logpart, double delta_scale, float* delta_inst,
+                       int32_t* work, int64_t* y, int32_t* absorb_q, int Q);
 // The contracted search's trees (variant >= 32) are complete only after
 // launch_chain_fill of the same trees; fill = true launches it right after.
 hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, const uint2* radj, label_t* labels,
                         const Scratch& scr, int slots, const InstState* st, const float* delta_inst, int variant,
                         int early, int t_begin, int t_end, bool fill = true);
-hipError_t launch_sssp(hipStream_t s, const NetDev& net, const DemDev& dem, const float* cost, const uint2* radj,
+// launch_prep and launch_trees of every tree
+hipError_t launch_sssp(hipStream_t s, const NetDev& net, const DemDev& dem, const double* logpart, const uint2* radj,
                        label_t* labels, const Scratch& scr, int slots, const InstState* st, double delta_scale,
-                       float* delta_inst, double* logsum, int variant, int early, bool fill = true);
+                       float* delta_inst, int variant, int early, bool fill = true, int64_t* y = nullptr,
+                       int32_t* absorb_q = nullptr);
 hipError_t launch_chain_fill(hipStream_t s, const NetDev& net, const DemDev& dem, label_t* labels,
                              const InstState* st, int t_begin, int t_end);
 

@@ -7,7 +7,7 @@
 //                wavefront per tree
 //   k_walk       route truncation (Eq. 2) and loading along the successor
 //                links (Eq. 5, Alg. 3), int64 fixed-point atomics
-//   k_gap_sums   exact sums for the relative gap / stop test
+//   k_gap        exact sums for the relative gap, stop test
 //   k_ls_*       line search on the Beckmann objective (Eq. 6, Eq. 8-10,
 //                Alg. 8-9), K step sizes per pass over the links
 //   k_fw_update  f <- f + rint(alpha (y - f))
@@ -56,14 +56,6 @@ __device__ __forceinline__ int32_t ld_coherent(const int32_t* p) {
 // Every access this wavefront has issued (atomics without a result too) is done.
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// round-half-even(x * 2^16) as int128; flags values that are not finite or
-// beyond the int128 range.
-__device__ __forceinline__ i128 quant(double x, int& bad) {
-    double v = __builtin_rint(x * kSumQ);
-    if (!(__builtin_fabs(v) < 1.7e38)) { bad = 1; return 0; }
-    return (i128)v;
-}
-
 // Exact int128 accumulation with 64-bit atomics: the value is kept as three
 // signed chunk sums, v = c2 * 2^84 + c1 * 2^42 + c0.  A term takes as few of
 // them as it needs (each part below 2^42 in size, so 2^20 terms fit a chunk):
@@ -107,7 +99,7 @@ __device__ __forceinline__ i128 get128(const long long* in) {
 // order does not matter: five FP64 additions a term, where the same term as an
 // int128 took the compiler's double -> int128 conversion and a 4-word add.
 // A larger term goes straight to the global accumulator; one beyond the int128
-// range (or not finite) sets bad, as quant does.
+// range (or not finite) sets bad.
 struct XSum {
     double H = 0.0, L = 0.0;
 };
@@ -127,16 +119,71 @@ __device__ __forceinline__ void xsum_add(XSum& a, double s, long long* acc, int&
 }
 __device__ __forceinline__ i128 xsum_value(const XSum& a) { return (i128)a.H + (i128)a.L; }
 
-// Workgroup sum of one int128 per thread, added to an exact accumulator.
-__device__ void wg_acc_add(i128 v, long long* acc, i128* lds) {
-    lds[threadIdx.x] = v;
+// Workgroup sums of two terms per thread, added to this workgroup's copy of an
+// instance's exact accumulators ([copy][2][3] words, kSumReps copies).
+__device__ void wg_pair_add(const XSum& x0, const XSum& x1, long long* acc, double (*red)[kWG]) {
+    const int tid = threadIdx.x;
+    red[0][tid] = x0.H;
+    red[1][tid] = x0.L;
+    red[2][tid] = x1.H;
+    red[3][tid] = x1.L;
     __syncthreads();
     for (int s = kWG / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
+        if (tid < s)
+            for (int q = 0; q < 4; ++q) red[q][tid] += red[q][tid + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0 && lds[0] != 0) acc3_add(acc, lds[0]);
+    if (tid < 2) {
+        XSum x;
+        x.H = red[2 * tid][0];
+        x.L = red[2 * tid + 1][0];
+        acc3_add(acc + 3 * tid, xsum_value(x));
+    }
+}
+
+// Whether this workgroup is the last of its instance's `all` to get here (every
+// thread gets the answer); the ticket is back at zero then.  The workgroups'
+// atomics before this are done when the last one goes on.
+__device__ __forceinline__ bool last_of_instance(unsigned int* ticket, unsigned int all, int* lds) {
+    wait_memory();
     __syncthreads();
+    if (threadIdx.x == 0) {
+        *lds = atomicAdd(ticket, 1u) == all - 1;
+        if (*lds) *ticket = 0u;
+    }
+    __syncthreads();
+    return *lds != 0;
+}
+
+// The two sums over the copies of an instance's accumulators, which are set to
+// zero for the next use; one wavefront, every lane gets both.
+__device__ __forceinline__ void take_sums(long long* acc, int lane, i128& s0, i128& s1) {
+    long long c = 0;
+    if (lane < 6) {
+        long long w[kSumReps];
+#pragma unroll
+        for (int r = 0; r < kSumReps; ++r)
+            w[r] = __hip_atomic_load(acc + r * 6 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int r = 0; r < kSumReps; ++r) {
+            c += w[r];
+            acc[r * 6 + lane] = 0;
+        }
+    }
+    long long v[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) v[j] = __shfl(c, j);
+    s0 = acc3_value(v);
+    s1 = acc3_value(v + 3);
+}
+
+// Workgroups per link chunk for the kernels that stream over the links once:
+// one per kWG links while that is not more than the card has CUs (their sums'
+// atomics meet on a few words), else fewer.
+static int sum_split(int nblk) {
+    int split = 1;
+    while (split < kChunk / kWG && nblk * split < 256) split *= 2;
+    return split;
 }
 
 // BPR curve (Eq. 1): c0 (1 + alpha (kappa F / C)^beta) in FP64; with
@@ -211,106 +258,70 @@ __device__ __forceinline__ bool inst_live(const InstState* st, int i) {
     return st == nullptr || (st[i].active && !st[i].converged);
 }
 
+// The cost of link a into the link records: the reverse records (source node,
+// cost) read by the shortest-path kernels, the forward records (head node,
+// cost) read by the walks, and the contracted records.
+__device__ __forceinline__ void put_cost(const NetDev& net, uint2* __restrict__ radj, int a, float c) {
+    const uint32_t w = __float_as_uint(c);
+    radj[net.revpos[a]].y = w;
+    net.fadj[a].y = w;
+    if (net.cbuf) {
+        const int2 at = net.cslot[a];
+        if (at.x >= 0) net.cbuf[at.x] = w;
+        if (at.y >= 0) net.cbuf[at.y] = w;
+    }
+}
+
+// This workgroup's part of sum log(cost) (see k_prep), when asked for.
+__device__ __forceinline__ void put_logsum(double s, double* logpart) {
+    __shared__ double part[kWG / 64];
+    if (!logpart) return;
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int k = 0; k < kWG / 64; ++k) t += part[k];
+        logpart[blockIdx.x * gridDim.y + blockIdx.y] = t;
+    }
+}
+
+// One link per thread: kChunk / kWG workgroups per chunk (a workgroup that took
+// a whole chunk held a 1,520-link network's costs for 7 us).
 __global__ __launch_bounds__(kWG) void k_bpr(NetDev net, const int64_t* __restrict__ f, double alpha, int beta,
                                              float* __restrict__ cost, uint2* __restrict__ radj,
                                              const InstState* st, int only_active, int* err,
-                                             float* __restrict__ tcost) {
+                                             float* __restrict__ tcost, double* logpart) {
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
     if (only_active && !inst_live(st, inst)) return;
     const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    int bad = 0;
-    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
+    const int a = net.blk_start[b] + (int)blockIdx.y * kWG + (int)threadIdx.x;
+    double lg = 0.0;
+    if (a < I.link0 + I.m) {
+        int bad = 0;
         const double F = (double)f[a] * kFxInv;
-        double c = bpr64(F, net.c0[a], net.cap[a], alpha, beta, I.kappa, net.objective);
-        float c32 = (float)c;
+        const float c0 = net.c0[a], cap = net.cap[a];
+        const float c32 = (float)bpr64(F, c0, cap, alpha, beta, I.kappa, net.objective);
         if (!(c32 <= 3.4028234663852886e38f)) bad = 1;
         cost[a] = c32;
         if (tcost) {
-            const float t32 = net.objective ? (float)bpr64(F, net.c0[a], net.cap[a], alpha, beta, I.kappa) : c32;
+            const float t32 = net.objective ? (float)bpr64(F, c0, cap, alpha, beta, I.kappa) : c32;
             if (!(t32 <= 3.4028234663852886e38f)) bad = 1;
             tcost[a] = t32;
         }
-        if (radj) {
-            radj[net.revpos[a]].y = __float_as_uint(c32);
-            net.fadj[a].y = __float_as_uint(c32);
-            if (net.cbuf) {
-                const int2 w = net.cslot[a];
-                if (w.x >= 0) net.cbuf[w.x] = __float_as_uint(c32);
-                if (w.y >= 0) net.cbuf[w.y] = __float_as_uint(c32);
-            }
-        }
+        if (radj) put_cost(net, radj, a, c32);
+        if (logpart) lg = log((double)c32);
+        if (bad) atomicOr(err, 1);
     }
-    if (bad) atomicOr(err, 1);
+    put_logsum(lg, logpart);
 }
 
 hipError_t launch_bpr(hipStream_t s, const NetDev& net, const int64_t* f, double alpha, int beta, float* cost,
-                      uint2* radj, const InstState* st, int only_active, int* err, float* tcost) {
+                      uint2* radj, const InstState* st, int only_active, int* err, float* tcost, double* logpart) {
     if (net.nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bpr, dim3(net.nblk), dim3(kWG), 0, s, net, f, alpha, beta, cost, radj, st, only_active,
-                       err, tcost);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// A4: exact sums for the relative gap, sum c F and sum c Y
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kWG) void k_gap_sums(NetDev net, const float* __restrict__ cost,
-                                                  const int64_t* __restrict__ f, const int64_t* __restrict__ y,
-                                                  long long* acc, const InstState* st, int* err) {
-    __shared__ i128 lds[kWG];
-    const int b = blockIdx.x;
-    const int inst = net.blk_inst[b];
-    if (!inst_live(st, inst)) return;
-    const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    i128 sf = 0, sy = 0;
-    int bad = 0;
-    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
-        double c = (double)cost[a];
-        sf += quant(c * ((double)f[a] * kFxInv), bad);
-        sy += quant(c * ((double)y[a] * kFxInv), bad);
-    }
-    if (bad) atomicOr(err, 1);
-    wg_acc_add(sf, acc + inst * 6 + 0, lds);
-    wg_acc_add(sy, acc + inst * 6 + 3, lds);
-}
-
-hipError_t launch_gap_sums(hipStream_t s, const NetDev& net, const float* cost, const int64_t* f, const int64_t* y,
-                           long long* acc, const InstState* st, int* err) {
-    if (net.nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gap_sums, dim3(net.nblk), dim3(kWG), 0, s, net, cost, f, y, acc, st, err);
-    return hipGetLastError();
-}
-
-// Stop test of iteration j (Alg. 6): relative gap, or the iteration cap.
-// Also advances the iteration index j of each live instance, so a captured
-// iteration replays with the right j.
-__global__ void k_gap_decide(int ninst, const long long* acc, InstState* st, int stop_rule, double tol,
-                             int fixed_iters, int cap_iter) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
-    InstState& S = st[i];
-    if (!S.active || S.converged) return;
-    S.iter += 1;
-    i128 scf = acc3_value(acc + i * 6), scy = acc3_value(acc + i * 6 + 3);
-    S.gap = (double)(scf - scy) / (double)scf;
-    if (fixed_iters <= 0 && stop_rule == 0 && __builtin_fabs(S.gap) < tol) {
-        S.converged = 1;
-        S.stopped_by = 1;
-    } else if (S.iter > cap_iter) {
-        S.converged = 1;
-        S.stopped_by = 0;
-    }
-}
-
-hipError_t launch_gap_decide(hipStream_t s, int ninst, const long long* acc, InstState* st, int stop_rule,
-                             double tol, int fixed_iters, int cap_iter) {
-    hipLaunchKernelGGL(k_gap_decide, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, acc, st, stop_rule, tol,
-                       fixed_iters, cap_iter);
+    hipLaunchKernelGGL(k_bpr, dim3(net.nblk, kLogParts), dim3(kWG), 0, s, net, f, alpha, beta, cost, radj, st,
+                       only_active, err, tcost, logpart);
     return hipGetLastError();
 }
 
@@ -343,6 +354,68 @@ __device__ void ls_begin_wave(InstState& S, double* al, long long* acc, int K, i
         S.ls_pass = 0;
         S.ls_done = ls_mode == 2 ? 1 : 0;
     }
+}
+
+// A4: exact sums for the relative gap, sum c F and sum c Y, and the stop test.
+// The last workgroup of an instance takes the sums and decides (Alg. 6): the
+// relative gap against tol, or the iteration cap; it also advances the
+// iteration index j, so a captured iteration replays with the right j, and
+// starts the line search of an instance that goes on.
+__global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict__ cost,
+                                             const int64_t* __restrict__ f, const int64_t* __restrict__ y,
+                                             long long* acc, InstState* st, int* err, unsigned int* ticket,
+                                             GapRule G, double* alphas, long long* ls_acc) {
+    __shared__ double red[4][kWG];
+    __shared__ int s_last;
+    const int b = blockIdx.x;
+    const int inst = net.blk_inst[b];
+    if (!inst_live(st, inst)) return;
+    const InstDev I = net.inst[inst];
+    const int part = kChunk / (int)gridDim.y;
+    const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
+    const int a1 = min(a0 + part, I.link0 + I.m);
+    long long* sums = acc + (long long)inst * kSumReps * 6;
+    long long* mine = sums + ((blockIdx.y * gridDim.x + blockIdx.x) % kSumReps) * 6;
+    XSum sf, sy;
+    int bad = 0;
+    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
+        const double c = (double)cost[a];
+        xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, mine, bad);
+        xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, mine + 3, bad);
+    }
+    if (bad) atomicOr(err, 1);
+    wg_pair_add(sf, sy, mine, red);
+    const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
+    if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
+    InstState& S = st[inst];
+    int go = 0;
+    i128 scf, scy;
+    take_sums(sums, (int)threadIdx.x, scf, scy);
+    if (threadIdx.x == 0) {
+        S.iter += 1;
+        S.gap = (double)(scf - scy) / (double)scf;
+        if (G.fixed_iters <= 0 && G.stop_rule == 0 && __builtin_fabs(S.gap) < G.tol) {
+            S.converged = 1;
+            S.stopped_by = 1;
+        } else if (S.iter > G.cap_iter) {
+            S.converged = 1;
+            S.stopped_by = 0;
+        } else {
+            go = 1;
+        }
+    }
+    if (__shfl(go, 0))
+        ls_begin_wave(S, alphas + (long long)inst * G.K, ls_acc + (long long)inst * G.K * 6 * kLsReps, G.K, G.ls_mode,
+                      G.dx, (int)threadIdx.x);
+}
+
+hipError_t launch_gap(hipStream_t s, const NetDev& net, const float* cost, const int64_t* f, const int64_t* y,
+                      long long* acc, InstState* st, int* err, unsigned int* ticket, const GapRule& rule,
+                      double* alphas, long long* ls_acc) {
+    if (net.nblk == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_gap, dim3(net.nblk, sum_split(net.nblk)), dim3(kWG), 0, s, net, cost, f, y, acc, st, err,
+                       ticket, rule, alphas, ls_acc);
+    return hipGetLastError();
 }
 
 // Start the line search of iteration j for every live instance.
@@ -597,15 +670,9 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
         acc3_add(acc + kk * 6 + 3 * w, xsum_value(x));
     }
     if (!rule.on) return;
-    wait_memory();                            // this workgroup's sums are in before its ticket
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
-        s_last = atomicAdd(&rule.ticket[inst], 1u) == all - 1;
-        if (s_last) rule.ticket[inst] = 0u;
-    }
-    __syncthreads();
-    if (s_last && tid < 64) ls_decide_wave(st[inst], al, sums, rule, tid);
+    const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
+    if (last_of_instance(&rule.ticket[inst], all, &s_last) && tid < 64)
+        ls_decide_wave(st[inst], al, sums, rule, tid);
 }
 
 hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b,
@@ -633,21 +700,6 @@ hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, co
         else QDTA_LS(0, false);
     }
 #undef QDTA_LS
-    return hipGetLastError();
-}
-
-// A zero step leaves f unchanged, so the next iteration would repeat this
-// one: stop there unless a fixed iteration count was asked for.
-__global__ void k_stall_check(int ninst, InstState* st, int fixed_iters) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst || fixed_iters > 0) return;
-    InstState& S = st[i];
-    if (!S.active || S.converged) return;
-    if (S.alpha == 0.0) { S.converged = 1; S.stopped_by = 3; }
-}
-
-hipError_t launch_stall_check(hipStream_t s, int ninst, InstState* st, int fixed_iters) {
-    hipLaunchKernelGGL(k_stall_check, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, st, fixed_iters);
     return hipGetLastError();
 }
 
@@ -693,113 +745,125 @@ hipError_t noalloc_scratch(int device, long long** out) {
 }
 
 // Objective (Beckmann, or total travel time under the system optimum) of f
-// (slot 0) and of the would-be update f + rint(alpha (y - f)) (slot 1),
-// exact -- the Converged test of Eq. 7.
-__global__ __launch_bounds__(kWG) void k_obj_pair(NetDev net, const int64_t* __restrict__ f,
-                                                  const int64_t* __restrict__ y, double alpha_b, int beta,
-                                                  long long* acc, const InstState* st, int use_alpha, int* err) {
-    __shared__ i128 lds[kWG];
+// (slot 0) and, apply_rule = 1, of the would-be update f + rint(alpha (y - f))
+// (slot 1), exact.  The last workgroup of an instance decides: apply_rule = 1,
+// the Converged test of Eq. 7 on the two; 0, slot 0 is the objective of the
+// returned iterate.
+__global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restrict__ f,
+                                             const int64_t* __restrict__ y, double alpha_b, int beta,
+                                             long long* acc, InstState* st, int apply_rule, double tol, int* err,
+                                             unsigned int* ticket) {
+    __shared__ double red[4][kWG];
+    __shared__ int s_last;
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
-    if (st && !st[inst].active) return;
-    if (use_alpha && (st[inst].converged)) return;
+    if (!st[inst].active) return;
+    if (apply_rule && st[inst].converged) return;
     const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    const double alpha = use_alpha ? st[inst].alpha : 0.0;
-    i128 s0 = 0, s1 = 0;
+    const int part = kChunk / (int)gridDim.y;
+    const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
+    const int a1 = min(a0 + part, I.link0 + I.m);
+    long long* sums = acc + (long long)inst * kSumReps * 6;
+    long long* mine = sums + ((blockIdx.y * gridDim.x + blockIdx.x) % kSumReps) * 6;
+    const double alpha = apply_rule ? st[inst].alpha : 0.0;
+    XSum s0, s1;
     int bad = 0;
     for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
         double obj, der;
-        double F = (double)f[a] * kFxInv;
+        const double F = (double)f[a] * kFxInv;
         ls_terms(F, F, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-        s0 += quant(obj, bad);
-        if (use_alpha) {
-            int64_t fn = f[a] + (int64_t)__builtin_rint(alpha * (double)(y[a] - f[a]));
-            double Fn = (double)fn * kFxInv;
+        xsum_add(s0, obj * kSumQ, mine, bad);
+        if (apply_rule) {
+            const int64_t fn = f[a] + (int64_t)__builtin_rint(alpha * (double)(y[a] - f[a]));
+            const double Fn = (double)fn * kFxInv;
             ls_terms(Fn, Fn, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-            s1 += quant(obj, bad);
+            xsum_add(s1, obj * kSumQ, mine + 3, bad);
         }
     }
     if (bad) atomicOr(err, 1);
-    wg_acc_add(s0, acc + inst * 6, lds);
-    if (use_alpha) wg_acc_add(s1, acc + inst * 6 + 3, lds);
-}
-
-hipError_t launch_obj_pair(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b,
-                           int beta, long long* acc, const InstState* st, int use_alpha, int* err) {
-    if (net.nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_obj_pair, dim3(net.nblk), dim3(kWG), 0, s, net, f, y, alpha_b, beta, acc, st, use_alpha,
-                       err);
-    return hipGetLastError();
-}
-
-// apply_rule = 1: Eq. 7 test on (slot 0, slot 1); 0: record slot 0 as the
-// objective of the returned iterate.
-__global__ void k_obj_decide(int ninst, const long long* acc, InstState* st, double tol, int apply_rule) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
-    InstState& S = st[i];
-    if (!S.active) return;
+    wg_pair_add(s0, s1, mine, red);
+    const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
+    if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
+    i128 v0, v1;
+    take_sums(sums, (int)threadIdx.x, v0, v1);
+    if (threadIdx.x != 0) return;
     if (apply_rule) {
-        if (S.converged) return;
-        double b0 = (double)acc3_value(acc + i * 6), b1 = (double)acc3_value(acc + i * 6 + 3);
-        if (__builtin_fabs((b0 - b1) / b0) < tol) { S.converged = 1; S.stopped_by = 2; }
+        const double b0 = (double)v0, b1 = (double)v1;
+        if (__builtin_fabs((b0 - b1) / b0) < tol) {
+            st[inst].converged = 1;
+            st[inst].stopped_by = 2;
+        }
     } else {
-        S.obj = (double)acc3_value(acc + i * 6) / kSumQ;
+        st[inst].obj = (double)v0 / kSumQ;
     }
 }
 
-hipError_t launch_obj_decide(hipStream_t s, int ninst, const long long* acc, InstState* st, double tol,
-                             int apply_rule) {
-    hipLaunchKernelGGL(k_obj_decide, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, acc, st, tol, apply_rule);
+hipError_t launch_obj(hipStream_t s, const NetDev& net, const int64_t* f, const int64_t* y, double alpha_b, int beta,
+                      long long* acc, InstState* st, int apply_rule, double tol, int* err, unsigned int* ticket) {
+    if (net.nblk == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_obj, dim3(net.nblk, sum_split(net.nblk)), dim3(kWG), 0, s, net, f, y, alpha_b, beta, acc, st,
+                       apply_rule, tol, err, ticket);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // A6: link-flow update
 // ---------------------------------------------------------------------------
+// One link per thread.  alpha_per_inst NULL: the step of a running iteration,
+// S.alpha of each live instance, whose first workgroup also notes the applied
+// update -- or, when the step is zero and no fixed iteration count was asked
+// for, stops the instance: f would not change and the next iteration would
+// repeat this one (a workgroup that sees it stopped has nothing to add).
 __global__ __launch_bounds__(kWG) void k_fw_update(NetDev net, int64_t* __restrict__ f, const int64_t* __restrict__ y,
-                                                   const double* alpha_per_inst, const InstState* st) {
+                                                   const double* alpha_per_inst, InstState* st, int fixed_iters) {
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
     if (!inst_live(st, inst)) return;
     const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    const double alpha = alpha_per_inst[inst];
-    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
-        int64_t fa = f[a];
+    const double alpha = alpha_per_inst ? alpha_per_inst[inst] : st[inst].alpha;
+    const int a = net.blk_start[b] + (int)blockIdx.y * kWG + (int)threadIdx.x;
+    if (a < I.link0 + I.m) {
+        const int64_t fa = f[a];
         f[a] = fa + (int64_t)__builtin_rint(alpha * (double)(y[a] - fa));
     }
-}
-
-hipError_t launch_fw_update(hipStream_t s, const NetDev& net, int64_t* f, const int64_t* y,
-                            const double* alpha_per_inst, const InstState* st) {
-    if (net.nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fw_update, dim3(net.nblk), dim3(kWG), 0, s, net, f, y, alpha_per_inst, st);
-    return hipGetLastError();
-}
-
-// Costs into the link records: the reverse records (source node, cost) read
-// by the shortest-path kernels, one 8-byte record per in-link, and the
-// forward records (head node, cost) read by the walks.
-__global__ __launch_bounds__(kWG) void k_scatter_rcost(NetDev net, const float* __restrict__ cost,
-                                                       uint2* __restrict__ radj) {
-    for (int64_t a = blockIdx.x * (int64_t)kWG + threadIdx.x; a < net.M; a += (int64_t)gridDim.x * kWG) {
-        radj[net.revpos[a]].y = __float_as_uint(cost[a]);
-        net.fadj[a].y = __float_as_uint(cost[a]);
-        if (net.cbuf) {
-            const int2 w = net.cslot[a];
-            if (w.x >= 0) net.cbuf[w.x] = __float_as_uint(cost[a]);
-            if (w.y >= 0) net.cbuf[w.y] = __float_as_uint(cost[a]);
+    if (!alpha_per_inst && a == I.link0) {
+        InstState& S = st[inst];
+        if (alpha == 0.0 && fixed_iters <= 0) {
+            S.converged = 1;
+            S.stopped_by = 3;
+        } else {
+            S.iters = S.iter;
+            S.last_alpha = alpha;
         }
     }
 }
 
-hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj) {
-    if (net.M == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_rcost, dim3(grid_for(net.M)), dim3(kWG), 0, s, net, cost, radj);
+hipError_t launch_fw_update(hipStream_t s, const NetDev& net, int64_t* f, const int64_t* y,
+                            const double* alpha_per_inst, InstState* st, int fixed_iters) {
+    if (net.nblk == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fw_update, dim3(net.nblk, kLogParts), dim3(kWG), 0, s, net, f, y, alpha_per_inst, st,
+                       fixed_iters);
+    return hipGetLastError();
+}
+
+// Given costs into the link records, with the log sums of k_prep.
+__global__ __launch_bounds__(kWG) void k_scatter_rcost(NetDev net, const float* __restrict__ cost,
+                                                       uint2* __restrict__ radj, double* logpart) {
+    const int b = blockIdx.x;
+    const InstDev I = net.inst[net.blk_inst[b]];
+    const int a = net.blk_start[b] + (int)blockIdx.y * kWG + (int)threadIdx.x;
+    double lg = 0.0;
+    if (a < I.link0 + I.m) {
+        const float c = cost[a];
+        put_cost(net, radj, a, c);
+        lg = log((double)c);
+    }
+    put_logsum(lg, logpart);
+}
+
+hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart) {
+    if (net.nblk == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_scatter_rcost, dim3(net.nblk, kLogParts), dim3(kWG), 0, s, net, cost, radj, logpart);
     return hipGetLastError();
 }
 
@@ -814,21 +878,6 @@ __global__ __launch_bounds__(kWG) void k_cslot_init(NetDev net) {
 hipError_t launch_cslot_init(hipStream_t s, const NetDev& net) {
     if (net.M == 0 || !net.cbuf) return hipSuccess;
     hipLaunchKernelGGL(k_cslot_init, dim3(grid_for(net.M)), dim3(kWG), 0, s, net);
-    return hipGetLastError();
-}
-
-// Bookkeeping after an applied update of iteration j.
-__global__ void k_after_update(int ninst, InstState* st) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst) return;
-    InstState& S = st[i];
-    if (!S.active || S.converged) return;
-    S.iters = S.iter;
-    S.last_alpha = S.alpha;
-}
-
-hipError_t launch_after_update(hipStream_t s, int ninst, InstState* st) {
-    hipLaunchKernelGGL(k_after_update, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, st);
     return hipGetLastError();
 }
 
@@ -2329,43 +2378,49 @@ __global__ __launch_bounds__(kWG) void k_sssp_blk(NetDev net, DemDev dem, const 
     }
 }
 
-// Bucket width per instance: delta = scale * (geometric mean link cost of the
-// instance).  The geometric mean follows the typical link; the arithmetic
-// mean is dominated by the few links that congestion makes very slow.
-// Partial sums of log(cost) per link chunk, then one division per instance.
-__global__ __launch_bounds__(kWG) void k_logcost(NetDev net, const float* __restrict__ cost, double* logsum) {
+// What a launch of the search needs in place: the bucket width per instance,
+// delta = scale * (geometric mean link cost of the instance), from the log sums
+// the cost kernels leave per workgroup (added in a fixed order), the tree
+// counter, and, where given, y and the tie flags at zero.  The geometric mean
+// follows the typical link; the arithmetic mean is dominated by the few links
+// that congestion makes very slow.
+__global__ __launch_bounds__(kWG) void k_prep(NetDev net, const double* __restrict__ logpart, double scale,
+                                              float* delta_inst, int32_t* work, int64_t* __restrict__ y,
+                                              int32_t* __restrict__ absorb_q, int Q) {
     __shared__ double part[kWG];
-    const int b = blockIdx.x;
-    const int inst = net.blk_inst[b];
-    const InstDev I = net.inst[inst];
-    const int a0 = net.blk_start[b];
-    const int a1 = min(a0 + kChunk, I.link0 + I.m);
-    double s = 0.0;
-    for (int a = a0 + threadIdx.x; a < a1; a += kWG) s += log((double)cost[a]);
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = kWG / 2; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) part[threadIdx.x] += part[threadIdx.x + k];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *work = 0;
+    const int64_t first = blockIdx.x * (int64_t)kWG + threadIdx.x, stride = (int64_t)gridDim.x * kWG;
+    if (y)
+        for (int64_t a = first; a < net.M; a += stride) y[a] = 0;
+    if (absorb_q)
+        for (int64_t q = first; q < Q; q += stride) absorb_q[q] = 0;
+    for (int inst = blockIdx.x; inst < net.ninst; inst += gridDim.x) {
+        const InstDev I = net.inst[inst];
+        // the instance's workgroups are a run: its first chunk is the one at link0
+        const int n = (I.m + kChunk - 1) / kChunk * kLogParts;
+        double s = 0.0;
+        for (int k = threadIdx.x; k < n; k += kWG) s += logpart[(int64_t)net.inst_blk[inst] * kLogParts + k];
+        part[threadIdx.x] = s;
+        __syncthreads();
+        for (int k = kWG / 2; k > 0; k >>= 1) {
+            if ((int)threadIdx.x < k) part[threadIdx.x] += part[threadIdx.x + k];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            double d = I.m > 0 ? scale * exp(part[0] / (double)I.m) : 1.0;
+            if (!(d > 0.0) || !(d < 3.0e38)) d = 3.0e38;
+            delta_inst[inst] = (float)d;
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicAdd(&logsum[inst], part[0]);
 }
 
-__global__ void k_delta(NetDev net, const double* logsum, double scale, float* delta_inst) {
-    const int inst = blockIdx.x * blockDim.x + threadIdx.x;
-    if (inst >= net.ninst) return;
-    const InstDev I = net.inst[inst];
-    double d = I.m > 0 ? scale * exp(logsum[inst] / (double)I.m) : 1.0;
-    if (!(d > 0.0) || !(d < 3.0e38)) d = 3.0e38;
-    delta_inst[inst] = (float)d;
-}
-
-hipError_t launch_delta(hipStream_t s, const NetDev& net, const float* cost, double delta_scale, float* delta_inst,
-                        double* logsum) {
-    hipError_t e0 = launch_fill_i64(s, reinterpret_cast<int64_t*>(logsum), 0, net.ninst);
-    if (e0 != hipSuccess) return e0;
-    if (net.nblk > 0) hipLaunchKernelGGL(k_logcost, dim3(net.nblk), dim3(kWG), 0, s, net, cost, logsum);
-    hipLaunchKernelGGL(k_delta, dim3((net.ninst + 63) / 64), dim3(64), 0, s, net, logsum, delta_scale, delta_inst);
+hipError_t launch_prep(hipStream_t s, const NetDev& net, const double* logpart, double delta_scale, float* delta_inst,
+                       int32_t* work, int64_t* y, int32_t* absorb_q, int Q) {
+    const int64_t words = std::max<int64_t>(y ? net.M : 1, absorb_q ? Q : 1);
+    const int64_t g = std::max<int64_t>((words + 4 * kWG - 1) / (4 * kWG), std::min(net.ninst, 1024));
+    hipLaunchKernelGGL(k_prep, dim3((unsigned)std::min<int64_t>(g, 2048)), dim3(kWG), 0, s, net, logpart, delta_scale,
+                       delta_inst, work, y, absorb_q, Q);
     return hipGetLastError();
 }
 
@@ -2449,8 +2504,7 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
                         const Scratch& scr, int slots, const InstState* st, const float* delta_inst, int variant,
                         int early, int t_begin, int t_end, bool fill) {
     if (t_end <= t_begin) return hipSuccess;
-    hipError_t e = launch_fill_u32(s, reinterpret_cast<uint32_t*>(scr.work), 0u, 1);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     int blocks = (slots + (kWG / 64) - 1) / (kWG / 64);
     if (variant >= 32 || (variant >= 8 && variant < 16)) {
         // node queue, one workgroup of 128 U threads per tree (scratch slot =
@@ -2541,11 +2595,10 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
     return hipGetLastError();
 }
 
-hipError_t launch_sssp(hipStream_t s, const NetDev& net, const DemDev& dem, const float* cost, const uint2* radj,
+hipError_t launch_sssp(hipStream_t s, const NetDev& net, const DemDev& dem, const double* logpart, const uint2* radj,
                        label_t* labels, const Scratch& scr, int slots, const InstState* st, double delta_scale,
-                       float* delta_inst, double* logsum, int variant, int early, bool fill) {
-    if (dem.Q == 0) return hipSuccess;
-    hipError_t e = launch_delta(s, net, cost, delta_scale, delta_inst, logsum);
+                       float* delta_inst, int variant, int early, bool fill, int64_t* y, int32_t* absorb_q) {
+    hipError_t e = launch_prep(s, net, logpart, delta_scale, delta_inst, scr.work, y, absorb_q, dem.Q);
     if (e != hipSuccess) return e;
     return launch_trees(s, net, dem, radj, labels, scr, slots, st, delta_inst, variant, early, 0, dem.Q, fill);
 }

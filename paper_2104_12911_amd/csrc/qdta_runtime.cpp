@@ -73,7 +73,7 @@ struct qdta_ctx {
     int nblk = 0;
     std::vector<InstDev> h_inst;
     std::vector<int64_t> node_off, link_off, leg_off, dest_off;
-    DBuf<int32_t> row_ptr, col, rptr, rsrc, rlink, revpos, blk_inst, blk_start;
+    DBuf<int32_t> row_ptr, col, rptr, rsrc, rlink, revpos, blk_inst, blk_start, inst_blk;
     DBuf<float> c0, cap;
     DBuf<InstDev> d_inst;
 
@@ -100,7 +100,7 @@ struct qdta_ctx {
     DBuf<int64_t> sw_acc;             // indexed like the labels, zero between launches
     DBuf<unsigned long long> sssp_stats;  // nodes taken, in-links relaxed (reset by qdta_profile_enable)
     DBuf<float> delta_inst;
-    DBuf<double> logsum;
+    DBuf<double> logpart;             // sum log(cost) per workgroup of the cost kernels
 
     // chain contraction of the search (opts.sssp_kernel = 4), built for the
     // roots (destinations) seen so far
@@ -122,7 +122,7 @@ struct qdta_ctx {
     DBuf<uint32_t> frow;          // per link its head's forward row, packed (pack_row)
     DBuf<InstState> st;
     DBuf<long long> acc, ls_acc;
-    DBuf<double> alphas, alpha_arr;
+    DBuf<double> alphas;
     DBuf<unsigned int> ls_ticket; // workgroups of an instance done with the current line-search pass (zero between)
     DBuf<int> flags;              // [0] overflow, [1] unreach, [2] absorb count, [3] path-record faults
     DBuf<int32_t> absorb_q, int_node;
@@ -423,7 +423,7 @@ int ensure_network(qdta_ctx* c) {
     if (c->N >= INT32_MAX || c->M >= INT32_MAX) return set_err(c, QDTA_EARG, "total size beyond int32 ids");
     std::vector<int32_t> rp(c->N + 1), col(c->M), rptr(c->N + 1, 0), rsrc(c->M), rlink(c->M), revpos(c->M);
     std::vector<float> c0(c->M), cap(c->M);
-    std::vector<int32_t> bi, bs;
+    std::vector<int32_t> bi, bs, ib;
     for (int i = 0; i < ni; ++i) {
         const Instance& I = c->inst[i];
         int32_t n0 = (int32_t)c->node_off[i], l0 = (int32_t)c->link_off[i];
@@ -433,6 +433,7 @@ int ensure_network(qdta_ctx* c) {
             c0[l0 + a] = I.fftt[a];
             cap[l0 + a] = I.cap[a];
         }
+        ib.push_back((int32_t)bi.size());
         for (int a0 = 0; a0 < I.m; a0 += kChunk) {
             bi.push_back(i);
             bs.push_back(l0 + a0);
@@ -474,6 +475,8 @@ int ensure_network(qdta_ctx* c) {
     RC(upload(c, c->revpos, revpos));
     RC(upload(c, c->blk_inst, bi));
     RC(upload(c, c->blk_start, bs));
+    RC(upload(c, c->inst_blk, ib));
+    RC(dalloc(c, c->logpart, (size_t)c->nblk * kLogParts));
     RC(upload(c, c->d_inst, c->h_inst));
     RC(dalloc(c, c->f, c->M));
     RC(dalloc(c, c->y, c->M));
@@ -493,10 +496,10 @@ int ensure_network(qdta_ctx* c) {
     RC(dalloc(c, c->cfin, c->M));
     RC(dalloc(c, c->tcost, c->M));
     RC(dalloc(c, c->st, ni));
-    RC(dalloc(c, c->acc, (size_t)ni * 6));
+    RC(dalloc(c, c->acc, (size_t)ni * kSumReps * 6));
+    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)ni * kSumReps * 6));
     RC(dalloc(c, c->ls_acc, (size_t)ni * kMaxK * 6 * kLsReps));
     RC(dalloc(c, c->alphas, (size_t)ni * kMaxK));
-    RC(dalloc(c, c->alpha_arr, ni));
     RC(dalloc(c, c->ls_ticket, ni));
     HIPCHECK(c, launch_fill_u32(c->stream, c->ls_ticket.p, 0u, ni));
     RC(dalloc(c, c->flags, 4));
@@ -541,6 +544,7 @@ NetDev net_view(qdta_ctx* c, const qdta_opts* o = nullptr) {
     v.fill_chunks = ct ? c->c_fill_chunks : 0;
     v.blk_inst = c->blk_inst.p;
     v.blk_start = c->blk_start.p;
+    v.inst_blk = c->inst_blk.p;
     v.ninst = (int32_t)c->inst.size();
     v.nblk = c->nblk;
     v.N = c->N;
@@ -872,7 +876,6 @@ int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw) {
         HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->sssp_stats.p), 0, 2));
     }
     RC(dalloc(c, c->delta_inst, c->inst.size()));
-    RC(dalloc(c, c->logsum, c->inst.size()));
     return QDTA_OK;
 }
 
@@ -1082,13 +1085,16 @@ int aon_core(qdta_ctx* c, const qdta_opts* o, const float* cost, const float* ti
     if (marks) RC(prof_mark(c, PH_SSSP, 0));
     if (o->launch_form == 2) {
         // plain form: one launch per destination tree (one workgroup each)
-        HIPCHECK(c, launch_delta(c->stream, net, cost, delta_scale(o), c->delta_inst.p, c->logsum.p));
-        for (int64_t t = 0; t < c->Q; ++t)
+        HIPCHECK(c, launch_prep(c->stream, net, c->logpart.p, delta_scale(o), c->delta_inst.p, c->work.p, y,
+                                c->absorb_q.p, (int)c->Q));
+        for (int64_t t = 0; t < c->Q; ++t) {
+            HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->work.p), 0u, 1));
             HIPCHECK(c, launch_trees(c->stream, net, dem, c->radj.p, c->labels.p, scr_view(c), 4, st, c->delta_inst.p,
                                      sssp_variant(c, o), 1, (int)t, (int)t + 1, false));
+        }
     } else {
-        HIPCHECK(c, launch_sssp(c->stream, net, dem, cost, c->radj.p, c->labels.p, scr_view(c), c->slots, st,
-                                delta_scale(o), c->delta_inst.p, c->logsum.p, sssp_variant(c, o), 1, false));
+        HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, st,
+                                delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1, false, y, c->absorb_q.p));
     }
     if (marks) RC(prof_mark(c, PH_SSSP, 1));
     if (sssp_variant(c, o) >= 32) {   // the contracted search's left-out chain nodes, timed apart
@@ -1097,8 +1103,6 @@ int aon_core(qdta_ctx* c, const qdta_opts* o, const float* cost, const float* ti
         if (marks) RC(prof_mark(c, PH_FILL, 1));
     }
     if (marks) RC(prof_mark(c, PH_WALK, 0));
-    HIPCHECK(c, launch_fill_i64(c->stream, y, 0, c->M));
-    HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->absorb_q.p), 0u, c->Q));
     if (use_sweep(c, o)) {
         HIPCHECK(c, launch_sweep(c->stream, net, dem, c->labels.p, y, stop, stop_delay, st, fl, c->sw_cnt.p,
                                  c->sw_acc.p));
@@ -1138,16 +1142,18 @@ int pull_state(qdta_ctx* c) {
     return QDTA_OK;
 }
 
-// Line search of the current iteration for every live instance (A5).
+// Line search of the current iteration for every live instance (A5); begin:
+// started here (the stop test of an iteration starts it otherwise).
 int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const int64_t* y,
-                     const NetDev* net_in = nullptr) {
+                     const NetDev* net_in = nullptr, bool begin = true) {
     NetDev net = net_in ? *net_in : net_view(c, o);
     int ni = (int)c->inst.size();
     int* err = c->flags.p;
     const bool plain = o->launch_form == 2;
     const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
     LsRule rule{!plain, K, o->ls_mode == QDTA_LS_QN ? 1 : 0, o->passes, o->max_ls, o->T1, o->T2, o->dx, c->ls_ticket.p};
-    HIPCHECK(c, launch_ls_begin(c->stream, ni, c->st.p, c->alphas.p, K, o->ls_mode, o->dx, c->ls_acc.p, 0));
+    if (begin)
+        HIPCHECK(c, launch_ls_begin(c->stream, ni, c->st.p, c->alphas.p, K, o->ls_mode, o->dx, c->ls_acc.p, 0));
     if (o->ls_mode == QDTA_LS_MSA) return QDTA_OK;
     // one pass over the links and its decision
     auto pass = [&]() -> int {
@@ -1459,10 +1465,11 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     auto add = [&](size_t n, size_t sz) { b += align_up(std::max<size_t>(n, 1) * sz); };
     // network and Frank-Wolfe state
     add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4); add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4);
-    add(nblk, 4); add(nblk, 4); add(ni, sizeof(InstDev));
+    add(nblk, 4); add(nblk, 4); add(ni, 4); add(nblk * kLogParts, 8); add(ni, sizeof(InstDev));
     add(M, 8); add(M, 8); add(M, 4); add(M, 8); add(M, 8); add(M, 4); add(M, 4); add(M, 4);
-    add(ni, sizeof(InstState)); add((size_t)ni * 6, 8); add((size_t)ni * kMaxK * 6 * kLsReps, 8); add((size_t)ni * kMaxK, 8);
-    add(ni, 8); add(ni, 4); add(4, 4); add(ni, 8);
+    add(ni, sizeof(InstState)); add((size_t)ni * 6 * kSumReps, 8);
+    add((size_t)ni * kMaxK * 6 * kLsReps, 8); add((size_t)ni * kMaxK, 8);
+    add(ni, 4); add(4, 4); add(ni, 8);
     // demand tables and shortest-path labels
     add(pq, 4); add(pq, 4); add(pq, 8); add(pq + 1, 4); add(pp, 4); add(pp, 8); add(pp, 4); add(pp, 4);
     add(labels, 4); add(pq, 4); add(pp, 4); add(pp, 4);
@@ -1482,7 +1489,7 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
             far_w = std::max(far_w, tw == 1 ? other : 2 * other);
         }
         add(near_w * nm, 4); add(far_w * nm, 4);
-        add(1, 4); add(2, 8); add(ni, 4); add(ni, 8);
+        add(1, 4); add(2, 8); add(ni, 4);
     }
     if (o->keep_history) {
         const size_t hcap = (size_t)(hist_iters(o) + 1);
@@ -1738,13 +1745,11 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         // place the instance's costs in the global link order
         if ((e = hipMemcpyAsync(c->cost.p + I.link0, cost, sizeof(float) * I.m, hipMemcpyDeviceToDevice, c->stream)))
             { rc = set_err(c, QDTA_EHIP, "copy cost: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p)))
+        if ((e = launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p, c->logpart.p)))
             { rc = set_err(c, QDTA_EHIP, "scatter: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_sssp(c->stream, net, dem, c->cost.p, c->radj.p, lab.p, scr_view(c), slots, nullptr,
-                             delta_scale(o), c->delta_inst.p, c->logsum.p, sssp_variant(c, o), 0)))
+        if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab.p, scr_view(c), slots, nullptr,
+                             delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 0, true, nullptr, aq.p)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(aq.p), 0u, nq)))
-            { rc = set_err(c, QDTA_EHIP, "fill: %s", hipGetErrorString(e)); break; }
         if ((e = launch_trees_out(c->stream, net, dem, lab.p, c->cost.p, inst, dist, succ, aq.p)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }
         FlagsDev fl = flags_view(c);
@@ -1778,7 +1783,7 @@ int qdta_aon(qdta_ctx* c, const qdta_opts* o, const float* cost, int64_t* y, int
     RC(clear_flags(c));
     NetDev net = net_view(c);
     HIPCHECK(c, hipMemcpyAsync(c->cost.p, cost, sizeof(float) * c->M, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHECK(c, launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p));
+    HIPCHECK(c, launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p, c->logpart.p));
     if (stop) HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(stop), 0xffffffffu, c->P));
     if (stop_delay) HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(stop_delay), 0u, c->P));
     RC(aon_core(c, o, c->cost.p, nullptr, y, stop, nullptr, true, stop_delay));
@@ -1889,7 +1894,7 @@ int qdta_fw_begin(qdta_ctx* c, const qdta_opts* o) {
     RC(prof_mark(c, PH_BPR, 0));
     float* tc = o->objective == QDTA_OBJ_SO ? c->tcost.p : nullptr;
     HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, c->st.p, 1, c->flags.p,
-                           tc));
+                           tc, c->logpart.p));
     RC(prof_mark(c, PH_BPR, 1));
     c->lab_hist_ok.clear();
     if (o->keep_history) RC(plan_label_history(c, o));
@@ -1929,33 +1934,29 @@ void fill_stats(qdta_ctx* c, qdta_stats* hs, int worst, const int* h) {
 // line search, update, for every live instance.  No host synchronisation
 // unless the quasi-Newton search is selected.
 int enqueue_iteration(qdta_ctx* c, const qdta_opts* o, bool marks) {
-    int ni = (int)c->inst.size();
     NetDev net = net_view(c, o);
     int* err = c->flags.p;
     const int cap_iter = o->fixed_iters > 0 ? o->fixed_iters : o->max_iter;
     if (marks) RC(prof_mark(c, PH_BPR, 0));
     float* tc = o->objective == QDTA_OBJ_SO ? c->tcost.p : nullptr;
-    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, c->st.p, 1, err, tc));
+    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, c->st.p, 1, err, tc,
+                           c->logpart.p));
     if (marks) RC(prof_mark(c, PH_BPR, 1));
     RC(aon_core(c, o, c->cost.p, tc, c->y.p, nullptr, c->st.p, marks));
     if (marks) RC(prof_mark(c, PH_GAP, 0));
-    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)ni * 6));
-    HIPCHECK(c, launch_gap_sums(c->stream, net, c->cost.p, c->f.p, c->y.p, c->acc.p, c->st.p, err));
-    HIPCHECK(c, launch_gap_decide(c->stream, ni, c->acc.p, c->st.p, o->stop_rule, o->tol, o->fixed_iters, cap_iter));
+    const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
+    HIPCHECK(c, launch_gap(c->stream, net, c->cost.p, c->f.p, c->y.p, c->acc.p, c->st.p, err, c->ls_ticket.p,
+                           GapRule{o->stop_rule, o->fixed_iters, cap_iter, K, o->ls_mode, o->tol, o->dx}, c->alphas.p,
+                           c->ls_acc.p));
     if (marks) RC(prof_mark(c, PH_GAP, 1));
     if (marks) RC(prof_mark(c, PH_LS, 0));
-    RC(line_search_core(c, o, c->f.p, c->y.p));
-    if (o->stop_rule == QDTA_STOP_OBJ && o->fixed_iters <= 0) {
-        HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)ni * 6));
-        HIPCHECK(c, launch_obj_pair(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 1, err));
-        HIPCHECK(c, launch_obj_decide(c->stream, ni, c->acc.p, c->st.p, o->tol, 1));
-    }
-    HIPCHECK(c, launch_stall_check(c->stream, ni, c->st.p, o->fixed_iters));
+    RC(line_search_core(c, o, c->f.p, c->y.p, nullptr, false));
+    if (o->stop_rule == QDTA_STOP_OBJ && o->fixed_iters <= 0)
+        HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 1, o->tol, err,
+                               c->ls_ticket.p));
     if (marks) RC(prof_mark(c, PH_LS, 1));
     if (marks) RC(prof_mark(c, PH_UPDATE, 0));
-    HIPCHECK(c, launch_copy_alpha(c->stream, ni, c->st.p, c->alpha_arr.p));
-    HIPCHECK(c, launch_fw_update(c->stream, net, c->f.p, c->y.p, c->alpha_arr.p, c->st.p));
-    HIPCHECK(c, launch_after_update(c->stream, ni, c->st.p));
+    HIPCHECK(c, launch_fw_update(c->stream, net, c->f.p, c->y.p, nullptr, c->st.p, o->fixed_iters));
     if (marks) RC(prof_mark(c, PH_UPDATE, 1));
     return QDTA_OK;
 }
@@ -2041,9 +2042,8 @@ int fw_finish(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs) {
     NetDev net = net_view(c, o);
     int h[4];
     // objective of the returned iterates
-    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)ni * 6));
-    HIPCHECK(c, launch_obj_pair(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 0, c->flags.p));
-    HIPCHECK(c, launch_obj_decide(c->stream, ni, c->acc.p, c->st.p, o->tol, 0));
+    HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 0, o->tol, c->flags.p,
+                           c->ls_ticket.p));
     HIPCHECK(c, hipMemcpyAsync(h, c->flags.p, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     RC(pull_state(c));
     int worst = flag_code(c, h);
@@ -2104,7 +2104,8 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     // else free flow
     if (!c->solved && c->fw_j < 0) HIPCHECK(c, launch_fill_i64(c->stream, c->f.p, 0, c->M));
     RC(clear_flags(c));
-    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, nullptr, 0, c->flags.p));
+    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, nullptr, 0, c->flags.p,
+                           nullptr, c->logpart.p));
     hipEvent_t e0, e1;
     HIPCHECK(c, hipEventCreate(&e0));
     HIPCHECK(c, hipEventCreate(&e1));
@@ -2145,8 +2146,8 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
         ts = (ts + 3) / 4 * 4;
         hipError_t e = hipEventRecord(e0, c->stream);
         if (e == hipSuccess)
-            e = launch_sssp(c->stream, net, dem, c->cost.p, c->radj.p, c->labels.p, scr_view(c), ts, nullptr,
-                            delta_scale(&t), c->delta_inst.p, c->logsum.p, sssp_variant(c, &t), 1);
+            e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), ts, nullptr,
+                            delta_scale(&t), c->delta_inst.p, sssp_variant(c, &t), 1);
         if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
@@ -2333,12 +2334,12 @@ int qdta_advance_interval(qdta_ctx* c, const qdta_opts* o) {
         const float* cj = c->hist_cost.p + (size_t)j * c->M;
         label_t* lab = c->labels.p;
         // the trees' costs c_j into the link records (the walk's tight test reads them)
-        HIPCHECK(c, launch_scatter_rcost(c->stream, net, cj, c->radj.p));
+        HIPCHECK(c, launch_scatter_rcost(c->stream, net, cj, c->radj.p, c->logpart.p));
         if ((size_t)j < c->lab_hist_ok.size() && c->lab_hist_ok[j]) {
             lab = c->lab_hist.p + (size_t)j * c->label_count;    // the solve's own trees of iterate j
         } else {
-            HIPCHECK(c, launch_sssp(c->stream, net, dem, cj, c->radj.p, c->labels.p, scr_view(c), c->slots, stj,
-                                    delta_scale(o), c->delta_inst.p, c->logsum.p, sssp_variant(c, o), 1));
+            HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, stj,
+                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1));
         }
         HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->absorb_q.p), 0u, c->Q));
         HIPCHECK(c, launch_walk(c->stream, net, dem, lab, c->cfin.p, nullptr, nullptr, stj, fl, 1, lamj,
@@ -2491,13 +2492,13 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
         NetDev net = net_view(c);
         DemDev dem = dem_view(c);
         const float* cj = c->hist_cost.p + (size_t)j * M;
-        HIPCHECK(c, launch_scatter_rcost(c->stream, net, cj, c->radj.p));
+        HIPCHECK(c, launch_scatter_rcost(c->stream, net, cj, c->radj.p, c->logpart.p));
         const label_t* lab = c->labels.p;
         if ((size_t)j < c->lab_hist_ok.size() && c->lab_hist_ok[j]) {
             lab = c->lab_hist.p + (size_t)j * c->label_count;   // the solve's own trees of iterate j
         } else {
-            HIPCHECK(c, launch_sssp(c->stream, net, dem, cj, c->radj.p, c->labels.p, scr_view(c), c->slots, nullptr,
-                                    delta_scale(o), c->delta_inst.p, c->logsum.p, sssp_variant(c, o), 1));
+            HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, nullptr,
+                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1));
         }
         RC(clear_flags(c));
         HIPCHECK(c, launch_path_walk(c->stream, net, dem, lab, nullptr, nullptr, nullptr, c->adj_len.p,

@@ -191,3 +191,33 @@ def test_residual_walk_counts_completed_weight_of_mixed_instances(q, orc, legs):
         eo, ed, ew = orc.merge_legs(eo, ed, ew)[:3]
         assert np.array_equal(ro, eo) and np.array_equal(rd, ed) and np.array_equal(rw, ew)
         assert done == edone
+
+
+@pytest.mark.parametrize("m", [1, 255, 257, 2047, 2049, 5000])
+@pytest.mark.parametrize("stop_rule,ls_mode", [(0, 0), (1, 0), (1, 1), (0, 2)])
+def test_stop_tests_at_split_edges(q, orc, m, stop_rule, ls_mode):
+    """Gap, objective change, stall and update decided by the last workgroup of an instance, two instances together:
+    flows, step sizes and why each stopped, against the oracle."""
+    import torch
+    rng = np.random.default_rng(m)
+    nets = [parallel_links(m, rng, 300.0), parallel_links(max(1, m // 3), rng, 900.0)]
+    trips = [40.0 * m, 2.0]
+    opts = q.default_opts(stop_rule=stop_rule, ls_mode=ls_mode, tol=1e-3, max_iter=12)
+    with q.Context() as ctx:
+        for i, net in enumerate(nets):
+            ctx.add(net)
+            ctx.set_demand(i, [0], [1], [trips[i]], float("inf"))
+        for again in range(2):
+            st, _ = ctx.solve(opts)
+            f = torch.empty(sum(net.m for net in nets), dtype=torch.int64, device="cuda")
+            ctx.get_flows(f)
+            f = f.cpu().numpy()
+            at = 0
+            for i, net in enumerate(nets):
+                o, d, w = orc.demand_legs(np.array([0], np.int32), np.array([1], np.int32), np.array([trips[i]]))
+                ref = orc.fw_solve(net, o, d, w, stop_rule=stop_rule, ls_mode=ls_mode, tol=1e-3, max_iter=12,
+                                   keep_history=False)
+                assert np.array_equal(f[at:at + net.m], ref.f)
+                assert (st[i]["iters"], st[i]["stopped_by"]) == (ref.iters, ref.stopped_by)
+                assert st[i]["gap"] == ref.gap and st[i]["last_alpha"] == ref.last_alpha
+                at += net.m
