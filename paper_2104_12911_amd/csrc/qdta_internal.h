@@ -154,10 +154,13 @@ struct Scratch {
     unsigned long long* stats; // [2] nodes taken and in-links relaxed, added up by the kernels
 };
 
+// err_overflow, err_unreach and absorb_any are words of pinned host memory that
+// kernels only ever set to 1, so that the host reads them without a copy once
+// the stream is done.
 struct FlagsDev {
     int* err_overflow;       // set on non-finite cost / exact-sum overflow
     int* err_unreach;        // set when a leg's origin cannot reach its destination
-    int* absorb_count;       // legs interrupted by FP32 absorption
+    int* absorb_any;         // set when FP32 absorption interrupts a leg
     int32_t* absorb_q;       // [Q] destination flagged for the tie fallback
     int32_t* int_node;       // [P] node where an interrupted leg stopped (-1 none)
     float* int_tau;          // [P] its elapsed time there
@@ -218,8 +221,12 @@ hipError_t launch_obj(hipStream_t s, const NetDev& net, const int64_t* f, const 
 hipError_t launch_fw_update(hipStream_t s, const NetDev& net, int64_t* f, const int64_t* y,
                             const double* alpha_per_inst, InstState* st, int fixed_iters = 0);
 
+hipError_t launch_init_state(hipStream_t s, const NetDev& net, InstState* st, int all, int iter);
+hipError_t launch_tree_tables(hipStream_t s, const int32_t* dest, int nq, int32_t node0, int32_t inst, int64_t words,
+                              int32_t* dest_node, int32_t* dest_inst, int64_t* dest_lab);
 hipError_t launch_copy_alpha(hipStream_t s, int ninst, const InstState* st, double* out);
-hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart);
+hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart,
+                                float* copy = nullptr);
 // contracted records' costs from the forward link records (after a rebuild)
 hipError_t launch_cslot_init(hipStream_t s, const NetDev& net);
 
@@ -283,7 +290,7 @@ hipError_t launch_resid_write(hipStream_t s, const NetDev& net, const DemDev& de
 
 hipError_t launch_trees_out(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels,
                             const float* cost_local, int32_t inst, float* dist, int32_t* succ,
-                            int32_t* absorb_q);
+                            int32_t* absorb_q, int* absorb_any);
 
 // frozen-path model and its reverse pass (OD calibration)
 hipError_t launch_path_walk(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels,

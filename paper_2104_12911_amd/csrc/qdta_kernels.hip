@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kWG) void k_bpr(NetDev net, const int64_t* __restri
         }
         if (radj) put_cost(net, radj, a, c32);
         if (logpart) lg = log((double)c32);
-        if (bad) atomicOr(err, 1);
+        if (bad) *err = 1;
     }
     put_logsum(lg, logpart);
 }
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
         xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, mine, bad);
         xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, mine + 3, bad);
     }
-    if (bad) atomicOr(err, 1);
+    if (bad) *err = 1;
     wg_pair_add(sf, sy, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
         }
         __syncthreads();
     }
-    if (bad) atomicOr(err, 1);
+    if (bad) *err = 1;
     s_red[0][tid] = sc.H;
     s_red[1][tid] = sc.L;
     s_red[2][tid] = sd.H;
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restri
             xsum_add(s1, obj * kSumQ, mine + 3, bad);
         }
     }
-    if (bad) atomicOr(err, 1);
+    if (bad) *err = 1;
     wg_pair_add(s0, s1, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
@@ -846,9 +846,11 @@ hipError_t launch_fw_update(hipStream_t s, const NetDev& net, int64_t* f, const 
     return hipGetLastError();
 }
 
-// Given costs into the link records, with the log sums of k_prep.
+// Given costs into the link records, with the log sums of k_prep, and into
+// copy where one is asked for.
 __global__ __launch_bounds__(kWG) void k_scatter_rcost(NetDev net, const float* __restrict__ cost,
-                                                       uint2* __restrict__ radj, double* logpart) {
+                                                       uint2* __restrict__ radj, double* logpart,
+                                                       float* __restrict__ copy) {
     const int b = blockIdx.x;
     const InstDev I = net.inst[net.blk_inst[b]];
     const int a = net.blk_start[b] + (int)blockIdx.y * kWG + (int)threadIdx.x;
@@ -856,14 +858,16 @@ __global__ __launch_bounds__(kWG) void k_scatter_rcost(NetDev net, const float* 
     if (a < I.link0 + I.m) {
         const float c = cost[a];
         put_cost(net, radj, a, c);
+        if (copy) copy[a] = c;
         lg = log((double)c);
     }
     put_logsum(lg, logpart);
 }
 
-hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart) {
+hipError_t launch_scatter_rcost(hipStream_t s, const NetDev& net, const float* cost, uint2* radj, double* logpart,
+                                float* copy) {
     if (net.nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_rcost, dim3(net.nblk, kLogParts), dim3(kWG), 0, s, net, cost, radj, logpart);
+    hipLaunchKernelGGL(k_scatter_rcost, dim3(net.nblk, kLogParts), dim3(kWG), 0, s, net, cost, radj, logpart, copy);
     return hipGetLastError();
 }
 
@@ -878,6 +882,40 @@ __global__ __launch_bounds__(kWG) void k_cslot_init(NetDev net) {
 hipError_t launch_cslot_init(hipStream_t s, const NetDev& net) {
     if (net.M == 0 || !net.cbuf) return hipSuccess;
     hipLaunchKernelGGL(k_cslot_init, dim3(grid_for(net.M)), dim3(kWG), 0, s, net);
+    return hipGetLastError();
+}
+
+// A fresh state of every instance, at iteration iter: active with links (all)
+// or with legs.
+__global__ void k_init_state(NetDev net, InstState* st, int all, int iter) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= net.ninst) return;
+    InstState S = {};
+    S.active = all ? net.inst[i].m > 0 : net.inst[i].nleg > 0;
+    S.iter = iter;
+    st[i] = S;
+}
+
+hipError_t launch_init_state(hipStream_t s, const NetDev& net, InstState* st, int all, int iter) {
+    hipLaunchKernelGGL(k_init_state, dim3((net.ninst + 63) / 64), dim3(64), 0, s, net, st, all, iter);
+    return hipGetLastError();
+}
+
+// The tables of nq trees of one instance, rooted at dest (local nodes), with
+// tree-major labels of `words` words each.
+__global__ void k_tree_tables(const int32_t* __restrict__ dest, int nq, int32_t node0, int32_t inst, int64_t words,
+                              int32_t* dest_node, int32_t* dest_inst, int64_t* dest_lab) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= nq) return;
+    dest_node[t] = node0 + dest[t];
+    dest_inst[t] = inst;
+    dest_lab[t] = t * words;
+}
+
+hipError_t launch_tree_tables(hipStream_t s, const int32_t* dest, int nq, int32_t node0, int32_t inst, int64_t words,
+                              int32_t* dest_node, int32_t* dest_inst, int64_t* dest_lab) {
+    hipLaunchKernelGGL(k_tree_tables, dim3((nq + 63) / 64), dim3(64), 0, s, dest, nq, node0, inst, words, dest_node,
+                       dest_inst, dest_lab);
     return hipGetLastError();
 }
 
@@ -2716,7 +2754,7 @@ __device__ __forceinline__ int64_t finish_leg(const WalkOut& o, int l, int s, in
             o.tr.delay[k] = delay;
             o.tr.w[k] = w;
         } else {
-            atomicOr(o.err, 1);
+            *o.err = 1;
         }
         return 0;
     }
@@ -2768,7 +2806,11 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
             s_key[x] = -1;
             s_sum[x] = 0ull;
         }
-    if (threadIdx.x == 0) s_done = 0ull;
+    __shared__ int s_absorbed;
+    if (threadIdx.x == 0) {
+        s_done = 0ull;
+        s_absorbed = 0;
+    }
     __syncthreads();
     auto load = [&](int e, int64_t d) {
         int h = (int)(((unsigned)e * 2654435761u) >> 20) & (SLOTS - 1);
@@ -2798,7 +2840,7 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
         float du = lab_val(lab, u - node0);
         fl.int_node[l] = -1;
         if (!(du <= 3.4028234663852886e38f)) {       // origin cannot reach q
-            atomicOr(fl.err_unreach, 1);
+            *fl.err_unreach = 1;
             if (o.stop) o.stop[l] = -1;
             continue;
         }
@@ -2819,7 +2861,7 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
                     fl.int_node[l] = u;
                     fl.int_tau[l] = tau;
                     fl.absorb_q[qi] = 1;
-                    atomicAdd(fl.absorb_count, 1);
+                    s_absorbed = 1;
                     absorbed = true;
                     break;
                 }
@@ -2843,6 +2885,7 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
         }
     }
     __syncthreads();
+    if (threadIdx.x == 0 && s_absorbed) *fl.absorb_any = 1;
     if (loads) {
         for (int x = threadIdx.x; x < SLOTS; x += NT)
             if (s_key[x] >= 0) atomicAdd(reinterpret_cast<unsigned long long*>(&o.y[s_key[x]]), s_sum[x]);
@@ -2943,7 +2986,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_push(NetDev net, DemDev dem, cons
     float du = lab_val(lab, u - node0);
     fl.int_node[l] = -1;
     if (!(du <= 3.4028234663852886e38f)) {
-        atomicOr(fl.err_unreach, 1);
+        *fl.err_unreach = 1;
         if (o.stop) o.stop[l] = -1;
         return;
     }
@@ -2967,7 +3010,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_push(NetDev net, DemDev dem, cons
             fl.int_node[l] = u;                         // finishes the leg
             fl.int_tau[l] = 0.0f;
             fl.absorb_q[qi] = 1;
-            atomicAdd(fl.absorb_count, 1);
+            *fl.absorb_any = 1;
             return;
         }
         atomicAdd((unsigned long long*)&o.y[e], (unsigned long long)carry);
@@ -3189,7 +3232,7 @@ hipError_t launch_resid_write(hipStream_t s, const NetDev& net, const DemDev& de
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kWG) void k_trees_out(NetDev net, DemDev dem, const label_t* __restrict__ labels,
                                                    const float* __restrict__ cost, int32_t inst, float* dist,
-                                                   int32_t* succ, int32_t* absorb_q) {
+                                                   int32_t* succ, int32_t* absorb_q, int* absorb_any) {
     const InstDev I = net.inst[inst];
     const int n = I.n;
     const int64_t total = (int64_t)dem.Q * n;
@@ -3203,16 +3246,17 @@ __global__ __launch_bounds__(kWG) void k_trees_out(NetDev net, DemDev dem, const
         int e = -1;
         if (g != dem.dest_node[t] && dv <= 3.4028234663852886e38f) {
             e = succ_strict(net, lab, I.node0, g, dv, cost);   // cost: global link order
-            if (e < 0) absorb_q[t] = 1;
+            if (e < 0 && atomicExch(&absorb_q[t], 1) == 0) *absorb_any = 1;
         }
         succ[i] = e >= 0 ? e - I.link0 : -1;
     }
 }
 
 hipError_t launch_trees_out(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels,
-                            const float* cost, int32_t inst, float* dist, int32_t* succ, int32_t* absorb_q) {
+                            const float* cost, int32_t inst, float* dist, int32_t* succ, int32_t* absorb_q, int* absorb_any) {
     if (dem.Q == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_trees_out, dim3(2048), dim3(kWG), 0, s, net, dem, labels, cost, inst, dist, succ, absorb_q);
+    hipLaunchKernelGGL(k_trees_out, dim3(2048), dim3(kWG), 0, s, net, dem, labels, cost, inst, dist, succ, absorb_q,
+                       absorb_any);
     return hipGetLastError();
 }
 
@@ -3241,7 +3285,7 @@ __global__ __launch_bounds__(kWG) void k_path_walk(NetDev net, DemDev dem, const
     const int64_t at = ptr ? ptr[l] : 0, end = ptr ? ptr[l + 1] : 0;
     int64_t k = 0;
     if (!(du <= 3.4028234663852886e38f)) {
-        atomicOr(bad, 1);
+        bad[0] = 1;
         if (len) len[l] = 0;
         return;
     }
@@ -3252,14 +3296,14 @@ __global__ __launch_bounds__(kWG) void k_path_walk(NetDev net, DemDev dem, const
         float ce = 0.0f;
         const int e = succ_rec(net, lab, node0, u, du, head, ce);
         if (e < 0 || hops > I.n) {
-            atomicOr(bad, 2);
+            bad[1] = 1;
             break;
         }
         const float nt = tau + ce;
         if (I.rule == RULE_FLOOR && nt > I.dt32) break;
         if (ptr) {
             if (at + k >= end) {
-                atomicOr(bad, 4);
+                bad[2] = 1;
                 break;
             }
             links[at + k] = e;
@@ -3291,7 +3335,7 @@ __global__ __launch_bounds__(kWG) void k_path_load(int64_t total, const int32_t*
     for (int64_t i = blockIdx.x * (int64_t)kWG + threadIdx.x; i < total; i += (int64_t)gridDim.x * kWG) {
         const double x = d[leg_of[i]] * 1048576.0;
         if (!(x > -9.0e18 && x < 9.0e18)) {
-            atomicOr(err, 1);
+            *err = 1;
             continue;
         }
         const int64_t w = (int64_t)__builtin_rint(x);

@@ -124,7 +124,12 @@ struct qdta_ctx {
     DBuf<long long> acc, ls_acc;
     DBuf<double> alphas;
     DBuf<unsigned int> ls_ticket; // workgroups of an instance done with the current line-search pass (zero between)
-    DBuf<int> flags;              // [0] overflow, [1] unreach, [2] absorb count, [3] path-record faults
+    // [0] overflow, [1] unreach, [2] absorption, [3..5] path-record faults: pinned
+    // host words that kernels set and the host reads after a synchronisation,
+    // before h_st
+    int* h_flags = nullptr;
+    bool flags_open = false;      // kernels that set flags may be in flight
+    DBuf<int> sink;               // where the flags of a call that does not read them go
     DBuf<int32_t> absorb_q, int_node;
     DBuf<float> int_tau;
     DBuf<float> hist_cost;
@@ -151,6 +156,12 @@ struct qdta_ctx {
     qdta_opts graph_opts;
     InstState* h_st = nullptr;    // pinned mirror
     int h_st_n = 0;
+    // qdta_trees: its destinations on the host (pinned) and its tables and labels
+    int32_t* h_dest = nullptr;
+    int h_dest_n = 0;
+    DBuf<int32_t> t_node, t_inst, t_absorb;
+    DBuf<int64_t> t_lab;
+    DBuf<label_t> t_labels;
     bool solved = false;
     int fw_j = -1;                // FW iteration of the running solve (-1: none)
     bool fw_live = false;
@@ -205,6 +216,9 @@ int set_err(qdta_ctx* c, int code, const char* fmt, ...) {
     } while (0)
 
 constexpr size_t kAlign = 256;
+constexpr size_t kKeepTreeBytes = (size_t)64 << 20;   // labels qdta_trees keeps between calls, at most
+constexpr size_t kFlagBytes = 64;        // qdta_ctx::h_flags, six words of it
+constexpr int kFlags = 6;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 void evict_label_history(qdta_ctx* c);
@@ -502,11 +516,16 @@ int ensure_network(qdta_ctx* c) {
     RC(dalloc(c, c->alphas, (size_t)ni * kMaxK));
     RC(dalloc(c, c->ls_ticket, ni));
     HIPCHECK(c, launch_fill_u32(c->stream, c->ls_ticket.p, 0u, ni));
-    RC(dalloc(c, c->flags, 4));
+    RC(dalloc(c, c->sink, 1));
     RC(dalloc(c, c->done_fx, ni));
     if (c->h_st_n < ni) {
-        if (c->h_st) (void)hipHostFree(c->h_st);
-        HIPCHECK(c, hipHostMalloc((void**)&c->h_st, sizeof(InstState) * ni, hipHostMallocDefault));
+        HIPCHECK(c, hipStreamSynchronize(c->stream));
+        if (c->h_flags) (void)hipHostFree(c->h_flags);
+        c->h_flags = nullptr;
+        c->h_st_n = 0;
+        HIPCHECK(c, hipHostMalloc((void**)&c->h_flags, kFlagBytes + sizeof(InstState) * ni, hipHostMallocCoherent));
+        memset(c->h_flags, 0, kFlagBytes + sizeof(InstState) * ni);
+        c->h_st = reinterpret_cast<InstState*>(reinterpret_cast<char*>(c->h_flags) + kFlagBytes);
         c->h_st_n = ni;
     }
     c->net_dirty = false;
@@ -1005,23 +1024,40 @@ int fallback_slots(const qdta_ctx* c, int64_t trees) {
 
 FlagsDev flags_view(qdta_ctx* c) {
     FlagsDev f;
-    f.err_overflow = c->flags.p;
-    f.err_unreach = c->flags.p + 1;
-    f.absorb_count = c->flags.p + 2;
+    f.err_overflow = c->h_flags;
+    f.err_unreach = c->h_flags + 1;
+    f.absorb_any = c->h_flags + 2;
     f.absorb_q = c->absorb_q.p;
     f.int_node = c->int_node.p;
     f.int_tau = c->int_tau.p;
     return f;
 }
 
-int clear_flags(qdta_ctx* c) {
-    HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->flags.p), 0u, 4));
+// Kernels that set the flags are about to be launched: those of an earlier call
+// that did not get to read its flags are waited for.  (Flags in device memory,
+// cleared by a launch and copied back by each call: 27 us for the link costs of
+// 1,520 links, 14 with the flags here.)
+int open_flags(qdta_ctx* c) {
+    if (c->flags_open) HIPCHECK(c, hipStreamSynchronize(c->stream));
+    c->flags_open = true;
     return QDTA_OK;
 }
 
+int clear_flags(qdta_ctx* c) {
+    RC(open_flags(c));
+    memset(c->h_flags, 0, kFlagBytes);
+    return QDTA_OK;
+}
+
+// The flags, for a stream that has been waited for.
+void take_flags(qdta_ctx* c, int* h) {
+    memcpy(h, c->h_flags, kFlags * sizeof(int));
+    c->flags_open = false;
+}
+
 int read_flags(qdta_ctx* c, int* h) {
-    HIPCHECK(c, hipMemcpyAsync(h, c->flags.p, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
+    take_flags(c, h);
     return QDTA_OK;
 }
 
@@ -1123,21 +1159,17 @@ int aon_core(qdta_ctx* c, const qdta_opts* o, const float* cost, const float* ti
 }
 
 int init_state(qdta_ctx* c, bool all_instances, int iter) {
-    int ni = (int)c->inst.size();
-    for (int i = 0; i < ni; ++i) {
-        InstState s;
-        memset(&s, 0, sizeof(s));
-        s.active = all_instances ? (c->inst[i].m > 0) : (c->h_inst[i].nleg > 0);
-        s.iter = iter;
-        c->h_st[i] = s;
-    }
-    HIPCHECK(c, hipMemcpyAsync(c->st.p, c->h_st, sizeof(InstState) * ni, hipMemcpyHostToDevice, c->stream));
+    HIPCHECK(c, launch_init_state(c->stream, net_view(c), c->st.p, all_instances, iter));
+    return QDTA_OK;
+}
+
+int copy_state(qdta_ctx* c) {
+    HIPCHECK(c, hipMemcpyAsync(c->h_st, c->st.p, sizeof(InstState) * c->inst.size(), hipMemcpyDeviceToHost, c->stream));
     return QDTA_OK;
 }
 
 int pull_state(qdta_ctx* c) {
-    int ni = (int)c->inst.size();
-    HIPCHECK(c, hipMemcpyAsync(c->h_st, c->st.p, sizeof(InstState) * ni, hipMemcpyDeviceToHost, c->stream));
+    RC(copy_state(c));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     return QDTA_OK;
 }
@@ -1148,7 +1180,7 @@ int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
                      const NetDev* net_in = nullptr, bool begin = true) {
     NetDev net = net_in ? *net_in : net_view(c, o);
     int ni = (int)c->inst.size();
-    int* err = c->flags.p;
+    int* err = c->h_flags;
     const bool plain = o->launch_form == 2;
     const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
     LsRule rule{!plain, K, o->ls_mode == QDTA_LS_QN ? 1 : 0, o->passes, o->max_ls, o->T1, o->T2, o->dx, c->ls_ticket.p};
@@ -1172,9 +1204,11 @@ int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
         for (int p = 0; p < o->passes; ++p) RC(pass());
         return QDTA_OK;
     }
-    // quasi-Newton (Alg. 8): iterate until every live instance is done
-    for (int l = 0; l < o->max_ls; ++l) {
-        RC(pass());
+    // quasi-Newton (Alg. 8): iterate until every live instance is done.  A few
+    // passes go before each look at the state (searches take 1 to 5 of them; a
+    // pass over a finished search ends at once, in less than the wait for a look)
+    for (int l = 0; l < o->max_ls;) {
+        for (int k = 0; k < 3 && l < o->max_ls; ++k, ++l) RC(pass());
         RC(pull_state(c));
         bool pending = false, fallback = false;
         for (int i = 0; i < ni; ++i) {
@@ -1419,7 +1453,8 @@ int qdta_destroy(qdta_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (void* p : c->allocs) (void)hipFree(p);
-    if (c->h_st) (void)hipHostFree(c->h_st);
+    if (c->h_flags) (void)hipHostFree(c->h_flags);
+    if (c->h_dest) (void)hipHostFree(c->h_dest);
     for (int p = 0; p < 8; ++p)
         for (int e = 0; e < 2; ++e)
             if (c->prof_ev[p][e]) (void)hipEventDestroy(c->prof_ev[p][e]);
@@ -1688,8 +1723,8 @@ int qdta_bpr(qdta_ctx* c, const qdta_opts* o, const int64_t* f, float* cost) {
     RC(ensure_network(c));
     if (c->dem_dirty) RC(ensure_demand(c, 0));   // kappa of each instance
     RC(clear_flags(c));
-    HIPCHECK(c, launch_bpr(c->stream, net_view(c, o), f, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->flags.p));
-    int h[4];
+    HIPCHECK(c, launch_bpr(c->stream, net_view(c, o), f, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->h_flags));
+    int h[kFlags];
     RC(read_flags(c, h));
     return flag_code(c, h);
 }
@@ -1704,31 +1739,42 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
     if (nq < 0 || (nq > 0 && (!cost || !dest || !dist || !succ))) return set_err(c, QDTA_EARG, "bad arguments");
     if (nq == 0) return QDTA_OK;
     const InstDev I = c->h_inst[inst];
-    std::vector<int32_t> hd(nq);
-    HIPCHECK(c, hipMemcpyAsync(hd.data(), dest, sizeof(int32_t) * nq, hipMemcpyDeviceToHost, c->stream));
+    if (c->h_dest_n < nq) {
+        if (c->h_dest) (void)hipHostFree(c->h_dest);
+        c->h_dest = nullptr;
+        c->h_dest_n = 0;
+        HIPCHECK(c, hipHostMalloc((void**)&c->h_dest, sizeof(int32_t) * std::max(nq, 1024), hipHostMallocDefault));
+        c->h_dest_n = std::max(nq, 1024);
+    }
+    int32_t* hd = c->h_dest;
+    HIPCHECK(c, hipMemcpyAsync(hd, dest, sizeof(int32_t) * nq, hipMemcpyDeviceToHost, c->stream));
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     for (int t = 0; t < nq; ++t)
         if (hd[t] < 0 || hd[t] >= I.n) return set_err(c, QDTA_EARG, "dest[%d] out of range", t);
-    // one tree per requested destination, in order, labels tree-major
-    std::vector<int32_t> dn(nq), di(nq, inst);
-    std::vector<int64_t> dl(nq);
-    for (int t = 0; t < nq; ++t) {
-        dn[t] = I.node0 + hd[t];
-        dl[t] = (int64_t)t * tree_words(I.n);
-    }
-    DBuf<int32_t> ddn, ddi, aq;
-    DBuf<int64_t> ddl;
-    DBuf<label_t> lab;
+    for (int t = 0; t < nq; ++t) hd[t] += I.node0;
+    // one tree per requested destination, in order, labels tree-major.  Small
+    // tables and labels are kept for the next call (40 trees of 400 nodes: 132 us a
+    // call, 185 with the five buffers allocated, filled from the host and freed by
+    // each); large ones, and those carved from a workspace, are given back.
+    DBuf<int32_t>&ddn = c->t_node, &ddi = c->t_inst, &aq = c->t_absorb;
+    DBuf<int64_t>& ddl = c->t_lab;
+    DBuf<label_t>& lab = c->t_labels;
     auto cleanup = [&]() {
-        for (void* p : {(void*)ddn.p, (void*)ddi.p, (void*)aq.p, (void*)ddl.p, (void*)lab.p}) dev_free(c, p);
+        if (!c->ws_base && lab.n * sizeof(label_t) <= kKeepTreeBytes) return;
+        dfree(c, ddn);
+        dfree(c, ddi);
+        dfree(c, aq);
+        dfree(c, ddl);
+        dfree(c, lab);
     };
+    RC(clear_flags(c));
     int rc = QDTA_OK;
     do {
-        if ((rc = upload(c, ddn, dn))) break;
-        if ((rc = upload(c, ddi, di))) break;
-        if ((rc = upload(c, ddl, dl))) break;
+        if ((rc = dalloc(c, ddn, (size_t)nq))) break;
+        if ((rc = dalloc(c, ddi, (size_t)nq))) break;
+        if ((rc = dalloc(c, ddl, (size_t)nq))) break;
         if ((rc = dalloc(c, lab, (size_t)nq * tree_words(I.n)))) break;
-        if ((rc = dalloc(c, aq, nq))) break;
+        if ((rc = dalloc(c, aq, (size_t)nq))) break;
         int saved_slots = c->slots;
         if ((rc = ensure_scratch(c, nq, std::max<int64_t>(c->nmax, I.n), waves_per_cu(o), tree_waves(o)))) break;
         int slots = c->slots;
@@ -1739,9 +1785,11 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         dem.dest_inst = ddi.p;
         dem.dest_lab = ddl.p;
         dem.Q = nq;
-        if (uses_contraction(o) && (rc = ensure_contraction(c, dn.data(), dn.size()))) break;
+        if (uses_contraction(o) && (rc = ensure_contraction(c, hd, (size_t)nq))) break;
         NetDev net = net_view(c);
         hipError_t e;
+        if ((e = launch_tree_tables(c->stream, dest, nq, I.node0, inst, tree_words(I.n), ddn.p, ddi.p, ddl.p)))
+            { rc = set_err(c, QDTA_EHIP, "tree tables: %s", hipGetErrorString(e)); break; }
         // place the instance's costs in the global link order
         if ((e = hipMemcpyAsync(c->cost.p + I.link0, cost, sizeof(float) * I.m, hipMemcpyDeviceToDevice, c->stream)))
             { rc = set_err(c, QDTA_EHIP, "copy cost: %s", hipGetErrorString(e)); break; }
@@ -1750,7 +1798,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab.p, scr_view(c), slots, nullptr,
                              delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 0, true, nullptr, aq.p)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_trees_out(c->stream, net, dem, lab.p, c->cost.p, inst, dist, succ, aq.p)))
+        if ((e = launch_trees_out(c->stream, net, dem, lab.p, c->cost.p, inst, dist, succ, aq.p, c->h_flags + 2)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }
         FlagsDev fl = flags_view(c);
         fl.absorb_q = aq.p;
@@ -1758,14 +1806,12 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
                                  scr_view(c), fallback_slots(c, nq), 0, nullptr, nullptr, nullptr,
                                  1, succ, I.n)))
             { rc = set_err(c, QDTA_EHIP, "fallback: %s", hipGetErrorString(e)); break; }
-        std::vector<int32_t> ha(nq);
-        if ((e = hipMemcpyAsync(ha.data(), aq.p, sizeof(int32_t) * nq, hipMemcpyDeviceToHost, c->stream)))
-            { rc = set_err(c, QDTA_EHIP, "copy: %s", hipGetErrorString(e)); break; }
         if ((e = hipStreamSynchronize(c->stream))) { rc = set_err(c, QDTA_EHIP, "sync: %s", hipGetErrorString(e)); break; }
-        for (int t = 0; t < nq; ++t)
-            if (ha[t]) rc = QDTA_WABSORB;
+        int h[kFlags];
+        take_flags(c, h);
+        if (h[2]) rc = QDTA_WABSORB;
     } while (0);
-    (void)hipStreamSynchronize(c->stream);
+    if (rc < 0) (void)hipStreamSynchronize(c->stream);
     cleanup();
     return rc;
 }
@@ -1782,12 +1828,10 @@ int qdta_aon(qdta_ctx* c, const qdta_opts* o, const float* cost, int64_t* y, int
     RC(init_state(c, false, 0));
     RC(clear_flags(c));
     NetDev net = net_view(c);
-    HIPCHECK(c, hipMemcpyAsync(c->cost.p, cost, sizeof(float) * c->M, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHECK(c, launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p, c->logpart.p));
-    if (stop) HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(stop), 0xffffffffu, c->P));
+    HIPCHECK(c, launch_scatter_rcost(c->stream, net, cost, c->radj.p, c->logpart.p, c->cost.p));
     if (stop_delay) HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(stop_delay), 0u, c->P));
     RC(aon_core(c, o, c->cost.p, nullptr, y, stop, nullptr, true, stop_delay));
-    int h[4];
+    int h[kFlags];
     RC(read_flags(c, h));
     prof_collect(c);
     RC(flag_code(c, h));
@@ -1806,9 +1850,9 @@ int qdta_ls_eval(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const int64_
     RC(clear_flags(c));
     HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->ls_acc.p), 0, (int64_t)ni * K * 6 * kLsReps));
     HIPCHECK(c, launch_ls_eval(c->stream, net_view(c, o), f, y, o->alpha, o->beta, K, const_cast<double*>(alphas),
-                               c->ls_acc.p, nullptr, 0, c->flags.p, LsRule{}));   // no decision: alphas stay
+                               c->ls_acc.p, nullptr, 0, c->h_flags, LsRule{}));   // no decision: alphas stay
     HIPCHECK(c, launch_ls_export(c->stream, ni, c->ls_acc.p, K, kLsReps, sums));
-    int h[4];
+    int h[kFlags];
     RC(read_flags(c, h));
     return flag_code(c, h);
 }
@@ -1853,11 +1897,9 @@ int qdta_line_search(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
     RC(clear_flags(c));
     RC(line_search_core(c, o, f, y));
     HIPCHECK(c, launch_copy_alpha(c->stream, ni, c->st.p, alpha_out));
-    int h[4];
+    int h[kFlags];
     RC(read_flags(c, h));
-    RC(flag_code(c, h));
-    RC(pull_state(c));
-    return QDTA_OK;
+    return flag_code(c, h);
 }
 
 int qdta_fw_update(qdta_ctx* c, int64_t* f, const int64_t* y, const double* alpha) {
@@ -1893,7 +1935,7 @@ int qdta_fw_begin(qdta_ctx* c, const qdta_opts* o) {
     HIPCHECK(c, launch_fill_i64(c->stream, c->f.p, 0, c->M));
     RC(prof_mark(c, PH_BPR, 0));
     float* tc = o->objective == QDTA_OBJ_SO ? c->tcost.p : nullptr;
-    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, c->st.p, 1, c->flags.p,
+    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, c->st.p, 1, c->h_flags,
                            tc, c->logpart.p));
     RC(prof_mark(c, PH_BPR, 1));
     c->lab_hist_ok.clear();
@@ -1935,7 +1977,7 @@ void fill_stats(qdta_ctx* c, qdta_stats* hs, int worst, const int* h) {
 // unless the quasi-Newton search is selected.
 int enqueue_iteration(qdta_ctx* c, const qdta_opts* o, bool marks) {
     NetDev net = net_view(c, o);
-    int* err = c->flags.p;
+    int* err = c->h_flags;
     const int cap_iter = o->fixed_iters > 0 ? o->fixed_iters : o->max_iter;
     if (marks) RC(prof_mark(c, PH_BPR, 0));
     float* tc = o->objective == QDTA_OBJ_SO ? c->tcost.p : nullptr;
@@ -1957,6 +1999,7 @@ int enqueue_iteration(qdta_ctx* c, const qdta_opts* o, bool marks) {
     if (marks) RC(prof_mark(c, PH_LS, 1));
     if (marks) RC(prof_mark(c, PH_UPDATE, 0));
     HIPCHECK(c, launch_fw_update(c->stream, net, c->f.p, c->y.p, nullptr, c->st.p, o->fixed_iters));
+    RC(copy_state(c));                    // read by the host after the iteration's synchronisation
     if (marks) RC(prof_mark(c, PH_UPDATE, 1));
     return QDTA_OK;
 }
@@ -2004,6 +2047,7 @@ int capture_iteration(qdta_ctx* c, const qdta_opts* o) { return capture_once(c, 
 // One Frank-Wolfe iteration j, then one host synchronisation.
 int fw_iteration(qdta_ctx* c, const qdta_opts* o, int* h) {
     int ni = (int)c->inst.size();
+    RC(open_flags(c));
     const int j = ++c->fw_j;
     if (graph_form(o)) {
         if (!c->graph_exec || c->graph_gen != c->gen || memcmp(&c->graph_opts, o, sizeof(qdta_opts)) != 0)
@@ -2020,8 +2064,8 @@ int fw_iteration(qdta_ctx* c, const qdta_opts* o, int* h) {
                                    hipMemcpyDeviceToDevice, c->stream));
         RC(stash_labels(c, j));
     }
-    HIPCHECK(c, hipMemcpyAsync(h, c->flags.p, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    RC(pull_state(c));
+    HIPCHECK(c, hipStreamSynchronize(c->stream));   // the state's copy too (enqueue_iteration)
+    take_flags(c, h);
     prof_collect(c);
     RC(flag_code(c, h));
     bool live = false;
@@ -2040,12 +2084,13 @@ int fw_iteration(qdta_ctx* c, const qdta_opts* o, int* h) {
 int fw_finish(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs) {
     int ni = (int)c->inst.size();
     NetDev net = net_view(c, o);
-    int h[4];
+    int h[kFlags];
+    RC(open_flags(c));
     // objective of the returned iterates
-    HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 0, o->tol, c->flags.p,
+    HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 0, o->tol, c->h_flags,
                            c->ls_ticket.p));
-    HIPCHECK(c, hipMemcpyAsync(h, c->flags.p, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     RC(pull_state(c));
+    take_flags(c, h);
     int worst = flag_code(c, h);
     for (int i = 0; i < ni; ++i) {
         const InstState& s = c->h_st[i];
@@ -2067,11 +2112,11 @@ int qdta_fw_step(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs, int32_t* live_
     if (c->fw_j < 0 || c->dem_dirty) return set_err(c, QDTA_ESTATE, "qdta_fw_step needs qdta_fw_begin");
     RC(ensure_sweep(c, o));
     RC(ensure_contract(c, o));
-    int h[4] = {0, 0, 0, 0};
+    int h[kFlags] = {0};
     if (c->fw_live) RC(fw_iteration(c, o, h));
     else {
-        HIPCHECK(c, hipMemcpyAsync(h, c->flags.p, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
         RC(pull_state(c));
+        take_flags(c, h);
     }
     for (int i = 0; i < (int)c->inst.size(); ++i) c->inst[i].solved_iters = c->h_st[i].iters;
     fill_stats(c, hs, QDTA_OK, h);
@@ -2082,7 +2127,7 @@ int qdta_fw_step(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs, int32_t* live_
 
 int qdta_solve(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs) {
     RC(qdta_fw_begin(c, o));
-    int h[4];
+    int h[kFlags];
     while (c->fw_live) RC(fw_iteration(c, o, h));
     return fw_finish(c, o, hs);
 }
@@ -2104,7 +2149,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     // else free flow
     if (!c->solved && c->fw_j < 0) HIPCHECK(c, launch_fill_i64(c->stream, c->f.p, 0, c->M));
     RC(clear_flags(c));
-    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, nullptr, 0, c->flags.p,
+    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cost.p, c->radj.p, nullptr, 0, c->h_flags,
                            nullptr, c->logpart.p));
     hipEvent_t e0, e1;
     HIPCHECK(c, hipEventCreate(&e0));
@@ -2249,7 +2294,7 @@ int qdta_get_costs(qdta_ctx* c, const qdta_opts* o, float* cost) {
     if (!c || !cost) return QDTA_EARG;
     if (!opts_ok(c, o)) return QDTA_EARG;
     if (!c->solved && c->fw_j < 0) return set_err(c, QDTA_ESTATE, "no solved or running interval");
-    HIPCHECK(c, launch_bpr(c->stream, net_view(c), c->f.p, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->flags.p));
+    HIPCHECK(c, launch_bpr(c->stream, net_view(c), c->f.p, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->sink.p));
     return QDTA_OK;
 }
 
@@ -2267,7 +2312,7 @@ int qdta_advance_interval(qdta_ctx* c, const qdta_opts* o) {
     FlagsDev fl = flags_view(c);
     RC(clear_flags(c));
     // final costs c_fin = BPR(f)
-    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cfin.p, nullptr, nullptr, 0, c->flags.p));
+    HIPCHECK(c, launch_bpr(c->stream, net, c->f.p, o->alpha, o->beta, c->cfin.p, nullptr, nullptr, 0, c->h_flags));
     int J = 0;
     for (const Instance& I : c->inst) J = std::max(J, I.solved_iters);
     // lambda_j = alpha_j prod_{k>j} (1 - alpha_k), alpha_0 = 1, per instance;
@@ -2396,7 +2441,7 @@ int qdta_advance_interval(qdta_ctx* c, const qdta_opts* o) {
             HIPCHECK(c, hipMemcpyAsync(tw.data(), c->tr_w.p, sizeof(int64_t) * ntr, hipMemcpyDeviceToHost, c->stream));
         }
     }
-    int h[4];
+    int h[kFlags];
     RC(read_flags(c, h));                  // synchronises the stream
     c->r_dense_zero = zero_after;
     // trees are instance-major, so each instance's legs are one run
@@ -2502,13 +2547,13 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
         }
         RC(clear_flags(c));
         HIPCHECK(c, launch_path_walk(c->stream, net, dem, lab, nullptr, nullptr, nullptr, c->adj_len.p,
-                                     c->flags.p + 3));
+                                     c->h_flags + 3));
         if (P) HIPCHECK(c, hipMemcpyAsync(len.data(), c->adj_len.p, sizeof(int64_t) * P, hipMemcpyDeviceToHost,
                                           c->stream));
-        int h[4];
+        int h[kFlags];
         RC(read_flags(c, h));
-        if (h[3] & 1) return set_err(c, QDTA_EUNREACH, "iterate %d: a leg's origin cannot reach its destination", j);
-        if (h[3] & 2) return set_err(c, QDTA_ESTATE, "iterate %d: FP32 absorption (tie fallback) on a path", j);
+        if (h[3]) return set_err(c, QDTA_EUNREACH, "iterate %d: a leg's origin cannot reach its destination", j);
+        if (h[4]) return set_err(c, QDTA_ESTATE, "iterate %d: FP32 absorption (tie fallback) on a path", j);
         ptr[0] = 0;
         for (int64_t l = 0; l < P; ++l) ptr[l + 1] = ptr[l] + len[l];
         RC(dalloc(c, c->adj_ptr[j], (size_t)P + 1));
@@ -2518,9 +2563,10 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
         HIPCHECK(c, hipMemcpyAsync(c->adj_ptr[j].p, ptr.data(), sizeof(int64_t) * (P + 1), hipMemcpyHostToDevice,
                                    c->stream));
         HIPCHECK(c, launch_path_walk(c->stream, net_view(c), dem_view(c), lab, c->adj_ptr[j].p, c->adj_links[j].p,
-                                     c->adj_leg[j].p, nullptr, c->flags.p + 3));
+                                     c->adj_leg[j].p, nullptr, c->h_flags + 3));
         RC(read_flags(c, h));
-        if (h[3]) return set_err(c, QDTA_ESTATE, "iterate %d: paths changed between the two walks", j);
+        if (h[3] || h[4] || h[5])
+            return set_err(c, QDTA_ESTATE, "iterate %d: paths changed between the two walks", j);
     }
     c->adj_J = J;
     c->adj_gen = c->gen;
@@ -2547,7 +2593,7 @@ int qdta_model_forward(qdta_ctx* c, const qdta_opts* o, const double* d, const f
         int64_t* yj = c->adj_y.p + (size_t)j * M;
         HIPCHECK(c, launch_fill_i64(c->stream, yj, 0, M));
         HIPCHECK(c, launch_path_load(c->stream, c->adj_total[j], c->adj_links[j].p, c->adj_leg[j].p, d, yj,
-                                     c->flags.p));
+                                     c->h_flags));
         if (j == 0) {
             HIPCHECK(c, hipMemcpyAsync(c->adj_cur.p, yj, sizeof(int64_t) * M, hipMemcpyDeviceToDevice, c->stream));
             continue;
@@ -2560,7 +2606,7 @@ int qdta_model_forward(qdta_ctx* c, const qdta_opts* o, const double* d, const f
         HIPCHECK(c, launch_fw_update(c->stream, net, c->adj_cur.p, yj, c->adj_alpha.p + j, nullptr));
     }
     HIPCHECK(c, launch_fx_to_veh(c->stream, M, c->adj_cur.p, f_out));
-    int h[4];
+    int h[kFlags];
     RC(read_flags(c, h));
     RC(flag_code(c, h));
     c->adj_fwd = true;
