@@ -122,9 +122,10 @@ typedef struct {
     double delta_scale;    /* delta-stepping bucket width as a multiple of the instance's geometric-mean
                               link cost: 0 auto (10.0); any value > 0 gives the same trees, only the speed
                               changes */
-    int32_t sssp_shape;    /* shortest-path kernel shape, 0 auto (3); a workgroup per tree, its threads in
-                              units of 128 x links per thread per step: 1 (1,2), 2 (1,4), 3 (2,4),
-                              4 (4,4), 5 (2,2), 6 (4,2); one wavefront per tree, nodes per lane per step
+    int32_t sssp_shape;    /* shortest-path kernel shape, 0 auto (3, or 4 for a workgroup per tree and no
+                              more trees than compute units); a workgroup per tree, its threads in units
+                              of 128 x links of a node per step: 1 (1,2), 2 (1,4), 3 (2,4), 4 (4,4),
+                              5 (2,2), 6 (4,2); one wavefront per tree, nodes per lane per step
                               x links per lane per chunk: 1 (1,4), 2 (2,4), 3 (4,4), 4 (4,8), 5 (8,8),
                               6 (1,1) */
     int32_t launch_form;   /* 0 batched: every tree of every instance in one launch, all K step sizes in

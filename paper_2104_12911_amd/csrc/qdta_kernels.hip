@@ -1282,16 +1282,22 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
 //     number of records already relaxed.  Records whose source is the parent,
 //     the node this value came from, are skipped: adding non-negative costs to a
 //     value that came from the parent's label cannot lower that label.
-//   - A step takes up to NT entries, one per thread: from a circular buffer in
-//     LDS, then from the ring in memory that takes the buffer's overflow.  Each
-//     thread relaxes up to V records of its entry, their loads issued together;
-//     the rest of a longer row is queued again in pieces of V.
+//   - A step takes up to NT entries, from a circular buffer in LDS, then from the
+//     ring in memory that takes the buffer's overflow.  V neighbouring lanes
+//     relax an entry, one record each, so that a row is one piece of memory to
+//     the load; a wavefront takes 64 / V entries a round, every wavefront as many
+//     rounds as the step's entries need (at most V, issued together).  The rest
+//     of a row longer than V is queued again in pieces of V.
 //   - No label is changed by an atomic: on this memory they are carried out
 //     beyond the L2 (one memory write each, and the line leaves the L2).  Only
-//     the tree's own workgroup touches its labels, so a step's improvements
-//     meet in a hash table in LDS; after a barrier the least candidate of each
-//     node (one of equal ones) stores the label and queues the node.  Two
-//     barriers a step, and two dependent memory accesses, record and label.
+//     the tree's own workgroup touches its labels, so a step's improvements meet
+//     in a table in LDS: each puts its key (step, value, its number) into the
+//     slot of its node's hash by one atomic minimum.  Keys of a later step are
+//     smaller, so the table is not cleared.  After a barrier a candidate whose
+//     key is still there stores the label and queues the node; one beaten by a
+//     key of the same node is done; one beaten by another node's key (about one
+//     in 20) has its record queued again, as a row of one, for the next step.
+//     Two barriers a step, and two dependent memory accesses, record and label.
 //   - Entries at or above the bucket bound thr go to the far queue.  When the
 //     near entries are used up, thr moves delta above the smallest far value and
 //     one pass moves the far entries below it, dropping those whose label has
@@ -1306,46 +1312,52 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
 // nodes' labels are filled from their chains' ends afterwards (k_chain_fill).
 //
 // Bound by memory traffic where all trees together are far larger than the L2
-// (550k nodes, 5,000 trees: 51 ms, 84 ms before this form; the same at 16 to 32
-// wavefronts per CU), by the latency of a step's chain of accesses below that
-// (metro network, 100k nodes, 1,000 trees: 2.4 ms, 5.7; 22,801-node grid, 300
-// trees: 0.80 ms, 3.77; 400-node grid, 40 trees: 0.07 ms, 0.13).  What each part
-// gave on the 550k nodes: no flag and no pop access 84 -> 65 ms, no atomics ->
-// 56, no dependent cost block for a chain -> 54.6, the step's two barriers and
-// branch-free phases -> 51 (and 2.7 -> 2.4 ms on the metro network, 1.2 -> 0.8
-// on the grid).
+// (550k nodes, 5,000 trees: 48 ms, 84 ms before this form), by the latency of a
+// step's chain of accesses and the issue of its instructions below that (metro
+// network, 100k nodes, 1,000 trees: 2.1 ms, 5.7; 22,801-node grid, 300 trees:
+// 0.69 ms, 3.77; 400-node grid, 40 trees: 0.06 ms, 0.13).  What each part gave on
+// the 550k nodes: no flag and no pop access 84 -> 65 ms, no atomics -> 56, no
+// dependent cost block for a chain -> 54.6, the step's two barriers and
+// branch-free phases -> 51 (and 2.7 -> 2.4 ms on the metro network, 1.2 -> 0.8 on
+// the grid), lanes over records with minimum keys instead of a thread per entry
+// with compare-and-swapped slots -> 48 (2.4 -> 2.1, 0.79 -> 0.69).
 //
-// W: wavefronts per SIMD the register allocation leaves room for (1: the
-// compiler's choice).  The LDS holds four workgroups of <2, 4> per CU whatever
-// it is; 7 keeps it at 72 VGPRs instead of 90, in the same time.
-template <int U, int V, bool CT, int W = 1>
-__global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(W))) void k_sssp_wg(
+// W: wavefronts per SIMD the register allocation aims at, at most; <2, 4> and
+// <2, 2> keep to 128 VGPRs, for the four workgroups per CU that the LDS holds
+// (151 of them, for three: 2.7 instead of 2.1 ms on the metro network, whose
+// 1,000 trees then take two turns).
+template <int U, int V, bool CT, int W = 8>
+__global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(U == 2 ? 4 : 1, W))) void k_sssp_wg(
     NetDev net, DemDev dem, const uint2* __restrict__ radj, label_t* labels, Scratch scr, const InstState* st,
     const float* __restrict__ delta_inst, int early, int t_begin, int t_end) {
     constexpr int NT = 128 * U;
+    constexpr int NW = NT / 64;
+    constexpr int E = 64 / V;                     // entries of a round: one record per lane
     constexpr int NB = 2 * NT;                    // entries of the LDS buffer
     constexpr int NH = 2 * V * NT;                // slots of the hash table, twice what a step can take
-    constexpr unsigned long long kFree = ~0ull;
+    constexpr int kIdBits = 11;
+    constexpr uint32_t kIdMask = (1u << kIdBits) - 1u;
+    constexpr uint32_t kEpochs = 1u << (32 - kIdBits);
+    static_assert(NT * V <= 1 << kIdBits, "a candidate's number fits");
     constexpr int F = NT >= 512 ? 1 : 512 / NT;   // far entries per thread and turn of a pass over them
     static_assert(NT * (V + 1) <= kSearchSlack, "the far queue has room for one step beyond a node each");
-    // 64 spare words after each array: what a lane without work reads and writes
-    // (its own word), so that the V accesses of a phase are issued back to back
-    // with no branch between them
+    // 64 spare words after the first two: what a lane without work reads and
+    // writes (its own word), so that the accesses of a phase are issued back to
+    // back with no branch between them
     __shared__ uint4 s_buf[NB + 64];              // near entries
-    __shared__ unsigned long long s_val[NH + 64]; // the step's improvements: least (candidate, its number)
-    __shared__ uint32_t s_key[NH + 64];           // of this node
+    __shared__ unsigned long long s_val[NH + 64]; // per slot the least key put into it
+    __shared__ uint2 s_cand[V * NT];              // node and value of each candidate of the step
     __shared__ unsigned long long s_cnt[2];       // far << 32 | near entries pushed in a step (odd, even)
     __shared__ int s_t;                           // next tree
     __shared__ uint32_t s_fm;                     // smallest value pushed to far
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lx = lane & (V - 1);
     const int cap = (int)scr.nmax;                // entries of the ring and of the far queue
     uint4* nearq = reinterpret_cast<uint4*>(scr.nearq) + (int64_t)blockIdx.x * scr.nmax;
     uint4* farq = reinterpret_cast<uint4*>(scr.farq) + (int64_t)blockIdx.x * scr.nmax;
     const uint4* __restrict__ crec = reinterpret_cast<const uint4*>(net.cbuf);
-    for (int x = tid; x < NH + 64; x += NT) {
-        s_key[x] = kNoNode;
-        s_val[x] = kFree;
-    }
+    for (int x = tid; x < NH + 64; x += NT) s_val[x] = ~0ull;
+    uint32_t epoch = kEpochs - 1u;
     unsigned long long n_taken = 0;               // counted by every thread alike (uniform values)
     unsigned int n_relaxed = 0;                   // this thread's own
     for (;;) {
@@ -1468,95 +1480,108 @@ __global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(W))) vo
                     __syncthreads();              // the counters' reset is seen
                     sweep_far(0.0f, true);        // keep only the live far entries
                 }
+                if (--epoch == 0u) {
+                    for (int x = tid; x < NH + 64; x += NT) s_val[x] = ~0ull;
+                    epoch = kEpochs - 2u;
+                    __syncthreads();
+                }
                 const int k = min(bc + rc, NT), kb = min(bc, k);
-                uint4 ent = make_uint4(0u, 0u, 0u, 0u), r[V];
-                int e0 = 0, deg = 0;
-                uint32_t cb[V], okm = 0u;         // candidates; bit x: record x may lower its source
-                int slot[V];
-                const bool some = (tid & ~63) < k;    // this wavefront has entries
-                if (some) {
-                    if (tid < kb) {
-                        ent = s_buf[(bh + tid) & (NB - 1)];
-                    } else if (tid < k) {
-                        int q = rh + (tid - kb);
-                        if (q >= cap) q -= cap;
-                        ent = nearq[q];
+                // this wavefront's rounds: every NW-th E entries
+                const int rounds = k > wv * E ? (k - wv * E + NW * E - 1) / (NW * E) : 0;
+                uint4 ent[V], r[V];
+                uint32_t cb[V];                   // candidates
+                uint32_t okm = 0u, lng = 0u;      // bit j: may lower its source; first of a row longer than V
+                auto row_of = [&](const uint4& e, int& first, int& deg) {
+                    if (e.y & kNoRow) {
+                        first = rptr[e.x] + (int)(e.y & ~kNoRow);
+                        deg = rptr[e.x + 1] - first;
+                        if (deg == 0) first = 0;
                     }
-                    if (tid < k) {
-                        e0 = (int)(ent.y >> kRowCountBits);
-                        deg = (int)(ent.y & ((1u << kRowCountBits) - 1u));
-                        if (!CT || (ent.y & kNoRow)) {
-                            e0 = rptr[ent.x] + (int)(ent.y & ~kNoRow);
-                            deg = rptr[ent.x + 1] - e0;
-                            if (deg == 0) e0 = 0;
+                };
+                auto slot_of = [&](uint32_t v, bool p) {
+                    return p ? (int)((v * 2654435761u) >> 16) & (NH - 1) : NH + lane;
+                };
+                auto relax = [&](auto nr) __attribute__((always_inline)) {
+                    constexpr int R = decltype(nr)::value;
+                    int e0[R], deg[R];
+                    bool in[R], un = false;
+#pragma unroll
+                    for (int j = 0; j < R; ++j) ent[j] = s_buf[(bh + (j * NW + wv) * E + lane / V) & (NB - 1)];
+                    if (k > kb) {
+#pragma unroll
+                        for (int j = 0; j < R; ++j) {
+                            const int i = (j * NW + wv) * E + lane / V;
+                            int q = rh + (i - kb);
+                            if (q >= cap) q -= cap;
+                            if (i >= kb && i < k) ent[j] = nearq[q];
                         }
                     }
-                    const int top = max(deg - 1, 0);
-                    const float d = __uint_as_float(ent.z);
-                    if (CT) {
 #pragma unroll
-                        for (int x = 0; x < V; ++x) r[x] = crec[e0 + min(x, top)];
-                    } else {
+                    for (int j = 0; j < R; ++j) {
+                        in[j] = (j * NW + wv) * E + lane / V < k;
+                        e0[j] = in[j] ? (int)(ent[j].y >> kRowCountBits) : 0;
+                        deg[j] = in[j] ? (int)(ent[j].y & ((1u << kRowCountBits) - 1u)) : 0;
+                        un |= in[j] && (ent[j].y & kNoRow);
+                    }
+                    if (__ballot(un)) {
 #pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            const uint2 q = radj[e0 + min(x, top)];
-                            r[x] = make_uint4(q.x, q.y, 0u, kNoRow);
+                        for (int j = 0; j < R; ++j)
+                            if (in[j]) row_of(ent[j], e0[j], deg[j]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        const int at = e0[j] + min(lx, max(deg[j] - 1, 0));
+                        if (CT) {
+                            r[j] = crec[at];
+                        } else {
+                            const uint2 q = radj[at];
+                            r[j] = make_uint4(q.x, q.y, 0u, kNoRow);
                         }
                     }
-                    uint32_t cur[V], two = 0u;
+                    uint32_t cur[R], two = 0u;
 #pragma unroll
-                    for (int x = 0; x < V; ++x) {
+                    for (int j = 0; j < R; ++j) {
                         // form 0: a link; 1, 2: a chain's two or three costs; the last
                         // word is the source's packed row but for form 2 (see below)
-                        const uint32_t form = CT ? r[x].x >> 30 : 0u;
-                        r[x].x = (CT ? r[x].x & 0x3fffffffu : r[x].x) - node0;
-                        const float c1 = d + __uint_as_float(r[x].y);
-                        const float c2 = c1 + __uint_as_float(r[x].z);
-                        const float c3 = c2 + __uint_as_float(r[x].w);
-                        cb[x] = __float_as_uint(form == 0u ? c1 : form == 1u ? c2 : c3);
-                        const bool ok = x < deg && r[x].x != ent.w;
-                        okm |= ok ? 1u << x : 0u;
-                        if (CT) two |= ok && form == 2u ? 1u << x : 0u;
-                        cur[x] = D[ok ? r[x].x : 0u];
+                        const float d = __uint_as_float(ent[j].z);
+                        const uint32_t form = CT ? r[j].x >> 30 : 0u;
+                        r[j].x = (CT ? r[j].x & 0x3fffffffu : r[j].x) - node0;
+                        const float c1 = d + __uint_as_float(r[j].y);
+                        const float c2 = c1 + __uint_as_float(r[j].z);
+                        const float c3 = c2 + __uint_as_float(r[j].w);
+                        cb[j] = __float_as_uint(form == 0u ? c1 : form == 1u ? c2 : c3);
+                        const bool ok = lx < deg[j] && r[j].x != ent[j].w;
+                        okm |= ok ? 1u << j : 0u;
+                        lng |= lx == 0 && deg[j] > V ? 1u << j : 0u;
+                        if (CT) two |= ok && form == 2u ? 1u << j : 0u;
+                        cur[j] = D[ok ? r[j].x : 0u];
+                        n_relaxed += lx < deg[j] ? 1u : 0u;
                     }
                     if (CT && __ballot(two != 0u)) {
 #pragma unroll
-                        for (int x = 0; x < V; ++x)
-                            if (two >> x & 1u) r[x].w = crow[r[x].x];
+                        for (int j = 0; j < R; ++j)
+                            if (two >> j & 1u) r[j].w = crow[r[j].x];
                     }
-                    n_relaxed += (unsigned)min(deg, V);
-                    // claim a slot per node, the V probes of a round together (at most
-                    // half of the slots are taken)
-                    uint32_t pend = 0u;
 #pragma unroll
-                    for (int x = 0; x < V; ++x) {
-                        pend |= cb[x] < cur[x] ? 1u << x : 0u;
-                        slot[x] = (int)((r[x].x * 2654435761u) >> 16) & (NH - 1);
+                    for (int j = 0; j < R; ++j) {
+                        const uint32_t id = (uint32_t)((j * NW + wv) * 64 + lane);
+                        const bool p = (okm >> j & 1u) && cb[j] < cur[j];
+                        okm = p ? okm : okm & ~(1u << j);
+                        const unsigned long long key =
+                            (unsigned long long)__builtin_amdgcn_alignbit(epoch, cb[j], 32 - kIdBits) << 32 |
+                            (cb[j] << kIdBits | id);
+                        atomicMin(&s_val[slot_of(r[j].x, p)], key);
+                        s_cand[id] = make_uint2(r[j].x, cb[j]);
                     }
-                    okm &= pend;
-                    pend = okm;
-                    do {
-                        uint32_t o[V], key[V];
-#pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            const bool p = pend >> x & 1u;
-                            key[x] = p ? r[x].x : kNoNode;
-                            o[x] = atomicCAS(&s_key[p ? slot[x] : NH + lane], kNoNode, key[x]);
-                        }
-#pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            const bool p = o[x] != kNoNode && o[x] != key[x];
-                            slot[x] = p ? (slot[x] + 1) & (NH - 1) : slot[x];
-                            pend &= p ? ~0u : ~(1u << x);
-                        }
-                    } while (__ballot(pend != 0u));
-#pragma unroll
-                    for (int x = 0; x < V; ++x) {
-                        const bool p = okm >> x & 1u;
-                        slot[x] = p ? slot[x] : NH + lane;
-                        atomicMin(&s_val[slot[x]],
-                                  p ? ((unsigned long long)cb[x] << 32) | (unsigned)(tid * V + x) : kFree);
-                    }
+                };
+                if constexpr (V == 2) {
+                    if (rounds == 1) relax(std::integral_constant<int, 1>{});
+                    else if (rounds) relax(std::integral_constant<int, 2>{});
+                } else {
+                    if (rounds == 1) relax(std::integral_constant<int, 1>{});
+                    else if (rounds == 2) relax(std::integral_constant<int, 2>{});
+                    else if (rounds == 3) relax(std::integral_constant<int, 3>{});
+                    else if (rounds) relax(std::integral_constant<int, V>{});
                 }
                 const int kr = k - kb;
                 bh = (bh + kb) & (NB - 1);
@@ -1566,50 +1591,105 @@ __global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(W))) vo
                 rc -= kr;
                 n_taken += (unsigned)k;
                 __syncthreads();
-                // the least candidate of each node (the lowest numbered of equal ones)
-                // writes the label, queues the node and clears the slot (a candidate
-                // that reads it afterwards loses as well)
-                if (some) {
-                    unsigned long long best[V], bn[V], bf[V];
+                // the least key of each slot is its candidate's, which writes the label
+                // and queues the node
+                auto resolve = [&](auto nr) __attribute__((always_inline)) {
+                    constexpr int R = decltype(nr)::value;
+                    uint32_t top[R], win = 0u, put;
+                    unsigned long long bn[R], bf[R];
                     int cn = 0, cf = 0;
 #pragma unroll
-                    for (int x = 0; x < V; ++x) best[x] = s_val[slot[x]];
-                    uint32_t win = 0u;
+                    for (int j = 0; j < R; ++j) top[j] = (uint32_t)s_val[slot_of(r[j].x, okm >> j & 1u)];
 #pragma unroll
-                    for (int x = 0; x < V; ++x) {
-                        const bool w = (okm >> x & 1u) && best[x] == (((unsigned long long)cb[x] << 32) |
-                                                                      (unsigned)(tid * V + x));
-                        const bool nr = __uint_as_float(cb[x]) < thr;
-                        win |= w ? 1u << x : 0u;
-                        bn[x] = __ballot(w && nr);
-                        bf[x] = __ballot(w && !nr);
-                        cn += __popcll(bn[x]);
-                        cf += __popcll(bf[x]);
-                        slot[x] = w ? slot[x] : NH + lane;
-                        s_val[slot[x]] = kFree;
-                        s_key[slot[x]] = kNoNode;
+                    for (int j = 0; j < R; ++j) {
+                        const uint32_t id = (uint32_t)((j * NW + wv) * 64 + lane);
+                        const bool w = (okm >> j & 1u) && top[j] == (cb[j] << kIdBits | id);
+                        win |= w ? 1u << j : 0u;
+                        if (w) D[r[j].x] = cb[j];
+                    }
+                    put = win;
+                    if (__ballot(lng != 0u)) {
+                        // the rest of a longer row: pieces of V records; or, if its row does
+                        // not pack or the near queues are full, one entry with all of it
+#pragma unroll
+                        for (int j = 0; j < R; ++j) {
+                            const bool l = lng >> j & 1u;
+                            if (!__ballot(l)) continue;
+                            int first = (int)(ent[j].y >> kRowCountBits), deg = l ? (int)(ent[j].y & ((1u << kRowCountBits) - 1u)) : 0;
+                            if (l) row_of(ent[j], first, deg);
+                            const int row0 = l ? rptr[ent[j].x] : 0;
+                            for (int done = V; __ballot(done < deg) != 0ull; done += V) {
+                                const bool more = done < deg;
+                                const uint32_t rest = kNoRow + (uint32_t)(first + done - row0);
+                                uint4 e = make_uint4(ent[j].x, pack_row(first + done, min(V, deg - done)), ent[j].z,
+                                                     ent[j].w);
+                                if (e.y == kNoRow) e.y = rest;
+                                const unsigned long long bm = __ballot(more);
+                                int p, q;
+                                reserve(__popcll(bm), 0, p, q);
+                                const bool full = more && !put_near(p + lanes_set_below(bm), e);
+                                const unsigned long long bw = __ballot(full);
+                                if (bw) {
+                                    e.y = rest;
+                                    reserve(0, __popcll(bw), p, q);
+                                    if (full) put_far(q + lanes_set_below(bw), e);
+                                }
+                                if (more && (e.y & kNoRow)) deg = 0;   // all of it is queued
+                            }
+                        }
+                    }
+                    uint32_t lost = okm & ~win, hard = 0u;
+                    if (__ballot(lost != 0u)) {
+                        // a candidate that met another node's key in its slot has its record
+                        // queued again, as a row of one; where that does not pack, see below
+                        uint32_t other[R];
+#pragma unroll
+                        for (int j = 0; j < R; ++j) other[j] = s_cand[top[j] & kIdMask].x;
+#pragma unroll
+                        for (int j = 0; j < R; ++j) {
+                            const bool l = (lost >> j & 1u) && other[j] != r[j].x;
+                            int first = (int)(ent[j].y >> kRowCountBits), deg = 0;
+                            if (l) row_of(ent[j], first, deg);
+                            const uint32_t y = pack_row(first + lx, 1);
+                            const bool again = l && y != kNoRow;
+                            hard |= l && !again ? 1u << j : 0u;
+                            put |= again ? 1u << j : 0u;
+                            r[j].x = again ? ent[j].x : r[j].x;
+                            r[j].w = again ? y : r[j].w;
+                            cb[j] = again ? ent[j].z : cb[j];
+                            ent[j].x = again ? ent[j].w : ent[j].x;
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        const bool p = put >> j & 1u, nr = __uint_as_float(cb[j]) < thr;
+                        bn[j] = __ballot(p && nr);
+                        bf[j] = __ballot(p && !nr);
+                        cn += __popcll(bn[j]);
+                        cf += __popcll(bf[j]);
                     }
                     int p, q;
                     reserve(cn, cf, p, q);
-#pragma unroll
-                    for (int x = 0; x < V; ++x)
-                        if (win >> x & 1u) D[r[x].x] = cb[x];
                     if (p + cn <= NB - bc) {      // this wavefront's near entries all go to the buffer
 #pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            const bool w = (win >> x & 1u) && __uint_as_float(cb[x]) < thr;
-                            const int at = (bh + bc + p + lanes_set_below(bn[x])) & (NB - 1);
-                            s_buf[w ? at : NB + lane] = make_uint4(r[x].x, r[x].w, cb[x], ent.x);
-                            p += __popcll(bn[x]);
+                        for (int j = 0; j < R; ++j) {
+                            const bool w = (put >> j & 1u) && __uint_as_float(cb[j]) < thr;
+                            const int at = (bh + bc + p + lanes_set_below(bn[j])) & (NB - 1);
+                            s_buf[w ? at : NB + lane] = make_uint4(r[j].x, r[j].w, cb[j], ent[j].x);
+                            p += __popcll(bn[j]);
                         }
                     } else {
 #pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            const uint4 e = make_uint4(r[x].x, r[x].w, cb[x], ent.x);
+                        for (int j = 0; j < R; ++j) {
+                            const uint4 e = make_uint4(r[j].x, r[j].w, cb[j], ent[j].x);
                             bool full = false;
-                            if ((win >> x & 1u) && __uint_as_float(cb[x]) < thr)
-                                full = !put_near(p + lanes_set_below(bn[x]), e);
-                            p += __popcll(bn[x]);
+                            if ((put >> j & 1u) && __uint_as_float(cb[j]) < thr)
+                                full = !put_near(p + lanes_set_below(bn[j]), e);
+                            p += __popcll(bn[j]);
+                            if (full && !(win >> j & 1u)) {
+                                hard |= 1u << j;
+                                full = false;
+                            }
                             const unsigned long long bx = __ballot(full);
                             if (bx) {             // ring full
                                 int p1, q1;
@@ -1620,31 +1700,40 @@ __global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(W))) vo
                     }
                     if (cf) {
 #pragma unroll
-                        for (int x = 0; x < V; ++x) {
-                            if ((win >> x & 1u) && !(__uint_as_float(cb[x]) < thr))
-                                put_far(q + lanes_set_below(bf[x]), make_uint4(r[x].x, r[x].w, cb[x], ent.x));
-                            q += __popcll(bf[x]);
+                        for (int j = 0; j < R; ++j) {
+                            if ((put >> j & 1u) && !(__uint_as_float(cb[j]) < thr))
+                                put_far(q + lanes_set_below(bf[j]), make_uint4(r[j].x, r[j].w, cb[j], ent[j].x));
+                            q += __popcll(bf[j]);
                         }
                     }
-                }
-                // the rest of a longer row: pieces of V records; or, if its row does
-                // not pack or the near queues are full, one entry with all of it
-                for (int done = V; __ballot(done < deg) != 0ull; done += V) {
-                    const bool more = done < deg;
-                    const uint32_t rest = kNoRow + (uint32_t)(e0 + done - (more ? rptr[ent.x] : 0));
-                    uint4 e = make_uint4(ent.x, CT ? pack_row(e0 + done, min(V, deg - done)) : kNoRow, ent.z, ent.w);
-                    if (e.y == kNoRow) e.y = rest;
-                    const unsigned long long bm = __ballot(more);
-                    int p, q;
-                    reserve(__popcll(bm), 0, p, q);
-                    const bool full = more && !put_near(p + lanes_set_below(bm), e);
-                    const unsigned long long bw = __ballot(full);
-                    if (bw) {
-                        e.y = rest;
-                        reserve(0, __popcll(bw), p, q);
-                        if (full) put_far(q + lanes_set_below(bw), e);
+                    if (__ballot(hard != 0u)) {
+                        // no room for the record, or its row does not pack: no other node's
+                        // key won this slot, so only such candidates write the label now
+#pragma unroll
+                        for (int j = 0; j < R; ++j) {
+                            const bool h = hard >> j & 1u;
+                            const uint32_t id = (uint32_t)((j * NW + wv) * 64 + lane);
+                            const uint2 c = s_cand[id];
+                            bool low = false;
+                            if (h) low = c.y < atomicMin(&D[c.x], c.y);
+                            const uint4 e = make_uint4(c.x, CT && h ? crow[c.x] : kNoRow, c.y, kNoNode);
+                            const unsigned long long bl = __ballot(low);
+                            if (bl) {
+                                reserve(0, __popcll(bl), p, q);
+                                if (low) put_far(q + lanes_set_below(bl), e);
+                            }
+                        }
+                        __threadfence();          // labels changed by atomics are not read from the L1
                     }
-                    if (more && (e.y & kNoRow)) deg = 0;   // all of it is queued
+                };
+                if constexpr (V == 2) {
+                    if (rounds == 1) resolve(std::integral_constant<int, 1>{});
+                    else if (rounds) resolve(std::integral_constant<int, 2>{});
+                } else {
+                    if (rounds == 1) resolve(std::integral_constant<int, 1>{});
+                    else if (rounds == 2) resolve(std::integral_constant<int, 2>{});
+                    else if (rounds == 3) resolve(std::integral_constant<int, 3>{});
+                    else if (rounds) resolve(std::integral_constant<int, V>{});
                 }
                 __syncthreads();
                 fold();
@@ -2546,17 +2635,21 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
     int blocks = (slots + (kWG / 64) - 1) / (kWG / 64);
     if (variant >= 32 || (variant >= 8 && variant < 16)) {
         // node queue, one workgroup of 128 U threads per tree (scratch slot =
-        // workgroup), V records per thread and step.  256 threads and 4 records by
-        // default: a step's entries are 100 to 250 on road networks and grids, so
-        // 512 threads mostly wait at barriers and 128 take twice the steps, and
-        // two records leave most rows to a second step.  Metro network, 1,000
-        // trees, <2, 4> / <4, 4> / <1, 4> / <2, 2>: 2.4 / 2.8 / 2.7 / 3.3 ms;
-        // 22,801-node grid, 300 trees, congested: 0.80 / 1.36 / 1.20 / 1.55.
+        // workgroup), V lanes per entry.  256 threads and 4 lanes where no other
+        // shape is asked for: a step's entries are 100 to 250 on road networks and
+        // grids, so 128 threads take twice the steps, 512 keep half as many trees in
+        // flight, and two lanes leave most rows to a second step.  Metro network,
+        // 1,000 trees, <2, 4> / <4, 4> / <1, 4> / <2, 2>, ms: 2.4 / 2.8 / 2.7 / 3.3;
+        // 22,801-node grid, 300 trees, congested: 0.80 / 1.36 / 1.20 / 1.55 (with a
+        // thread per entry).  With a CU for every tree, 512 threads share out a
+        // step's rounds further (auto_shape).
         const bool ct = variant >= 32;
         if (ct && !net.cbuf) return hipErrorInvalidValue;
         static const int units[] = {1, 1, 2, 4, 2, 4};
         const int v = min(variant - (ct ? 32 : 8), 5), nt = 128 * units[v];
-        blocks = min((slots * 64 + nt - 1) / nt, min(scr.near_w, scr.far_w) / 4);
+        // where every tree can have a CU it has its own workgroup
+        blocks = max((slots * 64 + nt - 1) / nt, min(t_end - t_begin, 256));
+        blocks = min(blocks, min(scr.near_w, scr.far_w) / 4);
         if (blocks <= 0) return hipErrorInvalidValue;
 #define QDTA_SSSP_WG(...)                                                                                          \
     hipLaunchKernelGGL((k_sssp_wg<__VA_ARGS__>), dim3(blocks), dim3(nt), 0, s, net, dem, radj, labels, scr, st,     \

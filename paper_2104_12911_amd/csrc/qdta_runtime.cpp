@@ -402,7 +402,12 @@ bool uses_contraction(const qdta_opts* o) {
 // node-per-thread queue; 32-37: the node queue over the chain-contracted
 // search (shapes as 8-13).  The
 // block-local kernel needs every instance within its block bitmap.
-int sssp_variant(const qdta_ctx* c, const qdta_opts* o) {
+// The search's shape where the options leave it open: 512 threads a tree where
+// each tree can have a CU (100 trees of 100k nodes: 1.37 ms, 1.66 with 256; 40 of
+// 400 nodes: the same), 256 beyond (see launch_trees).
+int auto_shape(const qdta_ctx* c, int64_t trees) { return trees <= c->cus ? 4 : 3; }
+
+int sssp_variant(const qdta_ctx* c, const qdta_opts* o, int64_t trees = -1) {
     int64_t nmax = 0;
     for (const Instance& I : c->inst) nmax = std::max<int64_t>(nmax, I.n);
     const bool fits = nmax <= (int64_t)kBlkMaxBits * blk_nodes(o->sssp_shape);
@@ -414,7 +419,8 @@ int sssp_variant(const qdta_ctx* c, const qdta_opts* o) {
         const int v = (o->sssp_shape >= 1 && o->sssp_shape <= 4) ? o->sssp_shape - 1 : 1;
         return 24 + v;
     }
-    const int v = (o->sssp_shape >= 1 && o->sssp_shape <= 6) ? o->sssp_shape - 1 : 2;
+    const bool set = o->sssp_shape >= 1 && o->sssp_shape <= 6;
+    const int v = (set ? o->sssp_shape : tree_waves(o) == 1 ? 3 : auto_shape(c, trees < 0 ? c->Q : trees)) - 1;
     if (uses_contraction(o)) return 32 + v;
     return tree_waves(o) == 1 ? v : v + 8;
 }
@@ -1796,7 +1802,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         if ((e = launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p, c->logpart.p)))
             { rc = set_err(c, QDTA_EHIP, "scatter: %s", hipGetErrorString(e)); break; }
         if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab.p, scr_view(c), slots, nullptr,
-                             delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 0, true, nullptr, aq.p)))
+                             delta_scale(o), c->delta_inst.p, sssp_variant(c, o, nq), 0, true, nullptr, aq.p)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
         if ((e = launch_trees_out(c->stream, net, dem, lab.p, c->cost.p, inst, dist, succ, aq.p, c->h_flags + 2)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }

@@ -221,3 +221,37 @@ def test_stop_tests_at_split_edges(q, orc, m, stop_rule, ls_mode):
                 assert (st[i]["iters"], st[i]["stopped_by"]) == (ref.iters, ref.stopped_by)
                 assert st[i]["gap"] == ref.gap and st[i]["last_alpha"] == ref.last_alpha
                 at += net.m
+
+
+@pytest.mark.parametrize("hubs", [3, 12, 40])
+@pytest.mark.parametrize("kernel", [1, 4])
+def test_search_queues_fuller_than_the_network(q, orc, hubs, kernel):
+    """Every leaf is lowered by each hub in turn while its earlier entries wait, all in one bucket: the near queue
+    takes several times the node count, and its overflow goes to the far queue."""
+    import torch
+    leaves = 1000
+    n = 1 + hubs + leaves
+    tail, head, cost = [], [], []
+    for i in range(hubs):
+        tail.append(1 + i), head.append(0), cost.append(1.0 + i)
+        for v in range(1 + hubs, n):
+            tail.append(v), head.append(1 + i), cost.append(4.0 * (hubs - i))
+    for v in range(1 + hubs, n):
+        tail.append(0), head.append(v), cost.append(1.0)
+    tail, head, cost = np.array(tail), np.array(head), np.array(cost, np.float32)
+    order = np.lexsort((head, tail))
+    row = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(tail, minlength=n), out=row[1:])
+    net = Network(n, row, head[order].astype(np.int32), cost[order], np.full(tail.size, 900.0, np.float32))
+    ref = orc.tree(net, net.fftt, 0)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], float("inf"))
+        dist = torch.empty((1, n), dtype=torch.float32, device="cuda")
+        succ = torch.empty((1, n), dtype=torch.int32, device="cuda")
+        for shape in (0, 1, 2, 3, 4, 5, 6):
+            for scale in (0.05, 1e6):
+                o = q.default_opts(sssp_kernel=kernel, sssp_shape=shape, delta_scale=scale)
+                ctx.trees(o, 0, dev(net.fftt), dev(np.zeros(1, np.int32)), dist, succ)
+                assert np.array_equal(dist[0].cpu().numpy(), ref[0]), (shape, scale)
+                assert np.array_equal(succ[0].cpu().numpy(), ref[1]), (shape, scale)
