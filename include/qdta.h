@@ -139,8 +139,11 @@ typedef struct {
                               one: what the workspace has left), < 0 none (the residual step grows
                               every tree again); never changes results */
     int32_t objective;     /* QDTA_OBJ_UE (default) or QDTA_OBJ_SO */
-    int32_t sssp_kernel;   /* shortest-path kernel: 0 auto (4, or 1 when tree_waves = 1), 1 node queue
-                              (tree_waves and sssp_shape as above), 2 block-local (a block of node ids is
+    int32_t sssp_kernel;   /* shortest-path kernel: 0 auto (1 when tree_waves = 1; passes over labels kept in
+                              LDS, whatever the shape and bucket width, for networks of at most 2,048
+                              nodes, or 4,096 with no more trees than compute units, and at most 8 links
+                              out of a node; else 4), 1 node queue (tree_waves and sssp_shape as above),
+                              2 block-local (a block of node ids is
                               relaxed to closure in LDS per load; sssp_shape 1..4 = blocks of 128, 128
                               (two per wavefront per step), 64, 256 nodes; instances of at most 8,192
                               blocks, else the node queue), 3 node queue with each thread relaxing its own

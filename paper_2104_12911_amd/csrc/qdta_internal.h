@@ -13,6 +13,10 @@ constexpr int kMaxK = 64;                // step sizes per line-search pass
 // block-local shortest-path kernel: blocks per tree its LDS bitmap covers
 // (instances up to kBlkMaxBits * block-size nodes)
 constexpr int kBlkMaxBits = 8192;
+// launch_trees variants from here on: k_sssp_pull for instances of at most
+// 256 << (variant - kPullVariant) nodes
+constexpr int kPullVariant = 64;
+constexpr int kPullNodes = 4096;
 // chain-contracted search: most nodes one chain holds (longer runs of
 // two-neighbour nodes are cut by keeping a node); the two or three link costs
 // of such a chain fit its record

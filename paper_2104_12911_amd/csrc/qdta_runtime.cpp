@@ -23,7 +23,7 @@ using namespace qdta;
 namespace {
 
 struct Instance {
-    int32_t n = 0, m = 0;
+    int32_t n = 0, m = 0, row_max = 0;   // row_max: most links out of a node
     std::vector<int32_t> row_ptr, col;
     std::vector<float> fftt, cap;
     // merged demand of the current interval, sorted by (dest, orig)
@@ -73,7 +73,7 @@ struct qdta_ctx {
     int nblk = 0;
     std::vector<InstDev> h_inst;
     std::vector<int64_t> node_off, link_off, leg_off, dest_off;
-    DBuf<int32_t> row_ptr, col, rptr, rsrc, rlink, revpos, blk_inst, blk_start, inst_blk;
+    DBuf<int32_t> row_ptr, col, rptr, rsrc, rlink, revpos, blk_inst, blk_start;
     DBuf<float> c0, cap;
     DBuf<InstDev> d_inst;
 
@@ -123,13 +123,16 @@ struct qdta_ctx {
     DBuf<InstState> st;
     DBuf<long long> acc, ls_acc;
     DBuf<double> alphas;
-    DBuf<unsigned int> ls_ticket; // workgroups of an instance done with the current line-search pass (zero between)
+    // behind the accumulators in acc: workgroups of an instance done with a pass
+    // over its links (zero between passes), and where the flags of a call that
+    // does not read them go
+    unsigned int* ticket = nullptr;
+    int* sink = nullptr;
     // [0] overflow, [1] unreach, [2] absorption, [3..5] path-record faults: pinned
     // host words that kernels set and the host reads after a synchronisation,
     // before h_st
     int* h_flags = nullptr;
     bool flags_open = false;      // kernels that set flags may be in flight
-    DBuf<int> sink;               // where the flags of a call that does not read them go
     DBuf<int32_t> absorb_q, int_node;
     DBuf<float> int_tau;
     DBuf<float> hist_cost;
@@ -402,14 +405,41 @@ bool uses_contraction(const qdta_opts* o) {
 // node-per-thread queue; 32-37: the node queue over the chain-contracted
 // search (shapes as 8-13).  The
 // block-local kernel needs every instance within its block bitmap.
+int64_t largest(const qdta_ctx* c) {
+    int64_t nmax = 0;
+    for (const Instance& I : c->inst) nmax = std::max<int64_t>(nmax, I.n);
+    return nmax;
+}
+
+// Trees by passes over labels in LDS (k_sssp_pull), where no kernel is asked for:
+// up to 2,048 nodes (whole calls for 40 / 1,200 trees, us, against the queue of
+// kernel 4: 2,025-node grid 89 / 266 against 183 / 340, 2,000-node road network
+// 96 / 286 against 194 / 366), and up to 4,096 with a CU for every tree (4,096
+// nodes, 40 / 300 / 1,200 trees: 147 / 249 / 556 against 244 / 270 / 481).  Its
+// threads read rows longer than 4 again in each pass, one link after the other.
+bool pull_trees(const qdta_ctx* c, const qdta_opts* o, int64_t trees) {
+    if (o->sssp_kernel != 0 || o->tree_waves == 1) return false;
+    for (const Instance& I : c->inst)
+        if (I.row_max > 8) return false;
+    return largest(c) <= (trees <= c->cus ? kPullNodes : kPullNodes / 2);
+}
+
+bool uses_contraction(const qdta_ctx* c, const qdta_opts* o, int64_t trees) {
+    return uses_contraction(o) && !pull_trees(c, o, trees);
+}
+
 // The search's shape where the options leave it open: 512 threads a tree where
 // each tree can have a CU (100 trees of 100k nodes: 1.37 ms, 1.66 with 256; 40 of
 // 400 nodes: the same), 256 beyond (see launch_trees).
 int auto_shape(const qdta_ctx* c, int64_t trees) { return trees <= c->cus ? 4 : 3; }
 
-int sssp_variant(const qdta_ctx* c, const qdta_opts* o, int64_t trees = -1) {
-    int64_t nmax = 0;
-    for (const Instance& I : c->inst) nmax = std::max<int64_t>(nmax, I.n);
+int sssp_variant(const qdta_ctx* c, const qdta_opts* o, int64_t trees) {
+    const int64_t nmax = largest(c);
+    if (pull_trees(c, o, trees)) {
+        int v = 0;
+        while ((int64_t)256 << v < nmax) ++v;
+        return kPullVariant + v;
+    }
     const bool fits = nmax <= (int64_t)kBlkMaxBits * blk_nodes(o->sssp_shape);
     if (o->sssp_kernel == 2 && fits) {
         const int v = (o->sssp_shape >= 1 && o->sssp_shape <= 4) ? o->sssp_shape - 1 : 1;
@@ -420,14 +450,16 @@ int sssp_variant(const qdta_ctx* c, const qdta_opts* o, int64_t trees = -1) {
         return 24 + v;
     }
     const bool set = o->sssp_shape >= 1 && o->sssp_shape <= 6;
-    const int v = (set ? o->sssp_shape : tree_waves(o) == 1 ? 3 : auto_shape(c, trees < 0 ? c->Q : trees)) - 1;
-    if (uses_contraction(o)) return 32 + v;
+    const int v = (set ? o->sssp_shape : tree_waves(o) == 1 ? 3 : auto_shape(c, trees)) - 1;
+    if (uses_contraction(c, o, trees)) return 32 + v;
     return tree_waves(o) == 1 ? v : v + 8;
 }
 
 // ---------------------------------------------------------------------------
 // network layout: instances concatenated, reverse CSR, link chunks
 // ---------------------------------------------------------------------------
+size_t acc_words(int ni) { return (size_t)ni * kSumReps * 6 + (ni + 2) / 2; }   // with the tickets and the sink
+
 int ensure_network(qdta_ctx* c) {
     if (!c->net_dirty) return QDTA_OK;
     if (c->inst.empty()) return set_err(c, QDTA_ESTATE, "no network added");
@@ -494,8 +526,8 @@ int ensure_network(qdta_ctx* c) {
     RC(upload(c, c->rlink, rlink));
     RC(upload(c, c->revpos, revpos));
     RC(upload(c, c->blk_inst, bi));
+    bs.insert(bs.end(), ib.begin(), ib.end());   // each instance's first chunk, behind the chunks
     RC(upload(c, c->blk_start, bs));
-    RC(upload(c, c->inst_blk, ib));
     RC(dalloc(c, c->logpart, (size_t)c->nblk * kLogParts));
     RC(upload(c, c->d_inst, c->h_inst));
     RC(dalloc(c, c->f, c->M));
@@ -516,17 +548,18 @@ int ensure_network(qdta_ctx* c) {
     RC(dalloc(c, c->cfin, c->M));
     RC(dalloc(c, c->tcost, c->M));
     RC(dalloc(c, c->st, ni));
-    RC(dalloc(c, c->acc, (size_t)ni * kSumReps * 6));
-    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)ni * kSumReps * 6));
+    RC(dalloc(c, c->acc, acc_words(ni)));
+    HIPCHECK(c, launch_fill_i64(c->stream, reinterpret_cast<int64_t*>(c->acc.p), 0, (int64_t)acc_words(ni)));
+    c->ticket = reinterpret_cast<unsigned int*>(c->acc.p + (size_t)ni * kSumReps * 6);
+    c->sink = reinterpret_cast<int*>(c->ticket + ni);
     RC(dalloc(c, c->ls_acc, (size_t)ni * kMaxK * 6 * kLsReps));
     RC(dalloc(c, c->alphas, (size_t)ni * kMaxK));
-    RC(dalloc(c, c->ls_ticket, ni));
-    HIPCHECK(c, launch_fill_u32(c->stream, c->ls_ticket.p, 0u, ni));
-    RC(dalloc(c, c->sink, 1));
     RC(dalloc(c, c->done_fx, ni));
     if (c->h_st_n < ni) {
-        HIPCHECK(c, hipStreamSynchronize(c->stream));
-        if (c->h_flags) (void)hipHostFree(c->h_flags);
+        if (c->h_flags) {
+            HIPCHECK(c, hipStreamSynchronize(c->stream));
+            (void)hipHostFree(c->h_flags);
+        }
         c->h_flags = nullptr;
         c->h_st_n = 0;
         HIPCHECK(c, hipHostMalloc((void**)&c->h_flags, kFlagBytes + sizeof(InstState) * ni, hipHostMallocCoherent));
@@ -569,7 +602,7 @@ NetDev net_view(qdta_ctx* c, const qdta_opts* o = nullptr) {
     v.fill_chunks = ct ? c->c_fill_chunks : 0;
     v.blk_inst = c->blk_inst.p;
     v.blk_start = c->blk_start.p;
-    v.inst_blk = c->inst_blk.p;
+    v.inst_blk = c->blk_start.p + c->nblk;
     v.ninst = (int32_t)c->inst.size();
     v.nblk = c->nblk;
     v.N = c->N;
@@ -859,7 +892,7 @@ int ensure_contraction(qdta_ctx* c, const int32_t* roots, size_t nroots) {
 
 // before a search of the current demand's trees
 int ensure_contract(qdta_ctx* c, const qdta_opts* o) {
-    if (!uses_contraction(o)) return QDTA_OK;
+    if (!uses_contraction(c, o, c->Q)) return QDTA_OK;
     return ensure_contraction(c, c->h_dest_node.data(), c->h_dest_node.size());
 }
 
@@ -1132,14 +1165,14 @@ int aon_core(qdta_ctx* c, const qdta_opts* o, const float* cost, const float* ti
         for (int64_t t = 0; t < c->Q; ++t) {
             HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->work.p), 0u, 1));
             HIPCHECK(c, launch_trees(c->stream, net, dem, c->radj.p, c->labels.p, scr_view(c), 4, st, c->delta_inst.p,
-                                     sssp_variant(c, o), 1, (int)t, (int)t + 1, false));
+                                     sssp_variant(c, o, c->Q), 1, (int)t, (int)t + 1, false));
         }
     } else {
         HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, st,
-                                delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1, false, y, c->absorb_q.p));
+                                delta_scale(o), c->delta_inst.p, sssp_variant(c, o, c->Q), 1, false, y, c->absorb_q.p));
     }
     if (marks) RC(prof_mark(c, PH_SSSP, 1));
-    if (sssp_variant(c, o) >= 32) {   // the contracted search's left-out chain nodes, timed apart
+    if (uses_contraction(c, o, c->Q)) {   // the contracted search's left-out chain nodes, timed apart
         if (marks) RC(prof_mark(c, PH_FILL, 0));
         HIPCHECK(c, launch_chain_fill(c->stream, net, dem, c->labels.p, st, 0, (int)c->Q));
         if (marks) RC(prof_mark(c, PH_FILL, 1));
@@ -1189,7 +1222,7 @@ int line_search_core(qdta_ctx* c, const qdta_opts* o, const int64_t* f, const in
     int* err = c->h_flags;
     const bool plain = o->launch_form == 2;
     const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
-    LsRule rule{!plain, K, o->ls_mode == QDTA_LS_QN ? 1 : 0, o->passes, o->max_ls, o->T1, o->T2, o->dx, c->ls_ticket.p};
+    LsRule rule{!plain, K, o->ls_mode == QDTA_LS_QN ? 1 : 0, o->passes, o->max_ls, o->T1, o->T2, o->dx, c->ticket};
     if (begin)
         HIPCHECK(c, launch_ls_begin(c->stream, ni, c->st.p, c->alphas.p, K, o->ls_mode, o->dx, c->ls_acc.p, 0));
     if (o->ls_mode == QDTA_LS_MSA) return QDTA_OK;
@@ -1506,11 +1539,11 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     auto add = [&](size_t n, size_t sz) { b += align_up(std::max<size_t>(n, 1) * sz); };
     // network and Frank-Wolfe state
     add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4); add(N + 1, 4); add(M, 4); add(M, 4); add(M, 4);
-    add(nblk, 4); add(nblk, 4); add(ni, 4); add(nblk * kLogParts, 8); add(ni, sizeof(InstDev));
+    add(nblk, 4); add(nblk + ni, 4); add(nblk * kLogParts, 8); add(ni, sizeof(InstDev));
     add(M, 8); add(M, 8); add(M, 4); add(M, 8); add(M, 8); add(M, 4); add(M, 4); add(M, 4);
-    add(ni, sizeof(InstState)); add((size_t)ni * 6 * kSumReps, 8);
+    add(ni, sizeof(InstState)); add(acc_words(ni), 8);
     add((size_t)ni * kMaxK * 6 * kLsReps, 8); add((size_t)ni * kMaxK, 8);
-    add(ni, 4); add(4, 4); add(ni, 8);
+    add(ni, 8);
     // demand tables and shortest-path labels
     add(pq, 4); add(pq, 4); add(pq, 8); add(pq + 1, 4); add(pp, 4); add(pp, 8); add(pp, 4); add(pp, 4);
     add(labels, 4); add(pq, 4); add(pp, 4); add(pp, 4);
@@ -1582,14 +1615,16 @@ int qdta_add_network(qdta_ctx* c, int32_t n, int32_t m, const int32_t* row_ptr, 
     if (n <= 0 || m < 0 || !row_ptr || (m > 0 && (!col || !fftt || !cap)))
         return set_err(c, QDTA_EARG, "bad sizes or null arrays");
     if (row_ptr[0] != 0 || row_ptr[n] != m) return set_err(c, QDTA_ECSR, "row_ptr must start at 0 and end at m");
-    for (int32_t v = 0; v < n; ++v)
+    Instance I;
+    for (int32_t v = 0; v < n; ++v) {
         if (row_ptr[v + 1] < row_ptr[v]) return set_err(c, QDTA_ECSR, "row_ptr decreases at node %d", v);
+        I.row_max = std::max(I.row_max, row_ptr[v + 1] - row_ptr[v]);
+    }
     for (int32_t a = 0; a < m; ++a) {
         if (col[a] < 0 || col[a] >= n) return set_err(c, QDTA_ECSR, "col[%d] = %d out of range", a, col[a]);
         if (!(fftt[a] > 0.0f) || !std::isfinite(fftt[a])) return set_err(c, QDTA_EVAL, "fftt[%d] not > 0 and finite", a);
         if (!(cap[a] > 0.0f) || !std::isfinite(cap[a])) return set_err(c, QDTA_EVAL, "cap[%d] not > 0 and finite", a);
     }
-    Instance I;
     I.n = n;
     I.m = m;
     I.row_ptr.assign(row_ptr, row_ptr + n + 1);
@@ -1791,7 +1826,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         dem.dest_inst = ddi.p;
         dem.dest_lab = ddl.p;
         dem.Q = nq;
-        if (uses_contraction(o) && (rc = ensure_contraction(c, hd, (size_t)nq))) break;
+        if (uses_contraction(c, o, nq) && (rc = ensure_contraction(c, hd, (size_t)nq))) break;
         NetDev net = net_view(c);
         hipError_t e;
         if ((e = launch_tree_tables(c->stream, dest, nq, I.node0, inst, tree_words(I.n), ddn.p, ddi.p, ddl.p)))
@@ -1993,7 +2028,7 @@ int enqueue_iteration(qdta_ctx* c, const qdta_opts* o, bool marks) {
     RC(aon_core(c, o, c->cost.p, tc, c->y.p, nullptr, c->st.p, marks));
     if (marks) RC(prof_mark(c, PH_GAP, 0));
     const int K = o->ls_mode == QDTA_LS_QN ? 3 : o->K;
-    HIPCHECK(c, launch_gap(c->stream, net, c->cost.p, c->f.p, c->y.p, c->acc.p, c->st.p, err, c->ls_ticket.p,
+    HIPCHECK(c, launch_gap(c->stream, net, c->cost.p, c->f.p, c->y.p, c->acc.p, c->st.p, err, c->ticket,
                            GapRule{o->stop_rule, o->fixed_iters, cap_iter, K, o->ls_mode, o->tol, o->dx}, c->alphas.p,
                            c->ls_acc.p));
     if (marks) RC(prof_mark(c, PH_GAP, 1));
@@ -2001,7 +2036,7 @@ int enqueue_iteration(qdta_ctx* c, const qdta_opts* o, bool marks) {
     RC(line_search_core(c, o, c->f.p, c->y.p, nullptr, false));
     if (o->stop_rule == QDTA_STOP_OBJ && o->fixed_iters <= 0)
         HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 1, o->tol, err,
-                               c->ls_ticket.p));
+                               c->ticket));
     if (marks) RC(prof_mark(c, PH_LS, 1));
     if (marks) RC(prof_mark(c, PH_UPDATE, 0));
     HIPCHECK(c, launch_fw_update(c->stream, net, c->f.p, c->y.p, nullptr, c->st.p, o->fixed_iters));
@@ -2094,7 +2129,7 @@ int fw_finish(qdta_ctx* c, const qdta_opts* o, qdta_stats* hs) {
     RC(open_flags(c));
     // objective of the returned iterates
     HIPCHECK(c, launch_obj(c->stream, net, c->f.p, c->y.p, o->alpha, o->beta, c->acc.p, c->st.p, 0, o->tol, c->h_flags,
-                           c->ls_ticket.p));
+                           c->ticket));
     RC(pull_state(c));
     take_flags(c, h);
     int worst = flag_code(c, h);
@@ -2172,7 +2207,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     // -1, after an untimed launch that takes the first-touch costs; another
     // replaces it only when at least 5% faster (single trials vary by about
     // 2%), so near-ties do not flip the choice from run to run
-    const int start_shape = o->sssp_shape ? o->sssp_shape : 3, start_tw = o->tree_waves ? o->tree_waves : 4;
+    const int start_shape = o->sssp_shape ? o->sssp_shape : o->tree_waves == 1 ? 3 : auto_shape(c, c->Q), start_tw = o->tree_waves ? o->tree_waves : 4;
     const double start_scale = delta_scale(o);
     for (double sc : scales)
         if (sc != start_scale) trials.push_back({start_shape, sc, start_tw});
@@ -2198,7 +2233,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
         hipError_t e = hipEventRecord(e0, c->stream);
         if (e == hipSuccess)
             e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), ts, nullptr,
-                            delta_scale(&t), c->delta_inst.p, sssp_variant(c, &t), 1);
+                            delta_scale(&t), c->delta_inst.p, sssp_variant(c, &t, c->Q), 1);
         if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
@@ -2300,7 +2335,7 @@ int qdta_get_costs(qdta_ctx* c, const qdta_opts* o, float* cost) {
     if (!c || !cost) return QDTA_EARG;
     if (!opts_ok(c, o)) return QDTA_EARG;
     if (!c->solved && c->fw_j < 0) return set_err(c, QDTA_ESTATE, "no solved or running interval");
-    HIPCHECK(c, launch_bpr(c->stream, net_view(c), c->f.p, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->sink.p));
+    HIPCHECK(c, launch_bpr(c->stream, net_view(c), c->f.p, o->alpha, o->beta, cost, nullptr, nullptr, 0, c->sink));
     return QDTA_OK;
 }
 
@@ -2390,7 +2425,7 @@ int qdta_advance_interval(qdta_ctx* c, const qdta_opts* o) {
             lab = c->lab_hist.p + (size_t)j * c->label_count;    // the solve's own trees of iterate j
         } else {
             HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, stj,
-                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1));
+                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o, c->Q), 1));
         }
         HIPCHECK(c, launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->absorb_q.p), 0u, c->Q));
         HIPCHECK(c, launch_walk(c->stream, net, dem, lab, c->cfin.p, nullptr, nullptr, stj, fl, 1, lamj,
@@ -2549,7 +2584,7 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
             lab = c->lab_hist.p + (size_t)j * c->label_count;   // the solve's own trees of iterate j
         } else {
             HIPCHECK(c, launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, c->labels.p, scr_view(c), c->slots, nullptr,
-                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o), 1));
+                                    delta_scale(o), c->delta_inst.p, sssp_variant(c, o, c->Q), 1));
         }
         RC(clear_flags(c));
         HIPCHECK(c, launch_path_walk(c->stream, net, dem, lab, nullptr, nullptr, nullptr, c->adj_len.p,

@@ -255,3 +255,30 @@ def test_search_queues_fuller_than_the_network(q, orc, hubs, kernel):
                 ctx.trees(o, 0, dev(net.fftt), dev(np.zeros(1, np.int32)), dist, succ)
                 assert np.array_equal(dist[0].cpu().numpy(), ref[0]), (shape, scale)
                 assert np.array_equal(succ[0].cpu().numpy(), ref[1]), (shape, scale)
+
+
+@pytest.mark.parametrize("n", [1, 2, 33, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
+@pytest.mark.parametrize("row", [4, 8, 9])
+def test_trees_of_small_networks(q, orc, n, row):
+    """Around the sizes where the trees of a small network change form (256, 512, 1,024, 2,048 and 4,096 nodes, rows of
+    4 and of 8 links), with nodes that reach no destination and whole-number costs that tie."""
+    import torch
+    rng = np.random.default_rng(n * 16 + row)
+    deg = rng.integers(0, row + 1, n)
+    deg[rng.integers(0, n)] = row
+    ptr = np.zeros(n + 1, np.int32)
+    np.cumsum(deg, out=ptr[1:])
+    m = int(ptr[-1])
+    near = (np.repeat(np.arange(n), deg) + rng.integers(-40, 41, m)) % n
+    net = Network(n, ptr, near.astype(np.int32), rng.integers(1, 6, m).astype(np.float32), np.full(m, 900.0, np.float32))
+    dests = rng.integers(0, n, 300 if n in (2048, 2049) else 5).astype(np.int32)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], float("inf"))
+        dist = torch.empty((dests.size, n), dtype=torch.float32, device="cuda")
+        succ = torch.empty((dests.size, n), dtype=torch.int32, device="cuda")
+        ctx.trees(q.default_opts(), 0, dev(net.fftt), dev(dests), dist, succ)
+        for k in list(range(5)) + [dests.size - 1]:
+            ref = orc.tree(net, net.fftt, int(dests[k]))
+            assert np.array_equal(dist[k].cpu().numpy(), ref[0]), k
+            assert np.array_equal(succ[k].cpu().numpy(), ref[1]), k
