@@ -2914,6 +2914,37 @@ __device__ __forceinline__ int succ_row(const NetDev& net, const label_t* lab, i
     return -1;
 }
 
+// The same by four neighbouring lanes for one u: each takes every fourth link of
+// the row, and all return the lowest tight strict one.
+__device__ __forceinline__ int succ_quad(const NetDev& net, const label_t* lab, int node0, int u, uint32_t row,
+                                         float du, int& head, float& cost, uint32_t& head_row, float& head_lab) {
+    const int lane = threadIdx.x & 63, j = lane & 3, quad = lane & 60;
+    int e0, deg;
+    if (row != kNoRow) {
+        e0 = (int)(row >> kRowCountBits);
+        deg = (int)(row & ((1u << kRowCountBits) - 1u));
+    } else {
+        e0 = net.row_ptr[u];
+        deg = net.row_ptr[u + 1] - e0;
+    }
+    for (int b = 0; b < deg; b += 4) {
+        const int e = e0 + min(b + j, deg - 1);
+        const uint2 r = net.fadj[e];
+        const uint32_t fr = net.frow[e];
+        const float dw = lab_val(lab, (int)r.x - node0), c = __uint_as_float(r.y);
+        const unsigned m = (unsigned)(__ballot(b + j < deg && dw < du && dw + c == du) >> quad) & 15u;
+        if (m) {
+            const int w = __ffs(m) - 1;
+            head = __shfl((int)r.x, quad + w);
+            cost = __shfl(c, quad + w);
+            head_row = (uint32_t)__shfl((int)fr, quad + w);
+            head_lab = __shfl(dw, quad + w);
+            return e0 + b + w;
+        }
+    }
+    return -1;
+}
+
 struct WalkOut {
     int64_t* y;
     int32_t* stop;
@@ -2975,19 +3006,20 @@ __device__ __forceinline__ bool stop_at_node(int rule, float tau, float dt) {
 
 // time_cost: the costs that clock the truncation (Eq. 2); NULL = the trees'
 // own costs (the forward records), as in the AON of an iteration.
-// NT threads of a workgroup walk a contiguous run of NT * LPT legs, LPT each.
-// Loads of a workgroup's legs are summed per link in an LDS table first
-// (legs of one destination share links); the table is added to y when the
-// workgroup is done, and a load whose probes find no slot goes to y directly.
-// Integer sums: the order does not change them.  16 slots per thread (48 KB at
-// 256 threads, twelve wavefronts per CU): half as many hold too few of the
-// distinct links (1,191 against 823 us at 316k legs), and twice as many leave
+// Q lanes walk a leg (1: succ_row, 4: succ_quad), the NT threads of a workgroup a
+// contiguous run of NT / Q * LPT legs.  Loads of a workgroup's legs are summed per
+// link in an LDS table first (legs of one destination share links); the table is
+// added to y when the workgroup is done, and a load whose probes find no slot goes
+// to y directly.  Integer sums: the order does not change them.  16 slots per
+// walker (48 KB at 256, twelve wavefronts per CU): half as many hold too few of
+// the distinct links (1,191 against 823 us at 316k legs), and twice as many leave
 // half the wavefronts.
-template <int NT, int LPT>
+template <int NT, int LPT, int Q>
 __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label_t* __restrict__ labels,
                                               const float* __restrict__ time_cost, const InstState* st,
                                               FlagsDev fl, WalkOut o, int l_begin, int l_end) {
-    constexpr int SLOTS = 16 * NT;
+    constexpr int SLOTS = 16 * NT / Q;
+    const bool lead = Q == 1 || threadIdx.x % Q == 0;
     __shared__ int s_key[SLOTS];
     __shared__ unsigned long long s_sum[SLOTS];
     // completed weight of the first leg's instance (residual mode): one global
@@ -3018,10 +3050,10 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
         }
         atomicAdd(reinterpret_cast<unsigned long long*>(&o.y[e]), (unsigned long long)d);
     };
-    const int base = l_begin + blockIdx.x * NT * LPT;
-    const int lim = min(l_end, base + NT * LPT);
+    const int base = l_begin + blockIdx.x * (NT / Q) * LPT;
+    const int lim = min(l_end, base + (NT / Q) * LPT);
     const int inst0 = dem.dest_inst[dem.leg_q[base]];
-    for (int l = base + threadIdx.x; l < lim; l += NT) {
+    for (int l = base + (int)threadIdx.x / Q; l < lim; l += NT / Q) {
         const int qi = dem.leg_q[l];
         const int inst = dem.dest_inst[qi];
         if (!inst_live(st, inst)) continue;
@@ -3032,10 +3064,10 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
         const int64_t d = dem.leg_dfx[l];
         int u = dem.leg_orig[l];
         float du = lab_val(lab, u - node0);
-        fl.int_node[l] = -1;
+        if (lead) fl.int_node[l] = -1;
         if (!(du <= 3.4028234663852886e38f)) {       // origin cannot reach q
             *fl.err_unreach = 1;
-            if (o.stop) o.stop[l] = -1;
+            if (lead && o.stop) o.stop[l] = -1;
             continue;
         }
         float tau = dem.leg_delay ? dem.leg_delay[l] : 0.0f;
@@ -3050,10 +3082,13 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
                 int head = 0;
                 float ce = 0.0f, hlab = 0.0f;
                 uint32_t hrow = kNoRow;
-                const int e = succ_row(net, lab, node0, u, urow, du, head, ce, hrow, hlab);
+                const int e = Q == 4 ? succ_quad(net, lab, node0, u, urow, du, head, ce, hrow, hlab)
+                                     : succ_row(net, lab, node0, u, urow, du, head, ce, hrow, hlab);
                 if (e < 0 || hops > I.n) {            // absorption: finish in the fallback
-                    fl.int_node[l] = u;
-                    fl.int_tau[l] = tau;
+                    if (lead) {
+                        fl.int_node[l] = u;
+                        fl.int_tau[l] = tau;
+                    }
                     fl.absorb_q[qi] = 1;
                     s_absorbed = 1;
                     absorbed = true;
@@ -3061,7 +3096,7 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
                 }
                 const float nt = tau + (time_cost ? time_cost[e] : ce);
                 if (I.rule == RULE_FLOOR && nt > I.dt32) break;
-                if (loads) load(e, d);
+                if (loads && lead) load(e, d);
                 tau = nt;
                 u = head;
                 urow = hrow;
@@ -3072,7 +3107,7 @@ __global__ __launch_bounds__(NT) void k_walk(NetDev net, DemDev dem, const label
                 }
             }
         }
-        if (!absorbed) {
+        if (lead && !absorbed) {
             const int64_t wd = finish_leg(o, l, u, q, qi, dem.dest_lab[qi], inst, node0, d, delay);
             if (wd && inst == inst0) atomicAdd(&s_done, (unsigned long long)wd);
             else if (wd) atomicAdd(&o.done_fx[inst], (unsigned long long)wd);
@@ -3097,18 +3132,21 @@ hipError_t launch_walk(hipStream_t s, const NetDev& net, const DemDev& dem, cons
     if (l_end <= l_begin) return hipSuccess;
     WalkOut o{y, stop, stop_delay, residual_mode, lambda, r_dense, done_fx,
               tr ? *tr : TransitOut{nullptr, nullptr, nullptr, nullptr, nullptr, 0u}, fl.err_overflow};
-    // Fewer legs than threads in flight (12 wavefronts per CU with this table,
-    // 196,608 threads): one leg per thread, since a thread's legs run one after
-    // another and a hop is two dependent loads, and 128-thread workgroups, which
-    // spread better.  More legs: two per thread, whose loads share the table.
-    // Phase times at 1 / 2 / 4 legs per thread, us: 1,560 legs 45 / 73 / 116;
-    // 73k legs of 250 trees 250 / 438 / 858; 90k legs of 300 static trees 506 /
-    // 833 / 1,560; 316k legs 823 / 704 / 1,084; 1.2M legs 3,688 / 3,655 / 4,507.
-#define QDTA_WALK(NT, LPT)                                                                                         \
-    hipLaunchKernelGGL((k_walk<NT, LPT>), dim3((unsigned)((l_end - l_begin + NT * LPT - 1) / (NT * LPT))), dim3(NT), \
-                       0, s, net, dem, labels, time_cost, st, fl, o, l_begin, l_end)
-    if (l_end - l_begin < 200000) QDTA_WALK(128, 1);
-    else QDTA_WALK(256, 2);
+    // Fewer legs than fit on the chip (196,608 with this table): one leg at a time
+    // per walker, since a walker's legs run one after another and a hop is two
+    // dependent loads, and four lanes a leg, which load a row's links together
+    // (one line instead of one a link).  More legs: two per thread, whose loads
+    // share the table; there four lanes a leg only put fewer legs in flight.
+    // Phase times at one leg per thread / two / one per four lanes, us: 1,560 legs
+    // 38 / 73 / 33; 73k legs of 250 trees 227 / 438 / 194; 90k legs of 300 static
+    // trees 471 / 833 / 447; 316k legs 823 / 686 / 854; 1.2M legs 3,688 / 3,766 /
+    // 4,090.
+#define QDTA_WALK(NT, LPT, Q)                                                                                      \
+    hipLaunchKernelGGL((k_walk<NT, LPT, Q>),                                                                       \
+                       dim3((unsigned)((l_end - l_begin + NT / Q * LPT - 1) / (NT / Q * LPT))), dim3(NT), 0, s,    \
+                       net, dem, labels, time_cost, st, fl, o, l_begin, l_end)
+    if (l_end - l_begin < 200000) QDTA_WALK(512, 1, 4);
+    else QDTA_WALK(256, 2, 1);
 #undef QDTA_WALK
     return hipGetLastError();
 }

@@ -282,3 +282,26 @@ def test_trees_of_small_networks(q, orc, n, row):
             ref = orc.tree(net, net.fftt, int(dests[k]))
             assert np.array_equal(dist[k].cpu().numpy(), ref[0]), k
             assert np.array_equal(succ[k].cpu().numpy(), ref[1]), k
+
+
+@pytest.mark.parametrize("leaves", [3, 4, 5, 62, 63, 64, 257])
+def test_walk_through_long_rows(q, orc, leaves):
+    """Legs through a hub whose row is one to many turns of four lanes, or does not pack, with ties on the way."""
+    import torch
+    rng = np.random.default_rng(leaves)
+    net = hub_net(rng, leaves, 40)
+    pair = rng.choice(net.n * net.n, min(700, net.n * net.n), replace=False)
+    o, d = (pair // net.n).astype(np.int32), (pair % net.n).astype(np.int32)
+    o, d = o[o != d], d[o != d]
+    trips = rng.uniform(0.1, 5.0, o.size)
+    legs = orc.demand_legs(o, d, trips)
+    for dt, rule in ((float("inf"), 0), (10.0, 1)):
+        ref_y, ref_stop = orc.aon(net, net.fftt, *legs, dt, rule=rule)[:2]
+        with q.Context() as ctx:
+            ctx.add(net)
+            ctx.set_demand(0, o, d, trips, dt)
+            y = torch.empty(net.m, dtype=torch.int64, device="cuda")
+            stop = torch.empty(o.size, dtype=torch.int32, device="cuda")
+            ctx.aon(q.default_opts(trunc_rule=rule), dev(net.fftt), y, stop)
+            assert np.array_equal(y.cpu().numpy(), ref_y)
+            assert np.array_equal(stop.cpu().numpy(), ref_stop)
