@@ -3560,27 +3560,55 @@ hipError_t launch_path_walk(hipStream_t s, const NetDev& net, const DemDev& dem,
 // y += rint(d 2^20) along every leg's path: the loading of Eq. 5 for a
 // real-valued demand, exact in int64 whatever the order of the atomics.
 // One lane per (leg, link) entry of the flattened paths, so the link ids
-// and leg indices are read coalesced and long paths spread over lanes.
-__global__ __launch_bounds__(kWG) void k_path_load(int64_t total, const int32_t* __restrict__ links,
+// and leg indices are read coalesced and long paths spread over lanes.  A
+// workgroup takes a run of kPathRun entries and sums it per link in LDS first, as
+// k_walk does: the legs of a destination are neighbours and share many of their
+// links, and an atomic on y is carried out beyond the L2 (27,400 legs of 300
+// destinations on 100k nodes: 67 us, 114 with an atomic on y per entry; 69 to 76
+// with smaller workgroups, 80 with runs of 1,024).
+constexpr int kPathRun = 4096, kPathWG = 1024;
+
+__global__ __launch_bounds__(kPathWG) void k_path_load(int64_t total, const int32_t* __restrict__ links,
                                                    const int32_t* __restrict__ leg_of, const double* __restrict__ d,
                                                    int64_t* y, int* err) {
-    for (int64_t i = blockIdx.x * (int64_t)kWG + threadIdx.x; i < total; i += (int64_t)gridDim.x * kWG) {
+    constexpr int SLOTS = kPathRun;
+    __shared__ int s_key[SLOTS];
+    __shared__ unsigned long long s_sum[SLOTS];
+    for (int x = threadIdx.x; x < SLOTS; x += kPathWG) {
+        s_key[x] = -1;
+        s_sum[x] = 0ull;
+    }
+    __syncthreads();
+    const int64_t i0 = blockIdx.x * (int64_t)kPathRun, i1 = min(total, i0 + kPathRun);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kPathWG) {
+        const int e = links[i];
         const double x = d[leg_of[i]] * 1048576.0;
         if (!(x > -9.0e18 && x < 9.0e18)) {
             *err = 1;
             continue;
         }
         const int64_t w = (int64_t)__builtin_rint(x);
-        if (w != 0) atomicAdd(reinterpret_cast<unsigned long long*>(&y[links[i]]), (unsigned long long)w);
+        if (w == 0) continue;
+        int h = (int)(((unsigned)e * 2654435761u) >> 16) & (SLOTS - 1);
+        bool in = false;
+        for (int probe = 0; probe < 4 && !in; ++probe) {
+            const int k = atomicCAS(&s_key[h], -1, e);
+            in = k == -1 || k == e;
+            if (!in) h = (h + 1) & (SLOTS - 1);
+        }
+        if (in) atomicAdd(&s_sum[h], (unsigned long long)w);
+        else atomicAdd(reinterpret_cast<unsigned long long*>(&y[e]), (unsigned long long)w);
     }
+    __syncthreads();
+    for (int x = threadIdx.x; x < SLOTS; x += kPathWG)
+        if (s_sum[x]) atomicAdd(reinterpret_cast<unsigned long long*>(&y[s_key[x]]), s_sum[x]);
 }
 
 hipError_t launch_path_load(hipStream_t s, int64_t total, const int32_t* links, const int32_t* leg_of,
                             const double* d, int64_t* y, int* err) {
     if (total == 0) return hipSuccess;
-    const int64_t b = (total + kWG - 1) / kWG;
-    hipLaunchKernelGGL(k_path_load, dim3((unsigned)(b < 8192 ? b : 8192)), dim3(kWG), 0, s, total, links, leg_of, d,
-                       y, err);
+    hipLaunchKernelGGL(k_path_load, dim3((unsigned)((total + kPathRun - 1) / kPathRun)), dim3(kPathWG), 0, s, total, links,
+                       leg_of, d, y, err);
     return hipGetLastError();
 }
 

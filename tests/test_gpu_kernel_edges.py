@@ -305,3 +305,32 @@ def test_walk_through_long_rows(q, orc, leaves):
             ctx.aon(q.default_opts(trunc_rule=rule), dev(net.fftt), y, stop)
             assert np.array_equal(y.cpu().numpy(), ref_y)
             assert np.array_equal(stop.cpu().numpy(), ref_stop)
+
+
+@pytest.mark.parametrize("legs", [1, 90, 1500])
+def test_path_loading_runs(q, orc, legs):
+    """Recorded paths of less than one run of the loading (4,096 links), of about one and of many, with legs of no
+    demand: the replayed flows are the oracle's, bit for bit."""
+    import torch
+    import synth
+    from oracle import adjoint as adj
+    rng = np.random.default_rng(legs)
+    net = synth.grid_network(40, rng)
+    pair = rng.choice(net.n * net.n, 2 * legs + 8, replace=False)
+    o, d = (pair // net.n).astype(np.int32), (pair % net.n).astype(np.int32)
+    keep = np.nonzero(o != d)[0][:legs]
+    o, d, trips = o[keep], d[keep], rng.uniform(0.1, 5.0, legs)
+    lo, ld, lw = orc.demand_legs(o, d, trips)
+    res = orc.fw_solve(net, lo, ld, lw, dt_s=float("inf"), fixed_iters=2, keep_history=True)
+    paths = adj.frozen_paths(net, lo, ld, lw, res.hist_cost, float("inf"))
+    demand = rng.uniform(0.0, 9.0, legs) * (rng.random(legs) < 0.8)
+    ref = adj.forward_contract(paths, net.m, demand, net.fftt, net.cap, 0.15, 4, float("inf"))[0]
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, o, d, trips, float("inf"))
+        opts = q.default_opts(fixed_iters=2, keep_history=1)
+        ctx.solve(opts)
+        ctx.adjoint_record(opts)
+        f = torch.empty(net.m, dtype=torch.float64, device="cuda")
+        ctx.model_forward(opts, dev(demand), None, f)
+        assert np.array_equal(f.cpu().numpy() * FX, ref.astype(np.float64))
