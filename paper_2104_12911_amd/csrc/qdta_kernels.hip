@@ -5,6 +5,7 @@
 //   k_sssp_wg    destination-rooted FP32 shortest-path trees, delta-stepping
 //   k_sssp_ds    (Get_shortest_path of Alg. 3 / Alg. 7), one workgroup or one
 //                wavefront per tree
+//   k_sssp_pull  the same trees on small networks, by passes over labels in LDS
 //   k_walk       route truncation (Eq. 2) and loading along the successor
 //                links (Eq. 5, Alg. 3), int64 fixed-point atomics
 //   k_gap        exact sums for the relative gap, stop test

@@ -162,9 +162,7 @@ struct qdta_ctx {
     // qdta_trees: its destinations on the host (pinned) and its tables and labels
     int32_t* h_dest = nullptr;
     int h_dest_n = 0;
-    DBuf<int32_t> t_node, t_inst, t_absorb;
-    DBuf<int64_t> t_lab;
-    DBuf<label_t> t_labels;
+    DBuf<char> t_buf;
     bool solved = false;
     int fw_j = -1;                // FW iteration of the running solve (-1: none)
     bool fw_live = false;
@@ -399,12 +397,6 @@ bool uses_contraction(const qdta_opts* o) {
     return o->sssp_kernel == 4 || (o->sssp_kernel == 0 && o->tree_waves != 1);
 }
 
-// Shortest-path kernel variant (see qdta_opts.sssp_kernel / sssp_shape).
-// Variants 0-5: node queue, one wavefront per tree; 8-13: node queue, one
-// workgroup per tree; 16-19: block-local, one workgroup per tree; 24-27:
-// node-per-thread queue; 32-37: the node queue over the chain-contracted
-// search (shapes as 8-13).  The
-// block-local kernel needs every instance within its block bitmap.
 int64_t largest(const qdta_ctx* c) {
     int64_t nmax = 0;
     for (const Instance& I : c->inst) nmax = std::max<int64_t>(nmax, I.n);
@@ -433,6 +425,12 @@ bool uses_contraction(const qdta_ctx* c, const qdta_opts* o, int64_t trees) {
 // 400 nodes: the same), 256 beyond (see launch_trees).
 int auto_shape(const qdta_ctx* c, int64_t trees) { return trees <= c->cus ? 4 : 3; }
 
+// Shortest-path kernel variant (see qdta_opts.sssp_kernel / sssp_shape).
+// Variants 0-5: node queue, one wavefront per tree; 8-13: node queue, one
+// workgroup per tree; 16-19: block-local, one workgroup per tree; 24-27:
+// node-per-thread queue; 32-37: the node queue over the chain-contracted
+// search (shapes as 8-13); kPullVariant on: passes over labels in LDS.  The
+// block-local kernel needs every instance within its block bitmap.
 int sssp_variant(const qdta_ctx* c, const qdta_opts* o, int64_t trees) {
     const int64_t nmax = largest(c);
     if (pull_trees(c, o, trees)) {
@@ -1797,53 +1795,48 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
     // tables and labels are kept for the next call (40 trees of 400 nodes: 132 us a
     // call, 185 with the five buffers allocated, filled from the host and freed by
     // each); large ones, and those carved from a workspace, are given back.
-    DBuf<int32_t>&ddn = c->t_node, &ddi = c->t_inst, &aq = c->t_absorb;
-    DBuf<int64_t>& ddl = c->t_lab;
-    DBuf<label_t>& lab = c->t_labels;
+    const size_t words = (size_t)nq * tree_words(I.n);
     auto cleanup = [&]() {
-        if (!c->ws_base && lab.n * sizeof(label_t) <= kKeepTreeBytes) return;
-        dfree(c, ddn);
-        dfree(c, ddi);
-        dfree(c, aq);
-        dfree(c, ddl);
-        dfree(c, lab);
+        if (c->ws_base || c->t_buf.n > kKeepTreeBytes) dfree(c, c->t_buf);
     };
     RC(clear_flags(c));
     int rc = QDTA_OK;
     do {
-        if ((rc = dalloc(c, ddn, (size_t)nq))) break;
-        if ((rc = dalloc(c, ddi, (size_t)nq))) break;
-        if ((rc = dalloc(c, ddl, (size_t)nq))) break;
-        if ((rc = dalloc(c, lab, (size_t)nq * tree_words(I.n)))) break;
-        if ((rc = dalloc(c, aq, (size_t)nq))) break;
+        // labels (whole runs of 128 bytes), then per tree its label offset, its
+        // destination, its instance and its absorption flag
+        if ((rc = dalloc(c, c->t_buf, words * sizeof(label_t) + (size_t)nq * (sizeof(int64_t) + 3 * sizeof(int32_t))))) break;
+        label_t* lab = reinterpret_cast<label_t*>(c->t_buf.p);
+        int64_t* ddl = reinterpret_cast<int64_t*>(lab + words);
+        int32_t* ddn = reinterpret_cast<int32_t*>(ddl + nq);
+        int32_t *ddi = ddn + nq, *aq = ddi + nq;
         int saved_slots = c->slots;
         if ((rc = ensure_scratch(c, nq, std::max<int64_t>(c->nmax, I.n), waves_per_cu(o), tree_waves(o)))) break;
         int slots = c->slots;
         c->slots = saved_slots;
         DemDev dem;
         memset(&dem, 0, sizeof(dem));
-        dem.dest_node = ddn.p;
-        dem.dest_inst = ddi.p;
-        dem.dest_lab = ddl.p;
+        dem.dest_node = ddn;
+        dem.dest_inst = ddi;
+        dem.dest_lab = ddl;
         dem.Q = nq;
         if (uses_contraction(c, o, nq) && (rc = ensure_contraction(c, hd, (size_t)nq))) break;
         NetDev net = net_view(c);
         hipError_t e;
-        if ((e = launch_tree_tables(c->stream, dest, nq, I.node0, inst, tree_words(I.n), ddn.p, ddi.p, ddl.p)))
+        if ((e = launch_tree_tables(c->stream, dest, nq, I.node0, inst, tree_words(I.n), ddn, ddi, ddl)))
             { rc = set_err(c, QDTA_EHIP, "tree tables: %s", hipGetErrorString(e)); break; }
         // place the instance's costs in the global link order
         if ((e = hipMemcpyAsync(c->cost.p + I.link0, cost, sizeof(float) * I.m, hipMemcpyDeviceToDevice, c->stream)))
             { rc = set_err(c, QDTA_EHIP, "copy cost: %s", hipGetErrorString(e)); break; }
         if ((e = launch_scatter_rcost(c->stream, net, c->cost.p, c->radj.p, c->logpart.p)))
             { rc = set_err(c, QDTA_EHIP, "scatter: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab.p, scr_view(c), slots, nullptr,
-                             delta_scale(o), c->delta_inst.p, sssp_variant(c, o, nq), 0, true, nullptr, aq.p)))
+        if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab, scr_view(c), slots, nullptr,
+                             delta_scale(o), c->delta_inst.p, sssp_variant(c, o, nq), 0, true, nullptr, aq)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_trees_out(c->stream, net, dem, lab.p, c->cost.p, inst, dist, succ, aq.p, c->h_flags + 2)))
+        if ((e = launch_trees_out(c->stream, net, dem, lab, c->cost.p, inst, dist, succ, aq, c->h_flags + 2)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }
         FlagsDev fl = flags_view(c);
-        fl.absorb_q = aq.p;
-        if ((e = launch_fallback(c->stream, net, dem, lab.p, c->cost.p, c->cost.p, nullptr, nullptr, nullptr, fl,
+        fl.absorb_q = aq;
+        if ((e = launch_fallback(c->stream, net, dem, lab, c->cost.p, c->cost.p, nullptr, nullptr, nullptr, fl,
                                  scr_view(c), fallback_slots(c, nq), 0, nullptr, nullptr, nullptr,
                                  1, succ, I.n)))
             { rc = set_err(c, QDTA_EHIP, "fallback: %s", hipGetErrorString(e)); break; }
