@@ -292,9 +292,8 @@ hipError_t launch_resid_count(hipStream_t s, const NetDev& net, const DemDev& de
 hipError_t launch_resid_write(hipStream_t s, const NetDev& net, const DemDev& dem, int64_t* r_dense,
                               const int64_t* off, int32_t* r_orig, int32_t* r_q, int64_t* r_w);
 
-hipError_t launch_trees_out(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels,
-                            const float* cost_local, int32_t inst, float* dist, int32_t* succ,
-                            int32_t* absorb_q, int* absorb_any);
+hipError_t launch_trees_out(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels, int n,
+                            int32_t inst, float* dist, int32_t* succ, int32_t* absorb_q, int* absorb_any);
 
 // frozen-path model and its reverse pass (OD calibration)
 hipError_t launch_path_walk(hipStream_t s, const NetDev& net, const DemDev& dem, const label_t* labels,

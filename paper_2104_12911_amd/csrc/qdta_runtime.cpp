@@ -1832,7 +1832,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab, scr_view(c), slots, nullptr,
                              delta_scale(o), c->delta_inst.p, sssp_variant(c, o, nq), 0, true, nullptr, aq)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_trees_out(c->stream, net, dem, lab, c->cost.p, inst, dist, succ, aq, c->h_flags + 2)))
+        if ((e = launch_trees_out(c->stream, net, dem, lab, I.n, inst, dist, succ, aq, c->h_flags + 2)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }
         FlagsDev fl = flags_view(c);
         fl.absorb_q = aq;
