@@ -25,10 +25,14 @@ constexpr int kFillChunk = 1024;         // chains per work item of the fill aft
 // A node's row of records packed in one word, (first record << 6) | count,
 // carried by the records that name the node as their source and by its queue
 // entries so that a pop need not read the row pointers; kNoRow when the row
-// does not fit (64 records or more, or a first record at 2^25 or beyond).
+// does not fit (64 records or more, or a first record at 2^25 or beyond).  An
+// empty row is 0: the search reads the record a row starts at before it knows
+// the count, and where no later node has a record the position of an empty row
+// is one past the last.
 constexpr uint32_t kNoRow = 0x80000000u;
 constexpr int kRowCountBits = 6;
 __host__ __device__ inline uint32_t pack_row(int64_t e0, int64_t count) {
+    if (count == 0) return 0u;
     return (count < (1 << kRowCountBits) && e0 < ((int64_t)1 << (31 - kRowCountBits)))
                ? (uint32_t)(e0 << kRowCountBits) | (uint32_t)count
                : kNoRow;

@@ -334,3 +334,30 @@ def test_path_loading_runs(q, orc, legs):
         f = torch.empty(net.m, dtype=torch.float64, device="cuda")
         ctx.model_forward(opts, dev(demand), None, f)
         assert np.array_equal(f.cpu().numpy() * FX, ref.astype(np.float64))
+
+
+@pytest.mark.parametrize("kernel", [1, 4])
+def test_search_from_a_last_node_without_in_links(q, orc, kernel):
+    """No chains, and the highest-numbered node has out-links only, so its record row is empty and no record lies
+    behind it (32 records: the buffer holds nothing else).  Every tree reaches that node."""
+    import torch
+    n, pairs = 6, [(a, b) for a in range(5) for b in range(5) if a != b]
+    pairs += [(5, b) for b in (0, 0, 0, 1, 1, 1, 2, 2, 2, 3, 3, 4)]
+    tail, head = np.array(pairs).T
+    ptr = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(tail, minlength=n), out=ptr[1:])
+    assert tail.size == 32 and not (head == 5).any()
+    cost = np.random.default_rng(3).integers(1, 6, 32).astype(np.float32)
+    net = Network(n, ptr, head.astype(np.int32), cost, np.full(32, 900.0, np.float32))
+    dests = np.arange(n, dtype=np.int32)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], float("inf"))
+        dist = torch.empty((n, n), dtype=torch.float32, device="cuda")
+        succ = torch.empty((n, n), dtype=torch.int32, device="cuda")
+        for shape in (0, 1, 2, 3, 4, 5, 6):
+            ctx.trees(q.default_opts(sssp_kernel=kernel, sssp_shape=shape), 0, dev(cost), dev(dests), dist, succ)
+            for t in range(n):
+                ref = orc.tree(net, cost, t)
+                assert np.array_equal(dist[t].cpu().numpy(), ref[0]), (shape, t)
+                assert np.array_equal(succ[t].cpu().numpy(), ref[1]), (shape, t)
