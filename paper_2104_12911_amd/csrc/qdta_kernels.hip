@@ -334,14 +334,16 @@ __device__ __forceinline__ void ks_alphas(double lo, double hi, int K, int lane,
     if (lane < K) out[lane] = lo + ((hi - lo) * (double)lane) / (double)(K - 1);
 }
 
-// Start the line search of iteration S.iter of one instance: one wavefront,
-// every lane with the same arguments.
-__device__ void ls_begin_wave(InstState& S, double* al, long long* acc, int K, int ls_mode, double dx, int lane) {
+// Start the line search of iteration j of one instance: one wavefront, every
+// lane with the same arguments (j too: S.iter is written by one lane of the same
+// kernel in k_gap, so the others must not read it there).
+__device__ void ls_begin_wave(InstState& S, int j, double* al, long long* acc, int K, int ls_mode, double dx,
+                              int lane) {
     for (int k = lane; k < K * 6 * kLsReps; k += 64) acc[k] = 0;
     if (ls_mode == 2) {                  // MSA
-        if (lane == 0) S.alpha = 1.0 / ((double)S.iter + 1.0);
+        if (lane == 0) S.alpha = 1.0 / ((double)j + 1.0);
     } else if (ls_mode == 1) {           // quasi-Newton, Alg. 8 initial guess
-        const double a = 2.0 / (2.0 + (double)S.iter);
+        const double a = 2.0 / (2.0 + (double)j);
         if (lane == 0) S.qn_alpha = a;
         if (lane < 3) al[lane] = lane == 0 ? a - dx : lane == 1 ? a : a + dx;
     } else {                              // K-section on [0, 1]
@@ -389,25 +391,27 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
     InstState& S = st[inst];
-    int go = 0;
+    int next = 0;                            // the iteration whose line search starts (0: none)
     i128 scf, scy;
     take_sums(sums, (int)threadIdx.x, scf, scy);
     if (threadIdx.x == 0) {
-        S.iter += 1;
+        const int j = S.iter + 1;
+        S.iter = j;
         S.gap = (double)(scf - scy) / (double)scf;
         if (G.fixed_iters <= 0 && G.stop_rule == 0 && __builtin_fabs(S.gap) < G.tol) {
             S.converged = 1;
             S.stopped_by = 1;
-        } else if (S.iter > G.cap_iter) {
+        } else if (j > G.cap_iter) {
             S.converged = 1;
             S.stopped_by = 0;
         } else {
-            go = 1;
+            next = j;
         }
     }
-    if (__shfl(go, 0))
-        ls_begin_wave(S, alphas + (long long)inst * G.K, ls_acc + (long long)inst * G.K * 6 * kLsReps, G.K, G.ls_mode,
-                      G.dx, (int)threadIdx.x);
+    next = __shfl(next, 0);
+    if (next)
+        ls_begin_wave(S, next, alphas + (long long)inst * G.K, ls_acc + (long long)inst * G.K * 6 * kLsReps, G.K,
+                      G.ls_mode, G.dx, (int)threadIdx.x);
 }
 
 hipError_t launch_gap(hipStream_t s, const NetDev& net, const float* cost, const int64_t* f, const int64_t* y,
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(64) void k_ls_begin(InstState* st, double* alphas, 
     InstState& S = st[i];
     if (!S.active || S.converged) return;
     if (only_fallback && S.ls_done != 2) return;
-    ls_begin_wave(S, alphas + (long long)i * K, ls_acc + (long long)i * K * 6 * kLsReps, K, ls_mode, dx,
+    ls_begin_wave(S, S.iter, alphas + (long long)i * K, ls_acc + (long long)i * K * 6 * kLsReps, K, ls_mode, dx,
                   (int)threadIdx.x);
 }
 

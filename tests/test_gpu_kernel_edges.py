@@ -361,3 +361,21 @@ def test_search_from_a_last_node_without_in_links(q, orc, kernel):
                 ref = orc.tree(net, cost, t)
                 assert np.array_equal(dist[t].cpu().numpy(), ref[0]), (shape, t)
                 assert np.array_equal(succ[t].cpu().numpy(), ref[1]), (shape, t)
+
+
+@pytest.mark.parametrize("n", [1, 2, 7])
+@pytest.mark.parametrize("ls_mode", [1, 2])
+def test_line_search_starts_from_the_running_iteration(q, n, ls_mode):
+    """The first step size of a search is a function of the iteration index alone, 2 / (2 + j) or 1 / (j + 1), and a
+    quasi-Newton search that any slope satisfies returns it: iteration n of a solve, two instances, three times."""
+    rng = np.random.default_rng(n)
+    want = 2.0 / (2.0 + n) if ls_mode == 1 else 1.0 / (n + 1.0)
+    opts = q.default_opts(ls_mode=ls_mode, T1=1e300, fixed_iters=n)
+    with q.Context() as ctx:
+        for i, m in enumerate((300, 5000)):
+            ctx.add(parallel_links(m, rng, 300.0))
+            ctx.set_demand(i, [0], [1], [40.0 * m], float("inf"))
+        for _ in range(3):
+            st, _ = ctx.solve(opts)
+            assert [s["last_alpha"] for s in st] == [want, want]
+            assert [s["iters"] for s in st] == [n, n]
