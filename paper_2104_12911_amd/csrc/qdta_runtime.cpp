@@ -128,9 +128,10 @@ struct qdta_ctx {
     // does not read them go
     unsigned int* ticket = nullptr;
     int* sink = nullptr;
-    // [0] overflow, [1] unreach, [2] absorption, [3..5] path-record faults: pinned
-    // host words that kernels set and the host reads after a synchronisation,
-    // before h_st
+    // [0] overflow, [1] unreach, [2] absorption, [3..5] path-record faults, [6]
+    // absorption in the trees of qdta_trees, which may be called between the steps
+    // of a solve whose absorption [2] holds: pinned host words that kernels set and
+    // the host reads after a synchronisation, before h_st
     int* h_flags = nullptr;
     bool flags_open = false;      // kernels that set flags may be in flight
     DBuf<int32_t> absorb_q, int_node;
@@ -218,8 +219,9 @@ int set_err(qdta_ctx* c, int code, const char* fmt, ...) {
 
 constexpr size_t kAlign = 256;
 constexpr size_t kKeepTreeBytes = (size_t)64 << 20;   // labels qdta_trees keeps between calls, at most
-constexpr size_t kFlagBytes = 64;        // qdta_ctx::h_flags, six words of it
-constexpr int kFlags = 6;
+constexpr size_t kFlagBytes = 64;        // qdta_ctx::h_flags, seven words of it
+constexpr int kFlags = 6;                // those of the calls that clear them (clear_flags)
+constexpr int kTreesTie = 6;             // qdta_trees' own word
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 void evict_label_history(qdta_ctx* c);
@@ -1082,7 +1084,7 @@ int open_flags(qdta_ctx* c) {
 
 int clear_flags(qdta_ctx* c) {
     RC(open_flags(c));
-    memset(c->h_flags, 0, kFlagBytes);
+    memset(c->h_flags, 0, kFlags * sizeof(int));
     return QDTA_OK;
 }
 
@@ -1799,7 +1801,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
     auto cleanup = [&]() {
         if (c->ws_base || c->t_buf.n > kKeepTreeBytes) dfree(c, c->t_buf);
     };
-    RC(clear_flags(c));
+    c->h_flags[kTreesTie] = 0;                   // set by this call alone, which ends synchronised
     int rc = QDTA_OK;
     do {
         // labels (whole runs of 128 bytes), then per tree its label offset, its
@@ -1832,7 +1834,8 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
         if ((e = launch_sssp(c->stream, net, dem, c->logpart.p, c->radj.p, lab, scr_view(c), slots, nullptr,
                              delta_scale(o), c->delta_inst.p, sssp_variant(c, o, nq), 0, true, nullptr, aq)))
             { rc = set_err(c, QDTA_EHIP, "sssp: %s", hipGetErrorString(e)); break; }
-        if ((e = launch_trees_out(c->stream, net, dem, lab, I.n, inst, dist, succ, aq, c->h_flags + 2)))
+        if ((e = launch_trees_out(c->stream, net, dem, lab, I.n, inst, dist, succ, aq,
+                                  c->h_flags + kTreesTie)))
             { rc = set_err(c, QDTA_EHIP, "trees_out: %s", hipGetErrorString(e)); break; }
         FlagsDev fl = flags_view(c);
         fl.absorb_q = aq;
@@ -1841,9 +1844,7 @@ int qdta_trees(qdta_ctx* c, const qdta_opts* o, int32_t inst, const float* cost,
                                  1, succ, I.n)))
             { rc = set_err(c, QDTA_EHIP, "fallback: %s", hipGetErrorString(e)); break; }
         if ((e = hipStreamSynchronize(c->stream))) { rc = set_err(c, QDTA_EHIP, "sync: %s", hipGetErrorString(e)); break; }
-        int h[kFlags];
-        take_flags(c, h);
-        if (h[2]) rc = QDTA_WABSORB;
+        if (c->h_flags[kTreesTie]) rc = QDTA_WABSORB;
     } while (0);
     if (rc < 0) (void)hipStreamSynchronize(c->stream);
     cleanup();

@@ -1,0 +1,69 @@
+"""Calls made between others on one context: what one call reports or keeps is not changed by the next."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2104_12911_amd import qdta
+    qdta.lib()
+    return qdta
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def demand(rng, n, legs):
+    return rng.integers(0, n, legs), rng.integers(0, n, legs), rng.uniform(1, 10, legs)
+
+
+def test_trees_between_steps_leave_the_solves_absorption(q):
+    """A solve that met FP32 absorption still says so after trees without any, and one without does not report that of
+    the trees grown in between."""
+    import torch
+    opts = q.default_opts(fixed_iters=1)
+    met = clean = 0
+    for seed in range(30):
+        rng = np.random.default_rng(seed)
+        net = synth.tiny_network(8, 10, rng, costs="huge")
+        plain = dev(rng.uniform(1.0, 2.0, net.m).astype(np.float32))
+        dem = demand(rng, 8, 30)
+        dests = dev(np.arange(8, dtype=np.int32))
+        dist = torch.empty((8, 8), dtype=torch.float32, device="cuda")
+        succ = torch.empty((8, 8), dtype=torch.int32, device="cuda")
+
+        def steps(fftt, between):
+            mid = []
+            with q.Context() as ctx:
+                ctx.add(synth.networks.Network(net.n, net.row_ptr, net.col, fftt, net.cap))
+                ctx.set_demand(0, *dem, float("inf"))
+                ctx.fw_begin(opts)
+                live, out = True, []
+                while live:
+                    mid.append(ctx.trees(opts, 0, between, dests, dist, succ))
+                    st, live = ctx.fw_step(opts)
+                    out.append(st[0]["absorb"])
+                mid.append(ctx.trees(opts, 0, between, dests, dist, succ))
+                out.append(ctx.fw_step(opts)[0][0]["absorb"])   # nothing runs any more: what the solve has recorded
+            return out, mid
+
+        huge = net.fftt.astype(np.float32)
+        out, mid = steps(huge, plain)
+        if out[0]:
+            assert mid == [q.OK] * len(mid) and all(out), seed
+            met += 1
+        out, mid = steps(rng.uniform(1.0, 2.0, net.m).astype(np.float32), dev(huge))
+        if mid[0] == q.WABSORB:
+            assert mid == [q.WABSORB] * len(mid) and not any(out), seed
+            clean += 1
+    assert met and clean
