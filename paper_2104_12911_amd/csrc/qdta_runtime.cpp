@@ -915,9 +915,7 @@ int search_slots(const qdta_ctx* c, int64_t trees, int wpc, int tw) {
 // (near, far) per nmax, one workgroup's (four wavefronts) at most 4 + 4; so
 // the near queue has a word per wavefront in either form.  Launches never use
 // more slots than exist.
-int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw) {
-    c->slots = search_slots(c, trees, wpc, tw);
-    const int near_w = c->slots, far_w = tw == 1 ? 2 * c->slots : c->slots;
+int grow_queues(qdta_ctx* c, int near_w, int far_w, int64_t nmax) {
     nmax = scratch_nmax(nmax);
     if (near_w > c->scr_near_w || far_w > c->scr_far_w || nmax > c->scr_nmax) {
         const int nw = std::max(near_w, c->scr_near_w), fw = std::max(far_w, c->scr_far_w);
@@ -928,6 +926,20 @@ int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw) {
         c->scr_far_w = fw;
         c->scr_nmax = nm;
     }
+    return QDTA_OK;
+}
+
+// Words for a launch of either form, with a workgroup (wpc4 wavefronts per CU)
+// or a wavefront (wpc1) per tree.
+void either_words(const qdta_ctx* c, int64_t trees, int wpc4, int wpc1, int* near_w, int* far_w) {
+    const int s4 = search_slots(c, trees, wpc4, 4), s1 = search_slots(c, trees, wpc1, 1);
+    *near_w = std::max(s4, s1);
+    *far_w = std::max(s4, 2 * s1);
+}
+
+int ensure_scratch(qdta_ctx* c, int64_t trees, int64_t nmax, int wpc, int tw) {
+    c->slots = search_slots(c, trees, wpc, tw);
+    RC(grow_queues(c, c->slots, tw == 1 ? 2 * c->slots : c->slots, nmax));
     RC(dalloc(c, c->work, 1));
     if (!c->sssp_stats.p) {
         RC(dalloc(c, c->sssp_stats, 2));
@@ -1548,7 +1560,8 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     add(pq, 4); add(pq, 4); add(pq, 8); add(pq + 1, 4); add(pp, 4); add(pp, 8); add(pp, 4); add(pp, 4);
     add(labels, 4); add(pq, 4); add(pp, 4); add(pp, 4);
     if (o->load_form == 2) { add(labels, 4); add(labels, 8); }   // plain-interval loading by merged paths
-    if (uses_contraction(o)) {                                    // chain contraction (at its bounds)
+    // chain contraction (at its bounds), also where the autotuner may ask for it
+    if (uses_contraction(o) || o->sssp_kernel == 0) {
         add(N + 1, 4); add(N, 4); add(contraction_words(N, M), 4); add(M, 8); add(N, 8);
         add(N, 16); add(ni + 1, 4);
     }
@@ -1556,13 +1569,10 @@ int qdta_workspace_query(qdta_ctx* c, const qdta_opts* o, int64_t max_legs, int6
     {
         const int tw = tree_waves(o), wpc = waves_per_cu(o);
         const size_t nm = (size_t)scratch_nmax(nmax);
-        size_t near_w = (size_t)search_slots(c, (int64_t)pq, wpc, tw), far_w = tw == 1 ? 2 * near_w : near_w;
-        if (o->sssp_kernel == 0) {                                // either form may be asked for later
-            const size_t other = (size_t)search_slots(c, (int64_t)pq, wpc, tw == 1 ? 4 : 1);
-            near_w = std::max(near_w, other);
-            far_w = std::max(far_w, tw == 1 ? other : 2 * other);
-        }
-        add(near_w * nm, 4); add(far_w * nm, 4);
+        int near_w = search_slots(c, (int64_t)pq, wpc, tw), far_w = tw == 1 ? 2 * near_w : near_w;
+        if (o->sssp_kernel == 0)                                  // either form may be asked for later
+            either_words(c, (int64_t)pq, wpc, wpc, &near_w, &far_w);
+        add((size_t)near_w * nm, 4); add((size_t)far_w * nm, 4);
         add(1, 4); add(2, 8); add(ni, 4);
     }
     if (o->keep_history) {
@@ -2174,7 +2184,24 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     if (!(budget_ms > 0.0)) return set_err(c, QDTA_EARG, "budget_ms must be > 0");
     for (const Instance& I : c->inst)
         if (!I.has_demand) return set_err(c, QDTA_ESTATE, "autotune needs the demand of every instance");
-    RC(ensure_demand(c, waves_per_cu(o), 1));             // slots for either kernel form
+    // queues for the trials of both tree forms, sized at once (what a workspace
+    // was sized for where one is bound), so that no trial runs on fewer than a
+    // solve of that form would and the solve finds them large enough
+    RC(ensure_demand(c, 0));
+    if (o->sssp_kernel < 2) {
+        qdta_opts one = *o;
+        one.tree_waves = 1;
+        qdta_opts four = *o;
+        four.tree_waves = 4;
+        const int wpc = waves_per_cu(o);
+        int near_w, far_w;
+        either_words(c, (int64_t)plan_dests(c, (size_t)c->Q), c->ws_base ? wpc : waves_per_cu(&four),
+                     c->ws_base ? wpc : waves_per_cu(&one), &near_w, &far_w);
+        RC(grow_queues(c, near_w, far_w, c->nmax));
+    }
+    const int saved_slots = c->slots;                     // a running solve's
+    RC(ensure_scratch(c, (int64_t)plan_dests(c, (size_t)c->Q), c->nmax, waves_per_cu(o), tree_waves(o)));
+    c->slots = saved_slots;
     RC(apply_rule(c, o));
     if (o->sssp_kernel == 0 || o->sssp_kernel == 4)       // trials of either tree form
         RC(ensure_contraction(c, c->h_dest_node.data(), c->h_dest_node.size()));
@@ -2219,8 +2246,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
         t.tree_waves = k < 0 ? start_tw : trials[k].tw;
         const int sh = t.sssp_shape, tw = t.tree_waves;
         const double sc = t.delta_scale;
-        // the trial's own occupancy (the scratch, sized for one wavefront per
-        // tree, covers both forms; launches never exceed it)
+        // the trial's own occupancy (launches never exceed the scratch)
         int ts = (int)std::min<int64_t>((int64_t)std::max<int64_t>(c->Q, 1) * (tw == 1 ? 1 : 4),
                                         (int64_t)c->cus * waves_per_cu(&t));
         ts = (ts + 3) / 4 * 4;

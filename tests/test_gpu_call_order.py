@@ -67,3 +67,35 @@ def test_trees_between_steps_leave_the_solves_absorption(q):
             assert mid == [q.WABSORB] * len(mid) and not any(out), seed
             clean += 1
     assert met and clean
+
+
+@pytest.mark.parametrize("workspace", [False, True])
+@pytest.mark.parametrize("tree_waves", [0, 1])
+def test_autotune_before_the_first_solve_leaves_it_its_queues(q, workspace, tree_waves):
+    """The autotuner times both tree forms on queues as large as a solve of either form takes: none of them allocates
+    any more afterwards, and inside a workspace of the queried size the solve still fits."""
+    import torch
+    rng = np.random.default_rng(5)
+    net = synth.grid_network(71, rng)
+    dem = demand(rng, net.n, 2000)
+    opts = q.default_opts(fixed_iters=2, tree_waves=tree_waves)
+    ref = torch.empty(net.m, dtype=torch.int64, device="cuda")
+    got = torch.empty_like(ref)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, *dem, 900.0)
+        ctx.solve(opts)
+        ctx.get_flows(ref)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, *dem, 900.0)
+        if workspace:
+            ws = torch.empty(ctx.workspace_query(opts), dtype=torch.uint8, device="cuda")
+            ctx.bind_workspace(ws)
+        ctx.autotune(q.default_opts(fixed_iters=2, tree_waves=tree_waves), 2.0)
+        before = ctx.alloc_count()
+        for tw in (4, 1):
+            ctx.solve(q.default_opts(fixed_iters=2, tree_waves=tw))
+            ctx.get_flows(got)
+            assert torch.equal(got, ref)
+        assert ctx.alloc_count() == before
