@@ -2188,11 +2188,10 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     // was sized for where one is bound), so that no trial runs on fewer than a
     // solve of that form would and the solve finds them large enough
     RC(ensure_demand(c, 0));
+    qdta_opts one = *o, four = *o;
+    one.tree_waves = 1;
+    four.tree_waves = 4;
     if (o->sssp_kernel < 2) {
-        qdta_opts one = *o;
-        one.tree_waves = 1;
-        qdta_opts four = *o;
-        four.tree_waves = 4;
         const int wpc = waves_per_cu(o);
         int near_w, far_w;
         either_words(c, (int64_t)plan_dests(c, (size_t)c->Q), c->ws_base ? wpc : waves_per_cu(&four),
@@ -2203,7 +2202,7 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     RC(ensure_scratch(c, (int64_t)plan_dests(c, (size_t)c->Q), c->nmax, waves_per_cu(o), tree_waves(o)));
     c->slots = saved_slots;
     RC(apply_rule(c, o));
-    if (o->sssp_kernel == 0 || o->sssp_kernel == 4)       // trials of either tree form
+    if (uses_contraction(c, &four, c->Q))                 // trials of a workgroup per tree
         RC(ensure_contraction(c, c->h_dest_node.data(), c->h_dest_node.size()));
     NetDev net = net_view(c, o);
     DemDev dem = dem_view(c);
@@ -2228,14 +2227,24 @@ int qdta_autotune(qdta_ctx* c, qdta_opts* o, double budget_ms, double* best_ms_o
     // -1, after an untimed launch that takes the first-touch costs; another
     // replaces it only when at least 5% faster (single trials vary by about
     // 2%), so near-ties do not flip the choice from run to run
-    const int start_shape = o->sssp_shape ? o->sssp_shape : o->tree_waves == 1 ? 3 : auto_shape(c, c->Q), start_tw = o->tree_waves ? o->tree_waves : 4;
+    const int start_tw = o->tree_waves ? o->tree_waves : 4;
+    const int start_shape = o->sssp_shape ? o->sssp_shape : start_tw == 1 ? 3 : auto_shape(c, c->Q);
     const double start_scale = delta_scale(o);
-    for (double sc : scales)
-        if (sc != start_scale) trials.push_back({start_shape, sc, start_tw});
-    for (int tw : tws)
+    // where a workgroup per tree means passes over labels in LDS, neither shape nor
+    // width changes it: one trial of it, the start's own if that is one
+    const bool pull = pull_trees(c, &four, c->Q);
+    if (!(pull && start_tw == 4))
+        for (double sc : scales)
+            if (sc != start_scale) trials.push_back({start_shape, sc, start_tw});
+    for (int tw : tws) {
+        if (pull && tw == 4) {
+            if (start_tw != 4) trials.push_back({auto_shape(c, c->Q), start_scale, tw});
+            continue;
+        }
         for (double sc : scales)
             for (int sh : shapes)
                 if (!(tw == start_tw && sh == start_shape)) trials.push_back({sh, sc, tw});
+    }
     int best_shape = start_shape, best_tw = start_tw;
     double best_scale = start_scale, best = 1e300, start_ms = 1e300, spent = 0.0;
     int rc = QDTA_OK;

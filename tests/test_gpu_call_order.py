@@ -99,3 +99,28 @@ def test_autotune_before_the_first_solve_leaves_it_its_queues(q, workspace, tree
             ctx.get_flows(got)
             assert torch.equal(got, ref)
         assert ctx.alloc_count() == before
+
+
+def test_autotune_on_a_small_network_keeps_the_path_record(q):
+    """Trees of a small network need no contraction, so the autotuner builds none and a recorded interval stays
+    usable; its choice is a configuration a solve takes."""
+    import torch
+    rng = np.random.default_rng(6)
+    net = synth.grid_network(12, rng)
+    o, d, trips = demand(rng, net.n, 300)
+    opts = q.default_opts(fixed_iters=2, keep_history=1)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, o, d, trips, 900.0)
+        ctx.solve(opts)
+        ctx.adjoint_record(opts)
+        legs = ctx.legs()[2].astype(np.float64) / (1 << 20)
+        f0, f1 = (torch.empty(net.m, dtype=torch.float64, device="cuda") for _ in range(2))
+        ctx.model_forward(opts, dev(legs), None, f0)
+        before = ctx.alloc_count()
+        for tw in (0, 1, 4):
+            tuned, ms = ctx.autotune(q.default_opts(fixed_iters=2, tree_waves=tw), 5.0)
+            assert tuned.tree_waves in (1, 4) and 1 <= tuned.sssp_shape <= 6 and ms > 0.0
+        assert ctx.alloc_count() == before
+        ctx.model_forward(opts, dev(legs), None, f1)
+        assert torch.equal(f0, f1)
