@@ -149,6 +149,7 @@ struct qdta_ctx {
     std::vector<char> lab_hist_ok;  // iterate j's labels are at lab_hist + j * label_count
     DBuf<double> lam_hist;
     DBuf<unsigned long long> done_fx;
+    uint64_t lay_gen = 0;         // bumped when the networks or the demand are laid out anew
     uint64_t gen = 0;             // bumped on every (re)allocation and every rebuild of the
                                   // network or demand tables: a captured iteration is valid
                                   // only for the generation it was captured in
@@ -171,7 +172,7 @@ struct qdta_ctx {
     // frozen-path model (OD calibration): each leg's truncated path under
     // every iterate's trees, and the states of the last model forward pass
     int adj_J = -1;
-    uint64_t adj_gen = 0, adj_solve = 0;
+    uint64_t adj_lay = 0, adj_solve = 0;
     bool adj_fwd = false;
     uint64_t adj_fwd_id = 0;      // bumped by every model forward; a backward names the one it reverses
     int adj_is_root = 1, adj_beta = 4;
@@ -571,6 +572,7 @@ int ensure_network(qdta_ctx* c) {
     c->dem_dirty = true;
     c->c_built = false;                // the contraction is rebuilt for the new layout
     c->croot.clear();
+    c->lay_gen++;
     c->gen++;                          // sizes baked into a captured iteration are stale
     return QDTA_OK;
 }
@@ -1021,6 +1023,7 @@ int ensure_demand(qdta_ctx* c, int wpc, int tw = 1) {
     c->dem_dirty = false;
     c->solved = false;
     c->lab_hist_ok.clear();
+    c->lay_gen++;
     c->gen++;                          // Q and P are baked into a captured iteration
     return QDTA_OK;
 }
@@ -2565,7 +2568,7 @@ int qdta_get_residual(qdta_ctx* c, int32_t inst, int64_t* count, int32_t* ho, in
 // Frozen-path model and its reverse pass (OD calibration)
 // ---------------------------------------------------------------------------
 static bool adj_valid(const qdta_ctx* c) {
-    return c->adj_J >= 0 && c->adj_gen == c->gen && c->adj_solve == c->solve_id && !c->dem_dirty && !c->net_dirty;
+    return c->adj_J >= 0 && c->adj_lay == c->lay_gen && c->adj_solve == c->solve_id && !c->dem_dirty && !c->net_dirty;
 }
 
 int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
@@ -2639,7 +2642,7 @@ int qdta_adjoint_record(qdta_ctx* c, const qdta_opts* o) {
             return set_err(c, QDTA_ESTATE, "iterate %d: paths changed between the two walks", j);
     }
     c->adj_J = J;
-    c->adj_gen = c->gen;
+    c->adj_lay = c->lay_gen;
     c->adj_solve = c->solve_id;
     return QDTA_OK;
 }

@@ -124,3 +124,50 @@ def test_autotune_on_a_small_network_keeps_the_path_record(q):
         assert ctx.alloc_count() == before
         ctx.model_forward(opts, dev(legs), None, f1)
         assert torch.equal(f0, f1)
+
+
+@pytest.mark.parametrize("k", [12, 70])
+def test_other_calls_keep_the_path_record(q, k):
+    """A recorded interval is usable until the next solve, demand or network, whatever other calls allocate: explicit
+    search kernels, other tree counts, line searches."""
+    import torch
+    rng = np.random.default_rng(k)
+    net = synth.grid_network(k, rng)
+    o, d, trips = demand(rng, net.n, 300)
+    opts = q.default_opts(fixed_iters=2, keep_history=1)
+    nq = 320
+    dist = torch.empty((nq, net.n), dtype=torch.float32, device="cuda")
+    succ = torch.empty((nq, net.n), dtype=torch.int32, device="cuda")
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, o, d, trips, 900.0)
+        ctx.solve(opts)
+        ctx.adjoint_record(opts)
+        legs = ctx.legs()[2].astype(np.float64) / (1 << 20)
+        f0, f1 = (torch.empty(net.m, dtype=torch.float64, device="cuda") for _ in range(2))
+        fbar = dev(rng.uniform(-1.0, 1.0, net.m))
+        grads = []
+        ctx.model_forward(opts, dev(legs), None, f0)
+        y = torch.empty(net.m, dtype=torch.int64, device="cuda")
+        cost = dev(net.fftt.astype(np.float32))
+        calls = [lambda: None,
+                 lambda: ctx.aon(q.default_opts(sssp_kernel=4), cost, y),
+                 lambda: ctx.aon(q.default_opts(tree_waves=1), cost, y),
+                 lambda: ctx.trees(q.default_opts(), 0, cost, dev(rng.integers(0, net.n, nq).astype(np.int32)), dist,
+                                   succ),
+                 lambda: ctx.autotune(q.default_opts(), 1.0)]
+        for call in calls:
+            call()
+            fid = ctx.model_forward(opts, dev(legs), None, f1)
+            assert torch.equal(f0, f1)
+            call()
+            dbar = torch.empty(legs.size, dtype=torch.float64, device="cuda")
+            cbar = torch.empty(net.m, dtype=torch.float64, device="cuda")
+            ctx.model_backward(fid, fbar, dbar, cbar)
+            torch.cuda.synchronize()
+            grads.append((dbar, cbar))
+        for g in grads[1:]:
+            assert torch.equal(g[0], grads[0][0]) and torch.equal(g[1], grads[0][1])
+        ctx.set_demand(0, o, d, trips, 900.0)
+        with pytest.raises(q.QdtaError):
+            ctx.model_forward(opts, dev(legs), None, f1)
