@@ -379,3 +379,31 @@ def test_line_search_starts_from_the_running_iteration(q, n, ls_mode):
             st, _ = ctx.solve(opts)
             assert [s["last_alpha"] for s in st] == [want, want]
             assert [s["iters"] for s in st] == [n, n]
+
+
+@pytest.mark.parametrize("tree_waves", [1, 4])
+@pytest.mark.parametrize("kernel", [0, 1])
+def test_tie_fallback_of_many_trees(q, orc, kernel, tree_waves):
+    """Most trees of a network whose dear links absorb the cheap ones are finished by the tie fallback, on as many
+    workgroups as the queues of the tree form hold: flows and stop nodes against the oracle."""
+    import torch
+    import synth
+    rng = np.random.default_rng(11)
+    net = synth.grid_network(9, rng)
+    cost = np.where(rng.random(net.m) < 0.5, rng.uniform(1e8, 4e8, net.m), rng.uniform(0.5, 8.0, net.m))
+    cost = cost.astype(np.float32)
+    pair = rng.choice(net.n * net.n, 2000, replace=False)
+    o, d = (pair // net.n).astype(np.int32), (pair % net.n).astype(np.int32)
+    o, d = o[o != d], d[o != d]
+    trips = rng.uniform(0.1, 5.0, o.size)
+    ref_y, ref_stop, code = orc.aon(net, cost, *orc.demand_legs(o, d, trips), float("inf"), rule=1)[:3]
+    assert code == orc.WARN_ABSORB
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, o, d, trips, float("inf"))
+        y = torch.empty(net.m, dtype=torch.int64, device="cuda")
+        stop = torch.empty(o.size, dtype=torch.int32, device="cuda")
+        rc = ctx.aon(q.default_opts(sssp_kernel=kernel, tree_waves=tree_waves), dev(cost), y, stop)
+        assert rc == q.WABSORB
+        assert np.array_equal(y.cpu().numpy(), ref_y)
+        assert np.array_equal(stop.cpu().numpy(), ref_stop)
