@@ -2639,7 +2639,10 @@ hipError_t launch_chain_fill(hipStream_t s, const NetDev& net, const DemDev& dem
 // only fall, each is written by its keeper alone, and any order of such steps
 // ends at the same least fixed point -- and every kPullPasses of them the
 // workgroup asks whether any label fell.  If none did, every pass since the last
-// question read the final labels.
+// question read the final labels.  Labels are compared by their bits, as the
+// queues do: a sum below zero (or NaN) lies above all others and is not taken.
+// Between two questions every label is lowered along one more link at least, so
+// n of them are enough where no cycle of costs is negative; no input takes more.
 // Bound by the passes' LDS reads, about as many passes as the longest shortest
 // path has links, so for small n only (pull_trees); no queue and no chain of
 // memory accesses in a step.  Whole call, 40 trees of a congested 400-node grid:
@@ -2683,6 +2686,7 @@ __global__ __launch_bounds__(NT) void k_sssp_pull(NetDev net, DemDev dem, label_
     const bool longer = __ballot(more) != 0ull;
     int passes = 0;
     bool fell;
+    int asked = 0;
     __syncthreads();
     do {
         fell = false;
@@ -2692,21 +2696,22 @@ __global__ __launch_bounds__(NT) void k_sssp_pull(NetDev net, DemDev dem, label_
                 float d[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) d[j] = lab[head[p][j]];
-                float low = fminf(fminf(d[0] + c[p][0], d[1] + c[p][1]), fminf(d[2] + c[p][2], d[3] + c[p][3]));
+                uint32_t low = min(min(__float_as_uint(d[0] + c[p][0]), __float_as_uint(d[1] + c[p][1])),
+                                   min(__float_as_uint(d[2] + c[p][2]), __float_as_uint(d[3] + c[p][3])));
                 if (longer)
                     for (int e = 4; e < deg[p]; ++e) {
                         const uint2 r = net.fadj[e0[p] + e];
-                        low = fminf(low, lab[(int)r.x - node0] + __uint_as_float(r.y));
+                        low = min(low, __float_as_uint(lab[(int)r.x - node0] + __uint_as_float(r.y)));
                     }
-                if (low < mine[p]) {
-                    mine[p] = low;
-                    lab[tid + p * NT] = low;
+                if (low < __float_as_uint(mine[p])) {
+                    mine[p] = __uint_as_float(low);
+                    lab[tid + p * NT] = mine[p];
                     fell = true;
                 }
             }
         }
         passes += kPullPasses;
-    } while (__syncthreads_or(fell));
+    } while (__syncthreads_or(fell) && ++asked < n);
     const int top = (n + 31) / 32 * 32;
 #pragma unroll
     for (int p = 0; p < P; ++p) {

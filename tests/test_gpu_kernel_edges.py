@@ -407,3 +407,29 @@ def test_tie_fallback_of_many_trees(q, orc, kernel, tree_waves):
         assert rc == q.WABSORB
         assert np.array_equal(y.cpu().numpy(), ref_y)
         assert np.array_equal(stop.cpu().numpy(), ref_stop)
+
+
+@pytest.mark.parametrize("kernel", [0, 1, 4])
+def test_trees_with_costs_that_are_none(q, kernel):
+    """Costs no assignment has: a negative one off every cycle counts like any other while the sum is not negative, a
+    sum below zero and NaN are never taken; and on a negative cycle the trees still end."""
+    import torch
+    # 0 is the destination; 1 -> 0, 2 -> 1, 3 -> 1, 4 -> 0 and 4 -> 2, 5 -> 4, and 6 <-> 7 with 6 -> 0
+    tail, head = np.array([1, 2, 3, 4, 4, 5, 6, 6, 7, 7]), np.array([0, 1, 1, 0, 2, 4, 0, 7, 6, 0])
+    cost = np.array([10.0, -3.0, -20.0, 9.0, 1.0, np.nan, 10.0, 1.0, 2.0, 50.0], np.float32)
+    row = np.zeros(9, np.int32)
+    np.cumsum(np.bincount(tail, minlength=8), out=row[1:])
+    net = Network(8, row, head.astype(np.int32), np.ones(10, np.float32), np.full(10, 900.0, np.float32))
+    inf = np.inf
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], inf)
+        dist = torch.empty((1, 8), dtype=torch.float32, device="cuda")
+        succ = torch.empty((1, 8), dtype=torch.int32, device="cuda")
+        o = q.default_opts(sssp_kernel=kernel)
+        ctx.trees(o, 0, dev(cost), dev(np.zeros(1, np.int32)), dist, succ)
+        assert dist[0].cpu().tolist() == [0.0, 10.0, 7.0, inf, 8.0, inf, 10.0, 12.0]
+        cost[7] = -2.5                                     # 6 -> 7 -> 6 costs -0.5
+        ctx.trees(o, 0, dev(cost), dev(np.zeros(1, np.int32)), dist, succ)
+        d = dist[0].cpu().tolist()
+        assert d[:6] == [0.0, 10.0, 7.0, inf, 8.0, inf] and 0.0 <= d[6] <= 10.0 and 0.0 <= d[7] <= 50.0
