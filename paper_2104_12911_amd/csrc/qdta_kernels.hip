@@ -99,30 +99,33 @@ __device__ __forceinline__ i128 get128(const long long* in) {
 // |H| stays below 2^79 and |L| below 2^39, so every addition is exact and the
 // order does not matter: five FP64 additions a term, where the same term as an
 // int128 took the compiler's double -> int128 conversion and a 4-word add.
-// A larger term goes straight to the global accumulator; one beyond the int128
-// range (or not finite) sets bad.
+// A larger term goes to the workgroup's own three words in LDS (acc3_add: 2^11
+// of them fit, while 2^22 of them, one by one, would overflow the words in
+// memory); one beyond the int128 range (or not finite) sets bad.
 struct XSum {
     double H = 0.0, L = 0.0;
 };
 constexpr double kXSplit = 453347182355485940514816.0;    // 1.5 * 2^78
 constexpr double kXLimit = 73786976294838206464.0;        // 2^66
-__device__ __forceinline__ void xsum_add(XSum& a, double s, long long* acc, int& bad) {
+__device__ __forceinline__ void xsum_add(XSum& a, double s, long long* big, int& bad) {
     const double v = __builtin_rint(s);
     if (__builtin_fabs(v) < kXLimit) {
         const double h = (v + kXSplit) - kXSplit;
         a.H += h;
         a.L += v - h;
     } else if (__builtin_fabs(v) < 1.7e38) {
-        acc3_add(acc, (i128)v);
+        acc3_add(big, (i128)v);
     } else {
         bad = 1;
     }
 }
 __device__ __forceinline__ i128 xsum_value(const XSum& a) { return (i128)a.H + (i128)a.L; }
 
-// Workgroup sums of two terms per thread, added to this workgroup's copy of an
-// instance's exact accumulators ([copy][2][3] words, kSumReps copies).
-__device__ void wg_pair_add(const XSum& x0, const XSum& x1, long long* acc, double (*red)[kWG]) {
+// Workgroup sums of two terms per thread and of their large terms (big, in LDS),
+// added to this workgroup's copy of an instance's exact accumulators ([copy][2][3]
+// words, kSumReps copies).
+__device__ void wg_pair_add(const XSum& x0, const XSum& x1, const long long* big, long long* acc,
+                            double (*red)[kWG]) {
     const int tid = threadIdx.x;
     red[0][tid] = x0.H;
     red[1][tid] = x0.L;
@@ -138,7 +141,7 @@ __device__ void wg_pair_add(const XSum& x0, const XSum& x1, long long* acc, doub
         XSum x;
         x.H = red[2 * tid][0];
         x.L = red[2 * tid + 1][0];
-        acc3_add(acc + 3 * tid, xsum_value(x));
+        acc3_add(acc + 3 * tid, xsum_value(x) + acc3_value(big + 3 * tid));
     }
 }
 
@@ -369,10 +372,13 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
                                              long long* acc, InstState* st, int* err, unsigned int* ticket,
                                              GapRule G, double* alphas, long long* ls_acc) {
     __shared__ double red[4][kWG];
+    __shared__ long long s_big[6];
     __shared__ int s_last;
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
     if (!inst_live(st, inst)) return;
+    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;
+    __syncthreads();
     const InstDev I = net.inst[inst];
     const int part = kChunk / (int)gridDim.y;
     const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
@@ -383,11 +389,11 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
     int bad = 0;
     for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
         const double c = (double)cost[a];
-        xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, mine, bad);
-        xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, mine + 3, bad);
+        xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, s_big, bad);
+        xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, s_big + 3, bad);
     }
     if (bad) *err = 1;
-    wg_pair_add(sf, sy, mine, red);
+    wg_pair_add(sf, sy, s_big, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
     InstState& S = st[inst];
@@ -596,8 +602,13 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
                                                  const int64_t* __restrict__ y, double alpha_b, int beta, int K,
                                                  double* alphas, long long* ls_acc, InstState* st, int only_pending,
                                                  int* err, int k0, int kstride, int reps, LsRule rule) {
-    __shared__ LsLink s_link[kLsTile];
-    __shared__ double s_red[4][kWG];
+    __shared__ union {                       // the links of a tile; after the last, the threads' sums
+        LsLink link[kLsTile];
+        double red[4][kWG];
+    } s_mem;
+    auto& s_link = s_mem.link;
+    auto& s_red = s_mem.red;
+    __shared__ long long s_big[2 * kMaxK * 3];   // large terms, per step size and sum
     __shared__ int s_last;
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
@@ -620,6 +631,7 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
     const bool fast = kappa > 0x1p-60 && kappa < 0x1p60;
     XSum sc, sd;
     int bad = 0;
+    for (int x = tid; x < K * 6; x += kWG) s_big[x] = 0;   // (before the first tile's barrier)
     for (int t0 = a0; t0 < a1; t0 += kLsTile) {
         const int nt = min(kLsTile, a1 - t0);
         if (tid < nt) {
@@ -639,14 +651,14 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
 #pragma unroll 2
                 for (int x = g; x < nt; x += G) {
                     ls_terms_q<BETA, SO, true>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
-                    xsum_add(sc, obj, acc + k * 6, bad);
-                    xsum_add(sd, der, acc + k * 6 + 3, bad);
+                    xsum_add(sc, obj, s_big + k * 6, bad);
+                    xsum_add(sd, der, s_big + k * 6 + 3, bad);
                 }
             } else {
                 for (int x = g; x < nt; x += G) {
                     ls_terms_q<BETA, SO, false>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
-                    xsum_add(sc, obj, acc + k * 6, bad);
-                    xsum_add(sd, der, acc + k * 6 + 3, bad);
+                    xsum_add(sc, obj, s_big + k * 6, bad);
+                    xsum_add(sd, der, s_big + k * 6 + 3, bad);
                 }
             }
         }
@@ -672,7 +684,7 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
         XSum x;
         x.H = s_red[2 * w][kk];
         x.L = s_red[2 * w + 1][kk];
-        acc3_add(acc + kk * 6 + 3 * w, xsum_value(x));
+        acc3_add(acc + kk * 6 + 3 * w, xsum_value(x) + acc3_value(s_big + kk * 6 + 3 * w));
     }
     if (!rule.on) return;
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
@@ -759,11 +771,14 @@ __global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restri
                                              long long* acc, InstState* st, int apply_rule, double tol, int* err,
                                              unsigned int* ticket) {
     __shared__ double red[4][kWG];
+    __shared__ long long s_big[6];
     __shared__ int s_last;
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
     if (!st[inst].active) return;
     if (apply_rule && st[inst].converged) return;
+    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;
+    __syncthreads();
     const InstDev I = net.inst[inst];
     const int part = kChunk / (int)gridDim.y;
     const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
@@ -777,16 +792,16 @@ __global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restri
         double obj, der;
         const double F = (double)f[a] * kFxInv;
         ls_terms(F, F, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-        xsum_add(s0, obj * kSumQ, mine, bad);
+        xsum_add(s0, obj * kSumQ, s_big, bad);
         if (apply_rule) {
             const int64_t fn = f[a] + (int64_t)__builtin_rint(alpha * (double)(y[a] - f[a]));
             const double Fn = (double)fn * kFxInv;
             ls_terms(Fn, Fn, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-            xsum_add(s1, obj * kSumQ, mine + 3, bad);
+            xsum_add(s1, obj * kSumQ, s_big + 3, bad);
         }
     }
     if (bad) *err = 1;
-    wg_pair_add(s0, s1, mine, red);
+    wg_pair_add(s0, s1, s_big, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
     i128 v0, v1;

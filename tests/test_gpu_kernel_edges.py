@@ -433,3 +433,33 @@ def test_trees_with_costs_that_are_none(q, kernel):
         ctx.trees(o, 0, dev(cost), dev(np.zeros(1, np.int32)), dist, succ)
         d = dist[0].cpu().tolist()
         assert d[:6] == [0.0, 10.0, 7.0, inf, 8.0, inf] and 0.0 <= d[6] <= 10.0 and 0.0 <= d[7] <= 50.0
+
+
+def test_line_search_sums_of_millions_of_large_terms(q, orc):
+    """2^22 links and more, every term beyond 2^66 with its low 42 bits well filled, on the one copy of the sums that
+    the call without allocations has: m times the oracle's term."""
+    import torch
+    m = (1 << 22) + 4097
+    one = np.ones(1, np.float32)
+    low = (1 << 42) - 1
+    for x in range(1000 * FX, 1001 * FX):
+        f, y = np.array([x], np.int64), np.array([3 * x], np.int64)
+        C, D, _ = orc.ls_eval(f, y, one, one, 0.15, 4, 900.0, np.array([0.0]))
+        if min(C[0], D[0]) > 1 << 66 and min(C[0] & low, D[0] & low) * m > 1.05 * (1 << 63):
+            break
+    else:
+        raise AssertionError("no such flow")
+    net = Network(2, np.array([0, m, m], np.int32), np.ones(m, np.int32), np.ones(m, np.float32),
+                  np.ones(m, np.float32))
+    F, Y = (torch.full((m,), v, dtype=torch.int64, device="cuda") for v in (x, 3 * x))
+    alphas = dev(np.zeros(1))
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [], [], [], 900.0)
+        ctx.layout()
+        for call in (ctx.ls_eval, ctx.ls_eval_noalloc):
+            sums = torch.zeros(4, dtype=torch.int64, device="cuda")
+            call(q.default_opts(), F, Y, alphas, sums)
+            s = sums.cpu().numpy().reshape(2, 2)
+            assert i128(*s[0]) == m * C[0], call
+            assert i128(*s[1]) == m * D[0], call
