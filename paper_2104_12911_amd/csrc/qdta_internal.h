@@ -159,6 +159,7 @@ struct Scratch {
     int64_t nmax;            // >= largest n + kSearchSlack + 65
     int32_t* work;           // tree work counter
     int32_t near_w, far_w;   // words allocated per nmax in either queue (a launch is clamped to the slots they hold)
+    int32_t cus;             // compute units of the device
     unsigned long long* stats; // [2] nodes taken and in-links relaxed, added up by the kernels
 };
 

@@ -1271,7 +1271,8 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
                 const int i = i0 + lane;
                 const bool h = i < fcnt;
                 uint2 ent = h ? farq[i] : make_uint2(0u, kInfBits);
-                if (h) ent.y = ld_coherent(&D[ent.x]) & kValueBits;   // the label now (see k_sssp_wg)
+                // by the label now: an improved node is not queued again
+                if (h) ent.y = ld_coherent(&D[ent.x]) & kValueBits;
                 const float dv = __uint_as_float(ent.y);
                 const bool ton = h && dv < thr;
                 const bool tok = h && !ton;
@@ -1342,10 +1343,12 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
 // the grid), lanes over records with minimum keys instead of a thread per entry
 // with compare-and-swapped slots -> 48 (2.4 -> 2.1, 0.79 -> 0.69).
 //
-// W: wavefronts per SIMD the register allocation aims at, at most; <2, 4> and
-// <2, 2> keep to 128 VGPRs, for the four workgroups per CU that the LDS holds
-// (151 of them, for three: 2.7 instead of 2.1 ms on the metro network, whose
-// 1,000 trees then take two turns).
+// The registers of <2, 4> and <2, 2> are kept to 128 VGPRs, for the four
+// workgroups per CU that the LDS holds (151 of them, for three: 2.7 instead of
+// 2.1 ms on the metro network, whose 1,000 trees then take two turns).  W is the
+// most wavefronts per SIMD that the allocation is told to aim at; with that
+// minimum it decides nothing (<2, 4, true> compiles to the same code with 7 and
+// with 8), but it is part of the name that kernel traces are searched for.
 template <int U, int V, bool CT, int W = 8>
 __global__ __launch_bounds__(128 * U) __attribute__((amdgpu_waves_per_eu(U == 2 ? 4 : 1, W))) void k_sssp_wg(
     NetDev net, DemDev dem, const uint2* __restrict__ radj, label_t* labels, Scratch scr, const InstState* st,
@@ -1807,13 +1810,8 @@ __global__ __launch_bounds__(kWG) void k_sssp_wn(NetDev net, DemDev dem, const u
                                                  const float* __restrict__ delta_inst, int early, int t_begin,
                                                  int t_end) {
     constexpr int NT = kWG;
-    constexpr int NW = NT / 64;
     constexpr int NP = NT * U;                    // nodes per step
-    __shared__ int s_pre[NP + 1];
-    __shared__ float s_dw[NP];
-    __shared__ int s_e0[NP];
     __shared__ int s_rh[64], s_rc[64], s_rhp[64], s_tail[64], s_push[64], s_tpre[64];
-    __shared__ int s_wsum[NW];
     __shared__ int s_t, s_nn, s_fn;
     __shared__ uint32_t s_fm;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1935,7 +1933,7 @@ __global__ __launch_bounds__(kWG) void k_sssp_wn(NetDev net, DemDev dem, const u
                 __syncthreads();
                 // every thread takes up to U nodes and relaxes all their in-links
                 // itself: in-degrees of road networks are small, so the owner
-                // search and the degree prefix sum of k_sssp_wg are left out
+                // search and the degree prefix sum of k_sssp_ds are left out
                 int wn_[U], e0_[U], e1_[U];
                 float dw_[U];
 #pragma unroll
@@ -2774,7 +2772,7 @@ hipError_t launch_trees(hipStream_t s, const NetDev& net, const DemDev& dem, con
         static const int units[] = {1, 1, 2, 4, 2, 4};
         const int v = min(variant - (ct ? 32 : 8), 5), nt = 128 * units[v];
         // where every tree can have a CU it has its own workgroup
-        blocks = max((slots * 64 + nt - 1) / nt, min(t_end - t_begin, 256));
+        blocks = max((slots * 64 + nt - 1) / nt, min(t_end - t_begin, scr.cus));
         blocks = min(blocks, min(scr.near_w, scr.far_w) / 4);
         if (blocks <= 0) return hipErrorInvalidValue;
 #define QDTA_SSSP_WG(...)                                                                                          \
@@ -3157,15 +3155,17 @@ hipError_t launch_walk(hipStream_t s, const NetDev& net, const DemDev& dem, cons
     if (l_end <= l_begin) return hipSuccess;
     WalkOut o{y, stop, stop_delay, residual_mode, lambda, r_dense, done_fx,
               tr ? *tr : TransitOut{nullptr, nullptr, nullptr, nullptr, nullptr, 0u}, fl.err_overflow};
-    // Fewer legs than fit on the chip (196,608 with this table): one leg at a time
-    // per walker, since a walker's legs run one after another and a hop is two
-    // dependent loads, and four lanes a leg, which load a row's links together
-    // (one line instead of one a link).  More legs: two per thread, whose loads
-    // share the table; there four lanes a leg only put fewer legs in flight.
-    // Phase times at one leg per thread / two / one per four lanes, us: 1,560 legs
-    // 38 / 73 / 33; 73k legs of 250 trees 227 / 438 / 194; 90k legs of 300 static
-    // trees 471 / 833 / 447; 316k legs 823 / 686 / 854; 1.2M legs 3,688 / 3,766 /
-    // 4,090.
+    // Four lanes a leg load a row's links together (one line instead of one a
+    // link), which pays while most legs are in flight at once (512 threads hold 128
+    // legs, about 98,000 on the card); two legs per thread put the most in flight
+    // and share the table between the most.  The line is where they were found to
+    // cross: legs, us of the phase with four lanes a leg / with two legs a thread:
+    // 85,713 326 / 533; 180,898 548 / 618; 175,041 697 / 691; 203,948 870 / 685;
+    // 229,780 752 / 731; 348,614 968 / 852; 1.13M 3,429 / 3,393 (road networks of 100k
+    // and 300k nodes at 900 s); static grids: 89,700 436 / 755; 175,980 793 / 909;
+    // 249,500 986 / 929; 359,400 1,344 / 1,289.  One leg per thread, not used, lies
+    // between them or below on some of these (125,800 legs: 401; 1.13M: 2,989) and
+    // above both on others (203,948: 793; 229,780: 863; 249,500: 1,047).
 #define QDTA_WALK(NT, LPT, Q)                                                                                      \
     hipLaunchKernelGGL((k_walk<NT, LPT, Q>),                                                                       \
                        dim3((unsigned)((l_end - l_begin + NT / Q * LPT - 1) / (NT / Q * LPT))), dim3(NT), 0, s,    \
@@ -3535,9 +3535,10 @@ hipError_t launch_trees_out(hipStream_t s, const NetDev& net, const DemDev& dem,
 // The truncated path of every leg under one iterate's trees: the links the
 // walk of that iterate loads (same successor rule, same clock), in walk
 // order.  ptr == NULL counts them into len[l]; otherwise they are written at
-// links[ptr[l]] (and the leg index at leg_of[ptr[l]]), never past ptr[l + 1].  bad: 1 an origin cannot reach its
-// destination, 2 FP32 absorption (the tie fallback's paths are not
-// recorded), 4 a path longer than counted.
+// links[ptr[l]] (and the leg index at leg_of[ptr[l]]), never past ptr[l + 1].
+// bad: three words, set to 1 where an origin cannot reach its destination, where
+// FP32 absorption ends a path (the tie fallback's paths are not recorded), and
+// where a path is longer than counted.
 __global__ __launch_bounds__(kWG) void k_path_walk(NetDev net, DemDev dem, const label_t* __restrict__ labels,
                                                    const int64_t* __restrict__ ptr, int32_t* __restrict__ links,
                                                    int32_t* __restrict__ leg_of, int64_t* __restrict__ len,

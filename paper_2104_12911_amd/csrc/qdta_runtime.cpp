@@ -1067,6 +1067,7 @@ Scratch scr_view(qdta_ctx* c) {
     s.work = c->work.p;
     s.near_w = c->scr_near_w;
     s.far_w = c->scr_far_w;
+    s.cus = c->cus;
     s.stats = c->sssp_stats.p;
     return s;
 }
