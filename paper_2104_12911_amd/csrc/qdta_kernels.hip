@@ -1332,8 +1332,10 @@ __global__ __launch_bounds__(kWG) void k_sssp_ds(NetDev net, DemDev dem, const u
 // is left out waits for the kept nodes its label depends on; the chain
 // nodes' labels are filled from their chains' ends afterwards (k_chain_fill).
 //
-// Bound by memory traffic where all trees together are far larger than the L2
-// (550k nodes, 5,000 trees: 48 ms, 84 ms before this form), by the latency of a
+// Bound by the rate of memory requests where all trees together are far larger
+// than the L2 (550k nodes, 5,000 trees: 48 ms, 84 ms before this form; 1.83G line
+// reads and 1.14G writes leave the L2, 38G reads a second beside 24G writes, where
+// a gather of random words, one read each, reaches 41G), by the latency of a
 // step's chain of accesses and the issue of its instructions below that (metro
 // network, 100k nodes, 1,000 trees: 2.1 ms, 5.7; 22,801-node grid, 300 trees:
 // 0.69 ms, 3.77; 400-node grid, 40 trees: 0.06 ms, 0.13).  What each part gave on
