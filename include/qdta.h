@@ -291,7 +291,8 @@ int qdta_bpr(qdta_ctx *ctx, const qdta_opts *opts, const int64_t *f_fx, float *c
  * dist[w] < dist[v]; where FP32 absorption leaves none, the lowest-uid tight
  * link to a node one hop closer to the destination in the tight subgraph
  * (then QDTA_WABSORB is returned; this call synchronises).  cost is the
- * instance's float[m] (device). */
+ * instance's float[m] (device), >= 0 (a sum below zero or NaN is never taken as
+ * a distance). */
 int qdta_trees(qdta_ctx *ctx, const qdta_opts *opts, int32_t inst, const float *cost, int32_t nq,
                const int32_t *dest, float *dist, int32_t *succ);
 

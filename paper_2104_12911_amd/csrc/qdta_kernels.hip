@@ -3601,11 +3601,17 @@ hipError_t launch_path_walk(hipStream_t s, const NetDev& net, const DemDev& dem,
 // real-valued demand, exact in int64 whatever the order of the atomics.
 // One lane per (leg, link) entry of the flattened paths, so the link ids
 // and leg indices are read coalesced and long paths spread over lanes.  A
-// workgroup takes a run of kPathRun entries and sums it per link in LDS first, as
-// k_walk does: the legs of a destination are neighbours and share many of their
-// links, and an atomic on y is carried out beyond the L2 (27,400 legs of 300
-// destinations on 100k nodes: 67 us, 114 with an atomic on y per entry; 69 to 76
-// with smaller workgroups, 80 with runs of 1,024).
+// workgroup takes a run of kPathRun entries and sums it per link in LDS first:
+// the legs of a destination are neighbours and share many of their links, and an
+// atomic on y is carried out beyond the L2.  The table keeps the 16 links of a
+// 128-byte line of y together (links along a path are neighbours too), so that
+// the sums leave it line by line, as the entries themselves would; with the lines
+// scattered over the slots, paths that share little took longer than an atomic on
+// y per entry.  Forward pass of the model, one iterate, us, with an atomic per entry
+// / with scattered slots / so: 261k legs to 5,000 of 550k nodes at 900 s 2,058 /
+// 2,716 / 1,600, to the end 5,058 / 4,791 / 2,730; 27,400 legs to 300 of 100k nodes
+// 401 / 282 / 241.  (Runs of 1,024 and 2,048 entries and smaller workgroups: up to
+// 20% longer.)
 constexpr int kPathRun = 4096, kPathWG = 1024;
 
 __global__ __launch_bounds__(kPathWG) void k_path_load(int64_t total, const int32_t* __restrict__ links,
@@ -3629,7 +3635,7 @@ __global__ __launch_bounds__(kPathWG) void k_path_load(int64_t total, const int3
         }
         const int64_t w = (int64_t)__builtin_rint(x);
         if (w == 0) continue;
-        int h = (int)(((unsigned)e * 2654435761u) >> 16) & (SLOTS - 1);
+        int h = ((int)(((unsigned)(e >> 4) * 2654435761u) >> 16) << 4 | (e & 15)) & (SLOTS - 1);
         bool in = false;
         for (int probe = 0; probe < 4 && !in; ++probe) {
             const int k = atomicCAS(&s_key[h], -1, e);
