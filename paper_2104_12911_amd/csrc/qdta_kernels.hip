@@ -99,31 +99,36 @@ __device__ __forceinline__ i128 get128(const long long* in) {
 // |H| stays below 2^79 and |L| below 2^39, so every addition is exact and the
 // order does not matter: five FP64 additions a term, where the same term as an
 // int128 took the compiler's double -> int128 conversion and a 4-word add.
-// A larger term goes to the workgroup's own three words in LDS (acc3_add: 2^11
-// of them fit, while 2^22 of them, one by one, would overflow the words in
-// memory); one beyond the int128 range (or not finite) sets bad.
+// Larger terms are left out and noted (odd): the workgroup then goes over its
+// links once more for those alone (xsum_large), adding them to three words of LDS
+// per sum, of which 2^11 such terms need a part, while 2^22 of them, one by one,
+// would overflow the words in memory.  One beyond the int128 range (or not finite)
+// sets bad.  A branch for them in the loop itself cost a pass 5%.
 struct XSum {
     double H = 0.0, L = 0.0;
 };
 constexpr double kXSplit = 453347182355485940514816.0;    // 1.5 * 2^78
 constexpr double kXLimit = 73786976294838206464.0;        // 2^66
-__device__ __forceinline__ void xsum_add(XSum& a, double s, long long* big, int& bad) {
+__device__ __forceinline__ void xsum_add(XSum& a, double s, int& odd) {
     const double v = __builtin_rint(s);
-    if (__builtin_fabs(v) < kXLimit) {
-        const double h = (v + kXSplit) - kXSplit;
-        a.H += h;
-        a.L += v - h;
-    } else if (__builtin_fabs(v) < 1.7e38) {
-        acc3_add(big, (i128)v);
-    } else {
-        bad = 1;
-    }
+    const bool in = __builtin_fabs(v) < kXLimit;
+    odd |= in ? 0 : 1;
+    const double u = in ? v : 0.0;
+    const double h = (u + kXSplit) - kXSplit;
+    a.H += h;
+    a.L += u - h;
+}
+__device__ __forceinline__ void xsum_large(long long* big, double s, int& bad) {
+    const double v = __builtin_rint(s);
+    if (__builtin_fabs(v) < kXLimit) return;
+    if (__builtin_fabs(v) < 1.7e38) acc3_add(big, (i128)v);
+    else bad = 1;
 }
 __device__ __forceinline__ i128 xsum_value(const XSum& a) { return (i128)a.H + (i128)a.L; }
 
-// Workgroup sums of two terms per thread and of their large terms (big, in LDS),
-// added to this workgroup's copy of an instance's exact accumulators ([copy][2][3]
-// words, kSumReps copies).
+// Workgroup sums of two terms per thread and of their large terms (big, in LDS;
+// NULL: none), added to this workgroup's copy of an instance's exact accumulators
+// ([copy][2][3] words, kSumReps copies).
 __device__ void wg_pair_add(const XSum& x0, const XSum& x1, const long long* big, long long* acc,
                             double (*red)[kWG]) {
     const int tid = threadIdx.x;
@@ -141,7 +146,7 @@ __device__ void wg_pair_add(const XSum& x0, const XSum& x1, const long long* big
         XSum x;
         x.H = red[2 * tid][0];
         x.L = red[2 * tid + 1][0];
-        acc3_add(acc + 3 * tid, xsum_value(x) + acc3_value(big + 3 * tid));
+        acc3_add(acc + 3 * tid, xsum_value(x) + (big ? acc3_value(big + 3 * tid) : 0));
     }
 }
 
@@ -377,8 +382,7 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
     const int b = blockIdx.x;
     const int inst = net.blk_inst[b];
     if (!inst_live(st, inst)) return;
-    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;
-    __syncthreads();
+    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;   // seen by all after __syncthreads_or below
     const InstDev I = net.inst[inst];
     const int part = kChunk / (int)gridDim.y;
     const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
@@ -386,14 +390,23 @@ __global__ __launch_bounds__(kWG) void k_gap(NetDev net, const float* __restrict
     long long* sums = acc + (long long)inst * kSumReps * 6;
     long long* mine = sums + ((blockIdx.y * gridDim.x + blockIdx.x) % kSumReps) * 6;
     XSum sf, sy;
-    int bad = 0;
+    int odd = 0;
     for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
         const double c = (double)cost[a];
-        xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, s_big, bad);
-        xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, s_big + 3, bad);
+        xsum_add(sf, c * ((double)f[a] * kFxInv) * kSumQ, odd);
+        xsum_add(sy, c * ((double)y[a] * kFxInv) * kSumQ, odd);
     }
-    if (bad) *err = 1;
-    wg_pair_add(sf, sy, s_big, mine, red);
+    odd = __syncthreads_or(odd);
+    if (odd) {
+        int bad = 0;
+        for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
+            const double c = (double)cost[a];
+            xsum_large(s_big, c * ((double)f[a] * kFxInv) * kSumQ, bad);
+            xsum_large(s_big + 3, c * ((double)y[a] * kFxInv) * kSumQ, bad);
+        }
+        if (bad) *err = 1;
+    }
+    wg_pair_add(sf, sy, odd ? s_big : nullptr, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
     InstState& S = st[inst];
@@ -630,9 +643,9 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
     // kappa far from 1 could take the quotient out of the normal range
     const bool fast = kappa > 0x1p-60 && kappa < 0x1p60;
     XSum sc, sd;
-    int bad = 0;
-    for (int x = tid; x < K * 6; x += kWG) s_big[x] = 0;   // (before the first tile's barrier)
-    for (int t0 = a0; t0 < a1; t0 += kLsTile) {
+    int odd = 0, bad = 0;
+    // the links of the tile at t0 into LDS; how many they are
+    auto stage = [&](int t0) __attribute__((always_inline)) {
         const int nt = min(kLsTile, a1 - t0);
         if (tid < nt) {
             const int a = t0 + tid;
@@ -645,26 +658,45 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
             s_link[tid] = l;
         }
         __syncthreads();
+        return nt;
+    };
+    for (int t0 = a0; t0 < a1; t0 += kLsTile) {
+        const int nt = stage(t0);
         if (live) {
             double obj, der;
             if (fast) {
 #pragma unroll 2
                 for (int x = g; x < nt; x += G) {
                     ls_terms_q<BETA, SO, true>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
-                    xsum_add(sc, obj, s_big + k * 6, bad);
-                    xsum_add(sd, der, s_big + k * 6 + 3, bad);
+                    xsum_add(sc, obj, odd);
+                    xsum_add(sd, der, odd);
                 }
             } else {
                 for (int x = g; x < nt; x += G) {
                     ls_terms_q<BETA, SO, false>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
-                    xsum_add(sc, obj, s_big + k * 6, bad);
-                    xsum_add(sd, der, s_big + k * 6 + 3, bad);
+                    xsum_add(sc, obj, odd);
+                    xsum_add(sd, der, odd);
                 }
             }
         }
         __syncthreads();
     }
-    if (bad) *err = 1;
+    odd = __syncthreads_or(odd);
+    if (odd) {                                // once more, for the large terms alone
+        for (int x = tid; x < K * 6; x += kWG) s_big[x] = 0;   // (before the first tile's barrier)
+        for (int t0 = a0; t0 < a1; t0 += kLsTile) {
+            const int nt = stage(t0);
+            if (live)
+                for (int x = g; x < nt; x += G) {
+                    double obj, der;
+                    ls_terms_q<BETA, SO, false>(s_link[x], alpha_b, beta, kappa, rbeta1, alpha, obj, der);
+                    xsum_large(s_big + k * 6, obj, bad);
+                    xsum_large(s_big + k * 6 + 3, der, bad);
+                }
+            __syncthreads();
+        }
+        if (bad) *err = 1;
+    }
     s_red[0][tid] = sc.H;
     s_red[1][tid] = sc.L;
     s_red[2][tid] = sd.H;
@@ -684,7 +716,7 @@ __global__ __launch_bounds__(kWG) void k_ls_eval(NetDev net, const int64_t* __re
         XSum x;
         x.H = s_red[2 * w][kk];
         x.L = s_red[2 * w + 1][kk];
-        acc3_add(acc + kk * 6 + 3 * w, xsum_value(x) + acc3_value(s_big + kk * 6 + 3 * w));
+        acc3_add(acc + kk * 6 + 3 * w, xsum_value(x) + (odd ? acc3_value(s_big + kk * 6 + 3 * w) : 0));
     }
     if (!rule.on) return;
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
@@ -777,8 +809,7 @@ __global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restri
     const int inst = net.blk_inst[b];
     if (!st[inst].active) return;
     if (apply_rule && st[inst].converged) return;
-    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;
-    __syncthreads();
+    if (threadIdx.x < 6) s_big[threadIdx.x] = 0;   // seen by all after __syncthreads_or below
     const InstDev I = net.inst[inst];
     const int part = kChunk / (int)gridDim.y;
     const int a0 = net.blk_start[b] + (int)blockIdx.y * part;
@@ -787,21 +818,36 @@ __global__ __launch_bounds__(kWG) void k_obj(NetDev net, const int64_t* __restri
     long long* mine = sums + ((blockIdx.y * gridDim.x + blockIdx.x) % kSumReps) * 6;
     const double alpha = apply_rule ? st[inst].alpha : 0.0;
     XSum s0, s1;
-    int bad = 0;
-    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
-        double obj, der;
+    int odd = 0;
+    auto terms = [&](int a, double& now, double& then) {
+        double der;
         const double F = (double)f[a] * kFxInv;
-        ls_terms(F, F, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-        xsum_add(s0, obj * kSumQ, s_big, bad);
+        ls_terms(F, F, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, now, der);
+        then = 0.0;
         if (apply_rule) {
             const int64_t fn = f[a] + (int64_t)__builtin_rint(alpha * (double)(y[a] - f[a]));
             const double Fn = (double)fn * kFxInv;
-            ls_terms(Fn, Fn, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, obj, der);
-            xsum_add(s1, obj * kSumQ, s_big + 3, bad);
+            ls_terms(Fn, Fn, net.c0[a], net.cap[a], alpha_b, beta, I.kappa, 0.0, net.objective, then, der);
         }
+    };
+    for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
+        double now, then;
+        terms(a, now, then);
+        xsum_add(s0, now * kSumQ, odd);
+        xsum_add(s1, then * kSumQ, odd);
     }
-    if (bad) *err = 1;
-    wg_pair_add(s0, s1, s_big, mine, red);
+    odd = __syncthreads_or(odd);
+    if (odd) {
+        int bad = 0;
+        for (int a = a0 + threadIdx.x; a < a1; a += kWG) {
+            double now, then;
+            terms(a, now, then);
+            xsum_large(s_big, now * kSumQ, bad);
+            xsum_large(s_big + 3, then * kSumQ, bad);
+        }
+        if (bad) *err = 1;
+    }
+    wg_pair_add(s0, s1, odd ? s_big : nullptr, mine, red);
     const unsigned int all = (unsigned int)((I.m + kChunk - 1) / kChunk) * gridDim.y;
     if (!last_of_instance(&ticket[inst], all, &s_last) || threadIdx.x >= 64) return;
     i128 v0, v1;
