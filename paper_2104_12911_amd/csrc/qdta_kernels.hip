@@ -732,7 +732,7 @@ hipError_t launch_ls_eval(hipStream_t s, const NetDev& net, const int64_t* f, co
     // Workgroups per chunk: enough of them to fill the card, each thread with
     // 16 evaluations at least (below that its reduction and atomics weigh more:
     // 256k links at K = 3 took 36 us a pass with 1,000 workgroups, 16 with 250).
-    // A pass over 1.25M links at K = 32: 77 us (307 us with one workgroup per
+    // A pass over 1.25M links at K = 32: 70 us (307 us with one workgroup per
     // chunk, int128 terms and divisions); over 1,520 links, where one chunk
     // used to be one workgroup: 8 us (114 us, and 8 us more for its decision).
     int split = 1;
