@@ -463,3 +463,26 @@ def test_line_search_sums_of_millions_of_large_terms(q, orc):
             s = sums.cpu().numpy().reshape(2, 2)
             assert i128(*s[0]) == m * C[0], call
             assert i128(*s[1]) == m * D[0], call
+
+
+@pytest.mark.parametrize("m", [2, 257, 5000])
+@pytest.mark.parametrize("stop_rule,objective", [(0, 0), (1, 0), (1, 1)])
+def test_gap_and_objective_of_large_terms(q, orc, m, stop_rule, objective):
+    """All demand on one link far beyond its capacity at first: its terms of the gap and the objective are beyond 2^66
+    while the others are ordinary.  Gap, objective, flows and why the solve stopped, against the oracle."""
+    import torch
+    rng = np.random.default_rng(m)
+    net = parallel_links(m, rng, 10.0)
+    o, d, w = orc.demand_legs(np.array([0], np.int32), np.array([1], np.int32), np.array([1e6]))
+    kw = dict(stop_rule=stop_rule, tol=1e-9, max_iter=5, objective=objective)
+    ref = orc.fw_solve(net, o, d, w, keep_history=False, **kw)
+    with q.Context() as ctx:
+        ctx.add(net)
+        ctx.set_demand(0, [0], [1], [1e6], float("inf"))
+        st, _ = ctx.solve(q.default_opts(**kw))
+        f = torch.empty(m, dtype=torch.int64, device="cuda")
+        ctx.get_flows(f)
+    assert np.array_equal(f.cpu().numpy(), ref.f)
+    assert (st[0]["iters"], st[0]["stopped_by"]) == (ref.iters, ref.stopped_by)
+    assert st[0]["gap"] == ref.gap and st[0]["objective"] == ref.objective
+    assert 1e6 * 0.15 * (1e6 / net.cap[np.argmin(net.fftt)]) ** 4 * net.fftt.min() * 2.0 ** 16 > 2.0 ** 66
