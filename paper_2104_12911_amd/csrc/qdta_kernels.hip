@@ -103,7 +103,8 @@ __device__ __forceinline__ i128 get128(const long long* in) {
 // links once more for those alone (xsum_large), adding them to three words of LDS
 // per sum, of which 2^11 such terms need a part, while 2^22 of them, one by one,
 // would overflow the words in memory.  One beyond the int128 range (or not finite)
-// sets bad.  A branch for them in the loop itself cost a pass 5%.
+// sets bad.  (A branch for them in the loop itself: 33.2 us a pass over 255,754
+// links at K = 32 with its atomics in memory, 34.8 in LDS, 32.1 so.)
 struct XSum {
     double H = 0.0, L = 0.0;
 };
